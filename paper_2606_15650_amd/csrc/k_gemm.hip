@@ -20,6 +20,8 @@
 //
 // Epilogues: bias (+ exact scaling of the Q columns by 1/sqrt(d)); bias + GELU;
 // bias + residual added in FP32 and rounded once to the output type.
+#include <math.h>
+
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -153,7 +155,7 @@ struct Staging {
   // fits before its first store; the others load nothing after the bias and
   // go strip by strip, one strip's stores draining under the next's math
   static constexpr int NS = EPI == EPI_RESID ? FIT : 1;
-  static_assert(NS >= 1 && CPR >= 4 && (CPR & (CPR - 1)) == 0, "epilogue staging does not fit");
+  static_assert(NS >= 1 && CPR >= 2 && (CPR & (CPR - 1)) == 0, "epilogue staging does not fit");
   static_assert((NS * 32 * CPR) % 64 == 0, "write-back covers whole waves");
 };
 
@@ -470,6 +472,25 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // has landed and every wave has finished reading tile k-1, whose slot then
 // takes tile k+ST-1.
 //
+// kAhead: the two operands have slots of their own, three for A and two for
+// W, and run at different distances: A two K tiles ahead, W one.  An
+// activation row block is read from beyond the L2 (1-2 us under load) by the
+// few tiles of its row, while a weight panel is shared by every row block in
+// flight and mostly hits it, so the same 160 KB that a two-stage ring leaves
+// a fifth of free cover the longer latency.  Every refill is branch-free
+// inside the MFMA block (the last three tiles are peeled), so its issue hides
+// behind the MFMAs; in the two-stage ring the refill's branch split the block
+// and the eight copies went out with the matrix pipe idle.  At 855,055 rows
+// of the base encoder (256x256x64): QKV 2.99 -> 2.79 ms, output projection
+// 1.17 -> 1.14, FFN1 4.76 -> 4.57, FFN2 3.64 -> 3.42 per launch; one tile
+// alone on the chip, K = 3072: 60.7 -> 54.2 us (a K tile 2690 -> 2380 clocks,
+// 2048 of them MFMA).  At full load the shader clock falls to 1.7-1.85 GHz
+// and a K tile takes 2400-2600 of its clocks, so the matrix pipe is 80-85%
+// busy outside the epilogue and the rest is bound by power.  A layout of 4
+// waves of 128x128 with its accumulators pinned in AGPRs reads a third less
+// LDS but has nothing to run while its one wave per SIMD waits: 3.06 / 1.29 /
+// 4.80 / 3.59 ms with the same ring, not kept.
+//
 // LDS layout: rows of BK elements, unpadded, with the 16-byte chunks of a
 // row XOR-permuted by a function of the row (chunk c of row r sits in slot
 // c ^ swz(r)): a 16-lane group reading the same logical chunk of 16
@@ -477,8 +498,38 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // wave's load instruction fills 1024 contiguous bytes.
 template <int CPR>
 __device__ __forceinline__ int lds_swz(int r) {
-  static_assert(CPR == 4 || CPR == 8, "rows of 64 or 128 bytes");
-  return CPR == 8 ? (r >> 1) & 7 : (r >> 2) & 3;
+  static_assert(CPR == 4 || CPR == 8 || CPR == 16, "rows of 64, 128 or 256 bytes");
+  return CPR == 16 ? r & 15 : CPR == 8 ? (r >> 1) & 7 : (r >> 2) & 3;
+}
+
+// dma16 with the source given as a uniform base, a lane offset and a uniform
+// offset (buffer_load_dwordx4 ... lds): no 64-bit address is formed per lane,
+// so a refill in the main loop is one instruction.  The descriptor covers
+// 2 GiB from the base; the callers' offsets stay inside their matrix.
+__device__ __forceinline__ void buf16(const char* base, uint32_t voff, int soff, char* l) {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0x7fffffff, 0x00027000),
+                                           (__attribute__((address_space(3))) void*)l, 16, voff, soff, 0, 0);
+#endif
+}
+// p, known to be the same for every lane, in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t a = (uint64_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a), hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  return (const char*)(((uint64_t)hi << 32) | lo);
+}
+
+// Waits until at most `left` K tiles (of LPT load instructions each) issued
+// after the wanted one are in flight; MAX of them is the ring's steady state,
+// fewer remain at the end of the K loop, where nothing is issued any more.
+template <int MAX, int LPT>
+__device__ __forceinline__ void wait_tiles(int left) {
+  if constexpr (MAX == 0) {
+    wait_vmcnt<0>();
+  } else {
+    if (left >= MAX) wait_vmcnt<MAX * LPT>();
+    else wait_tiles<MAX - 1, LPT>(left);
+  }
 }
 
 // Instruction order of one k-step (a scheduling region): the next k-step's
@@ -509,6 +560,10 @@ __device__ __forceinline__ void sched_step() {
   if constexpr (NMF > RG + VG) __builtin_amdgcn_sched_group_barrier(0x008, NMF - RG - VG, 0);
 }
 
+// "Ring stages" of the ring that runs A two K tiles and W one K tile ahead
+// (see gemm_dma_kernel).
+constexpr int kAhead = -1;
+
 template <typename TI, typename TO, typename TR, int EPI, int BM, int BN, int BK, int WGM, int WGN, int ST,
           int OCC>
 __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams p) {
@@ -528,9 +583,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
   constexpr int NCH = MF::KPL * (int)sizeof(TI) / 16;  // chunks per lane fragment
   constexpr int CPS = MF::KI / EPC;            // chunks per k-step
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile/waves mismatch");
-  static_assert(TM >= 1 && TN >= 1 && BK % MF::KI == 0 && ST >= 2, "bad tile");
-  static_assert((ST - 1) * LPT < 64, "vmcnt range");
-  constexpr int SMEM = ST * STAGE;
+  static_assert(TM >= 1 && TN >= 1 && BK % MF::KI == 0 && (ST >= 2 || ST == kAhead), "bad tile");
+  static_assert(ST == kAhead || (ST - 1) * LPT < 64, "vmcnt range");
+  constexpr bool AHEAD = ST == kAhead;
+  constexpr int SMEM = AHEAD ? 3 * A_BYTES + 2 * (STAGE - A_BYTES) : ST * STAGE;
   static_assert(SMEM <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
   __shared__ __align__(1024) char smem[SMEM];
 
@@ -613,14 +669,100 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int KT = K / BK;
-  // The ring always holds ST tiles in flight or resident; with more than two
-  // stages, refills past the last tile re-read tile KT-1 (valid memory, never
-  // multiplied), so the wait counts stay constants.
+  // The ring holds up to ST tiles in flight or resident.
+  if constexpr (!AHEAD) {
 #pragma unroll
-  for (int s = 0; s < ST; ++s) issue(min(s, KT - 1), s);
-  wait_vmcnt<(ST - 1) * LPT>();
-  __builtin_amdgcn_s_barrier();
+    for (int s = 0; s < ST; ++s)
+      if (s < KT) issue(s, s);
+    wait_tiles<ST - 1, LPT>(KT - 1);
+    __builtin_amdgcn_s_barrier();
+  }
 
+  if constexpr (AHEAD) {
+    // B tiles run one tile ahead in two slots, A tiles two ahead in three:
+    // during tile kt's last k-step its two slots are free and take B of tile
+    // kt+2 and A of tile kt+3.
+    static_assert(NKS % 2 == 0, "the fragment buffers of a k-step are the same in every tile");
+    constexpr int B0 = 3 * A_BYTES, B_BYTES = BN * ROWB;
+    const char* const ua = uniform_ptr(abase);
+    const char* const ub = uniform_ptr(bbase);
+    auto issue_a = [&](int kt, int slot) {
+#pragma unroll
+      for (int i = 0; i < A_INS; ++i)
+        buf16(ua, ga[i], kt * BK * (int)sizeof(TI), smem + slot * A_BYTES + (wave * A_INS + i) * 1024);
+    };
+    auto issue_b = [&](int kt, int slot) {
+#pragma unroll
+      for (int i = 0; i < B_INS; ++i)
+        buf16(ub, gb[i], kt * BK * (int)sizeof(TI), smem + B0 + slot * B_BYTES + (wave * B_INS + i) * 1024);
+    };
+    issue_b(0, 0);
+    issue_a(0, 0);
+    if (KT > 2) {
+      issue_b(1, 1);
+      issue_a(1, 1);
+      issue_a(2, 2);
+      wait_vmcnt<2 * A_INS + B_INS>();
+    } else if (KT > 1) {
+      issue_b(1, 1);
+      issue_a(1, 1);
+      wait_vmcnt<A_INS + B_INS>();
+    } else {
+      wait_vmcnt<0>();
+    }
+    __builtin_amdgcn_s_barrier();
+    frag fa[2][TM], fb[2][TN];
+    auto read_a = [&](int set, int slot, int ks) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[set][i] = rdfrag(smem + slot * A_BYTES, aoff[ks], i);
+    };
+    auto read_b = [&](int set, int slot, int ks) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[set][j] = rdfrag(smem + B0 - A_BYTES + slot * B_BYTES, boff[ks], j);
+    };
+    read_a(0, 0, 0);
+    read_b(0, 0, 0);
+    int sa = 0, sb = 0;  // this tile's slots
+    // one tile with LEFT tiles after it (3: three or more)
+    auto body = [&](int kt, auto leftc) {
+      constexpr int LEFT = decltype(leftc)::value;
+      constexpr int NRD = (TM + TN) * NCH;
+      const int na = sa == 2 ? 0 : sa + 1;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+        const int cur = ks & 1;
+        if (ks + 1 < NKS) {
+          read_a(cur ^ 1, sa, ks + 1 < NKS ? ks + 1 : 0);
+          read_b(cur ^ 1, sb, ks + 1 < NKS ? ks + 1 : 0);
+        } else if constexpr (LEFT > 0) {
+          // this wave's reads of the tile have returned and tile kt+1 has
+          // landed (of the later issues only A of kt+2 may be in flight);
+          // after the barrier both hold for every wave
+          __builtin_amdgcn_sched_barrier(0);
+          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) (vmcnt, expcnt at maxima)
+          wait_vmcnt<(LEFT > 1 ? A_INS : 0)>();
+          __builtin_amdgcn_s_barrier();
+          read_a(cur ^ 1, na, 0);
+          read_b(cur ^ 1, sb ^ 1, 0);
+          if constexpr (LEFT > 1) issue_b(kt + 2, sb);
+          if constexpr (LEFT > 2) issue_a(kt + 3, sa);
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fb[cur][j], fa[cur][i], acc[i][j]);
+        if (ks + 1 < NKS) sched_step<TM * TN, NRD, 0>();
+        else sched_step<TM * TN, (LEFT > 0 ? NRD : 0), (LEFT > 2 ? LPT : LEFT > 1 ? B_INS : 0)>();
+      }
+      sa = na;
+      sb ^= 1;
+    };
+    int kt = 0;
+    for (; kt + 3 < KT; ++kt) body(kt, std::integral_constant<int, 3>());
+    if (kt + 2 < KT) body(kt++, std::integral_constant<int, 2>());
+    if (kt + 1 < KT) body(kt++, std::integral_constant<int, 1>());
+    body(kt, std::integral_constant<int, 0>());
+  } else {
   // Fragments are double-buffered across k-steps, also across tiles: the
   // buffer of a k-step is the parity of its global k-step index, a
   // compile-time value once the tile loop is unrolled by two.
@@ -653,12 +795,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
         // wait, covering the latency of the reads it waits for.)
         __builtin_amdgcn_sched_barrier(0);
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) (vmcnt, expcnt at maxima)
-        wait_vmcnt<(ST - 2) * LPT>();
+        wait_tiles<ST - 2, LPT>(KT - 2 - kt);
         __builtin_amdgcn_s_barrier();
-        // past the last tile: a two-stage ring waits for every load, so the
-        // refill is left out (nothing to land before the epilogue); deeper
-        // rings re-read tile KT-1 to keep their wait counts constant
-        if (ST > 2 || kt + ST < KT) issue(min(kt + ST, KT - 1), stage);
+        if (kt + ST < KT) issue(kt + ST, stage);
         const char* nbase = smem + nstage * STAGE;
 #pragma unroll
         for (int i = 0; i < TM; ++i) fa[cur ^ 1][i] = rdfrag(nbase, aoff[0], i);
@@ -681,10 +820,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
     tile_body(kt, std::integral_constant<int, 0>());
     if (kt + 1 < KT) tile_body(kt + 1, std::integral_constant<int, 1>());
   }
-  // the refills issued by the last tiles must land before the staging below
-  // reuses the ring
-  wait_vmcnt<0>();
-  // and every wave must have finished reading it
+  }
+  // no refill is in flight (the last tiles issue none); every wave must have
+  // finished reading the ring before the staging below reuses it
   __syncthreads();
   epilogue<TO, TR, EPI, TM, TN, NW, SMEM>(p, acc, smem, wave, lane, m0 + wm * WTM, n0 + wn * WTN);
 }
@@ -700,7 +838,7 @@ struct Cfg {
 constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, int in_bytes, int out_bytes, int epi) {
   const int tn = bn / wgn / 32;
   if ((epi == EPI_ROPE || epi == EPI_GEGLU) && tn % 2 != 0) return false;
-  const int smem = st == 0 ? 2 * (bm + bn) * (bk + 16 / in_bytes) * in_bytes : st * (bm + bn) * bk * in_bytes;
+  const int smem = st == kAhead ? (3 * bm + 2 * bn) * bk * in_bytes : st == 0 ? 2 * (bm + bn) * (bk + 16 / in_bytes) * in_bytes : st * (bm + bn) * bk * in_bytes;
   const int otn = epi == EPI_GEGLU ? tn / 2 : tn;
   return smem >= wgm * wgn * 32 * otn * 32 * out_bytes;
 }
@@ -720,7 +858,15 @@ constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, in
   X(8, 256, 256, 64, 4, 2, 2, 1, "bf16_256x256x64_w4x2_s2")    \
   X(9, 256, 256, 32, 4, 2, 4, 1, "bf16_256x256x32_w4x2_s4")    \
   X(10, 256, 128, 32, 4, 2, 4, 1, "bf16_256x128x32_w4x2_s4")    \
-  X(11, 256, 256, 64, 2, 4, 2, 1, "bf16_256x256x64_w2x4_s2")
+  X(11, 256, 256, 64, 2, 4, kAhead, 1, "bf16_256x256x64_w2x4_a") \
+  X(12, 192, 256, 64, 2, 4, kAhead, 1, "bf16_192x256x64_w2x4_a") \
+  X(13, 128, 256, 64, 2, 4, kAhead, 1, "bf16_128x256x64_w2x4_a") \
+  X(14, 128, 128, 64, 2, 2, kAhead, 2, "bf16_128x128x64_w2x2_a") \
+  X(15, 64, 128, 64, 2, 2, kAhead, 2, "bf16_64x128x64_w2x2_a")   \
+  X(16, 64, 64, 64, 2, 2, kAhead, 4, "bf16_64x64x64_w2x2_a")     \
+  X(17, 64, 64, 128, 2, 2, kAhead, 2, "bf16_64x64x128_w2x2_a")   \
+  X(18, 32, 64, 128, 1, 2, kAhead, 2, "bf16_32x64x128_w1x2_a")   \
+  X(19, 64, 64, 64, 2, 1, kAhead, 2, "bf16_64x64x64_w2x1_a")
 #define ANON_F32_CFGS(X)                                 \
   X(0, 128, 128, 32, 2, 2, 0, 2, "f32_128x128x32_w2x2") \
   X(1, 64, 64, 32, 2, 2, 0, 2, "f32_64x64x32_w2x2")     \
@@ -734,7 +880,11 @@ constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, in
   X(4, 256, 128, 64, 4, 2, 3, 2, "fp8_256x128x64_w4x2_s3")  \
   X(5, 128, 256, 64, 2, 4, 3, 2, "fp8_128x256x64_w2x4_s3")  \
   X(6, 256, 256, 64, 4, 2, 4, 1, "fp8_256x256x64_w4x2_s4")  \
-  X(7, 256, 256, 128, 2, 4, 2, 1, "fp8_256x256x128_w2x4_s2")
+  X(7, 256, 256, 128, 2, 4, kAhead, 1, "fp8_256x256x128_w2x4_a") \
+  X(8, 128, 256, 128, 2, 4, kAhead, 1, "fp8_128x256x128_w2x4_a") \
+  X(9, 128, 128, 128, 2, 2, kAhead, 2, "fp8_128x128x128_w2x2_a") \
+  X(10, 64, 128, 128, 2, 2, kAhead, 2, "fp8_64x128x128_w2x2_a")  \
+  X(11, 64, 64, 128, 2, 2, kAhead, 4, "fp8_64x64x128_w2x2_a")
 
 #define ANON_CFG_ROW(i, bm, bn, bk, wgm, wgn, st, occ, name) {bm, bn, bk, wgm, wgn, st, occ, name},
 const Cfg kCfgBF16[] = {ANON_BF16_CFGS(ANON_CFG_ROW)};
@@ -855,12 +1005,74 @@ bool gemm_config_serves(const GemmParams& g, int config) {
   return staging_fits(k.bm, k.bn, k.bk, k.wgm, k.wgn, k.st, elem_bytes(g.in), elem_bytes(g.out), g.epi);
 }
 
+// Estimated time (us) of the tiles worth choosing, fitted to launches of the
+// base and large encoders' GEMMs at 16 to 50,000 rows on all 256 CUs (bf16 K
+// 768 and 3072, FP8 K 1024 and 4096).  With kt = 128-byte steps of K:
+//   f0 + f1 kt  a launch whose tiles all start at once (latency of one tile)
+//   g0 + g1 kt  each further tile per CU, all CUs busy
+//   gelu        added to both by the GELU epilogue
+// Whole: tiles of one workgroup per CU, so a last, partly filled round costs
+// between the first and the second figure.  Pair: at most two per CU, whose
+// second tile costs a round as soon as one CU has it.  Fine: tiles so small
+// that the CUs' loads even out.
+enum TileFill { kWhole, kPair, kFine };
+struct TileCost {
+  int config;
+  float f0, f1, g0, g1, gelu;
+  TileFill fill;
+};
+const TileCost kCostBF16[] = {
+    {11, 5.1f, 1.06f, 5.3f, 1.6f, 5.0f, kWhole},   {12, 3.8f, 0.9f, 4.0f, 1.35f, 3.8f, kWhole},
+    {13, 1.4f, 0.825f, 2.7f, 1.03f, 3.0f, kWhole}, {14, 2.7f, 0.506f, 0.7f, 0.53f, 1.0f, kPair},
+    {15, 0.6f, 0.508f, 1.27f, 0.303f, 0.6f, kPair}, {16, 0.5f, 0.406f, 0.3f, 0.19f, 0.4f, kFine},
+    {17, 2.5f, 0.261f, 0.65f, 0.2f, 0.4f, kFine},  {18, 2.9f, 0.2f, 0.96f, 0.134f, 0.4f, kFine},
+    {19, 0.5f, 0.46f, 0.3f, 0.25f, 0.4f, kFine},
+};
+const TileCost kCostFP8[] = {
+    {7, 6.3f, 1.02f, 8.0f, 1.25f, 9.0f, kWhole},   {8, 2.0f, 0.875f, 3.2f, 0.9f, 3.5f, kWhole},
+    {9, 3.1f, 0.53f, 0.7f, 0.54f, 1.1f, kPair},    {10, 3.7f, 0.25f, 0.7f, 0.34f, 0.5f, kFine},
+    {11, 3.1f, 0.19f, 0.34f, 0.2f, 0.3f, kFine},
+};
+
+static float tile_cost(const TileCost& t, const Cfg& c, const GemmParams& g) {
+  const float kt = (float)g.K * elem_bytes(g.in) / 128.f;
+  const float ge = g.epi == EPI_GELU || g.epi == EPI_GEGLU ? t.gelu : 0.f;
+  const float one = t.f0 + t.f1 * kt + ge, more = t.g0 + t.g1 * kt + ge;
+  const float r = (float)(((int64_t)g.M + c.bm - 1) / c.bm * (g.N / c.bn)) / 256.f;  // tiles per CU
+  if (t.fill == kWhole) {
+    const float full = floorf(r);
+    return full * more + (r > full ? one + (more - one) * (r - full) : 0.f);
+  }
+  if (r <= 1.f) return one;
+  if (t.fill == kFine) return one + (r - 1.f) * more;
+  return one + (r < 2.f ? 1.f : ceilf(2.f * r) * 0.5f - 1.f) * more;
+}
+
 int default_gemm_config(const GemmParams& g) {
-  // the preferred tile of the type if it serves the shape and epilogue,
-  // else the first one that does
+  // The cheapest tile for this many rows by the estimate above, else the
+  // first configuration that serves the shape and epilogue.  One tile shape
+  // for every size leaves most CUs idle on a small batch: with 256x256 tiles
+  // alone, a record of 137 tokens runs its four GEMMs of a layer on 3 to 12
+  // workgroups (20, 20, 25 and 61 us on the base shapes); the tiles chosen
+  // here take 5.3, 5.4, 5.8 and 12.1 us, and at 2,094 rows 13, 7, 17 and 22
+  // instead of 21, 21, 27 and 63.  At 8,192 rows and above the choice is
+  // worth 0-25% (the last round of 256x256 tiles), from 21,608 rows on it is
+  // mostly the 256x256 tile.
   const int n = gemm_num_configs(g.in);
-  const int pref = g.in == ET_BF16 ? 11 : (g.in == ET_FP8 ? 7 : 0);
-  if (gemm_config_serves(g, pref)) return pref;
+  int nc;
+  const Cfg* cs = cfgs(g.in, &nc);
+  int best = -1;
+  float best_t = 0.f;
+  auto consider = [&](const TileCost& t) {
+    if (!gemm_config_serves(g, t.config)) return;
+    const float us = tile_cost(t, cs[t.config], g);
+    if (best < 0 || us < best_t) best = t.config, best_t = us;
+  };
+  if (g.in == ET_BF16)
+    for (const TileCost& t : kCostBF16) consider(t);
+  else if (g.in == ET_FP8)
+    for (const TileCost& t : kCostFP8) consider(t);
+  if (best >= 0) return best;
   for (int c = 0; c < n; ++c)
     if (gemm_config_serves(g, c)) return c;
   return -1;
