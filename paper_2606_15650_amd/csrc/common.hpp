@@ -79,6 +79,31 @@ __device__ __forceinline__ T wave_max(T v) {
   return v;
 }
 
+// Largest b in [0, B) with cu[b] <= p (0 if there is none), by the whole
+// workgroup: every thread samples one boundary per round, so 65,536 records
+// take two dependent loads with 256 threads instead of sixteen.  All threads
+// call it with the same arguments and get the same result; a malformed cu
+// gives some index of [0, B).
+template <typename T>
+__device__ __forceinline__ int wg_find_record(const T* cu, int B, T p) {
+  const int nt = blockDim.x, tid = threadIdx.x;
+  int lo = 0, n = B;
+  while (n > 1) {
+    const int step = (n + nt - 1) / nt, at = tid * step;
+    const int cnt = __syncthreads_count(at < n && (at == 0 || cu[lo + at] <= p));
+    lo += (cnt - 1) * step;
+    n = min(step, n - (cnt - 1) * step);
+  }
+  return lo;
+}
+
+// 16 bytes from an address of any alignment
+__device__ __forceinline__ uint4 load16(const uint8_t* p) {
+  uint4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+
 // 16 bytes per lane from global memory straight into LDS
 // (global_load_lds_dwordx4): lane i's bytes land at l + 16 i, where l is
 // the same for the whole wave.

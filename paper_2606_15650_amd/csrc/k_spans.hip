@@ -4,10 +4,19 @@
 // Decoding is token-parallel.  A token opens a span iff its label is not O
 // and it is B-t, or it is the first token of its record, or the previous
 // token's type differs (so an I-t without an open span of type t opens one).
-// An exclusive scan of these flags gives every span its index in record-major
-// order; the opening token then walks forward over the following I-t tokens
-// of its record to find the span's last token.  Every token is visited by at
-// most one walk, so the work is O(T).
+// The flags are kept as bits with their ranks, 4096 tokens to a workgroup;
+// the workgroups' counts give every span its index in record-major order, and
+// the opening token then walks forward over the following I-t tokens of its
+// record (labels staged in LDS) to find the span's last token.  Every token
+// is visited by at most one walk, so the work is O(T).
+//
+// Bound by latency and launches: a call moves 1.5 bytes per token beyond the
+// spans themselves (labels read twice, a quarter byte of flags and ranks),
+// and takes two launches where an int flag per token, a three-kernel scan of
+// them and a record search per labelled token took six.  978,000 tokens in
+// 4096 records: 38 -> 14 us (6 and 8 in the two kernels).
+#include <limits.h>
+
 #include "kernels.hpp"
 
 namespace anon {
@@ -107,15 +116,35 @@ void exclusive_scan(const T* in, T* out, int64_t n, void* temp, hipStream_t s) {
     hipLaunchKernelGGL(scan_apply_kernel<T>, dim3(nparts), dim3(kScanThreads), 0, s, in, n, (const T*)part, out);
 }
 
-__device__ __forceinline__ int find_record(const int* cu, int B, int t) {
-  int lo = 0, hi = B - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (cu[mid] <= t) lo = mid;
-    else hi = mid - 1;
+// Counts of consecutive tiles -> exclusive prefix in place; tiles are few
+// (one per 4096 tokens or bytes), so one workgroup does it, a thread summing
+// a run of counts.  The total goes to part[n].
+__global__ __launch_bounds__(1024) void scan_counts_kernel(int* __restrict__ part, int n) {
+  __shared__ int sh[1024];
+  const int tid = threadIdx.x;
+  const int per = ((n + 1023) / 1024 + 3) & ~3;
+  const int a = min(n, tid * per), b = min(n, a + per);
+  int s = 0;
+  for (int i = a; i < b; ++i) s += part[i];
+  sh[tid] = s;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int x = tid >= o ? sh[tid - o] : 0;
+    __syncthreads();
+    sh[tid] += x;
+    __syncthreads();
   }
-  return lo;
+  int run = sh[tid] - s;
+  for (int i = a; i < b; ++i) {
+    const int v = part[i];
+    part[i] = run;
+    run += v;
+  }
+  if (tid == 1023) part[n] = sh[1023];
 }
+
+constexpr int kTile = 4096;           // tokens per workgroup, 16 per thread
+constexpr int kDirectTiles = 4096;    // up to here the writers sum the tiles before theirs themselves
 
 __device__ __forceinline__ int clean_label(int lab, int n_types, uint32_t* err) {
   if (lab > 2 * n_types) {
@@ -125,55 +154,167 @@ __device__ __forceinline__ int clean_label(int lab, int n_types, uint32_t* err) 
   return lab;
 }
 
-__global__ void bio_flags_kernel(const uint8_t* __restrict__ labels, const int* __restrict__ cu, int B, int T,
-                                 int n_types, int* __restrict__ flags, uint32_t* err) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
-  const int lab = clean_label(labels[t], n_types, err);
-  int f = 0;
-  if (lab != 0) {
-    const int b = find_record(cu, B, t);
-    const int typ = (lab + 1) >> 1;
-    bool open = (lab & 1) || t == cu[b] || t == 0;
-    if (!open) {
-      const int pl = labels[t - 1];
-      const int ptyp = pl > 2 * n_types ? 0 : (pl + 1) >> 1;
-      open = ptyp != typ;
-    }
-    f = open ? 1 : 0;
+// Exclusive sum of v over the workgroup's 256 threads and its total.
+__device__ __forceinline__ int wg_exclusive(int v, int* total) {
+  __shared__ int ws[4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int x = v;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
   }
-  flags[t] = f;
+  if (lane == 63) ws[wave] = x;
+  __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) base += ws[w];
+    all += ws[w];
+  }
+  *total = all;
+  __syncthreads();
+  return base + x - v;
 }
 
-__global__ void bio_write_kernel(const uint8_t* __restrict__ labels, const int* __restrict__ tok_off,
-                                 const int* __restrict__ cu, int B, int T, int n_types, const int* __restrict__ flags,
-                                 const int* __restrict__ excl, anon_span* __restrict__ spans, int span_cap) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T || !flags[t]) return;
-  const int idx = excl[t];
-  if (idx >= span_cap) return;
-  const int b = find_record(cu, B, t);
-  const int end_tok = min(cu[b + 1], T);
-  const int lab = labels[t];
-  const int typ = (lab + 1) >> 1;
-  const int cont = 2 * typ;  // I-typ
-  int e = t;
-  while (e + 1 < end_tok && labels[e + 1] == cont) ++e;
-  anon_span sp;
-  sp.record = b;
-  sp.type = typ;
-  sp.begin = tok_off[2 * t];
-  sp.end = tok_off[2 * e + 1];
-  spans[idx] = sp;
+// 16 labels from t0 on (zeros past T), byte i in bits 8 (i mod 4) of word i/4
+__device__ __forceinline__ uint4 load_labels(const uint8_t* labels, int t0, int T) {
+  if (T - t0 >= 16) return load16(labels + t0);
+  uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (i < T - t0) w[i >> 2] |= (uint32_t)labels[t0 + i] << (8 * (i & 3));
+  return uint4{w[0], w[1], w[2], w[3]};
 }
 
-__global__ void cu_spans_kernel(const int* __restrict__ cu, int B, int T, const int* __restrict__ excl,
-                                int* __restrict__ cu_spans, int span_cap, uint32_t* err) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b > B) return;
-  const int t = min(max(cu[b], 0), T);
-  cu_spans[b] = excl[t];
-  if (b == B && excl[T] > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
+// Opening flags of a tile of tokens: 16 bits per thread, their rank within
+// the tile, and the tile's count.  A token's record start matters only where
+// an I-t follows a token of type t, and is looked up in the tile's own record
+// boundaries (a bitmap in LDS), so no token searches the boundary array.
+__global__ __launch_bounds__(256) void bio_flags_kernel(const uint8_t* __restrict__ labels,
+                                                        const int* __restrict__ cu, int B, int T, int n_types,
+                                                        uint16_t* __restrict__ bits, uint16_t* __restrict__ rank,
+                                                        int* __restrict__ counts, int* __restrict__ rec0,
+                                                        uint32_t* err) {
+  __shared__ uint32_t starts[kTile / 32];
+  const int tid = threadIdx.x, base = blockIdx.x * kTile, last = base + kTile - 1, t0 = base + tid * 16;
+  const uint4 lv = load_labels(labels, t0, T);
+  const uint32_t l[4] = {lv.x, lv.y, lv.z, lv.w};
+  int prev = t0 > 0 && t0 < T ? labels[t0 - 1] : 0;
+  if (tid < kTile / 32) starts[tid] = 0;
+  // record boundaries inside the tile, from the last one at or before it
+  const int first = wg_find_record(cu, B, base);
+  for (int b = first;; b += 256) {
+    __syncthreads();
+    const int i = b + tid;
+    const int c = i <= B ? cu[i] : INT_MAX;
+    if (c >= base && c <= last) atomicOr(&starts[(c - base) >> 5], 1u << ((c - base) & 31));
+    if (!__syncthreads_or(tid == 255 && i < B && c <= last)) break;
+  }
+  const uint32_t rs = starts[tid >> 1] >> ((tid & 1) * 16);
+  uint32_t f = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int raw = (l[i >> 2] >> (8 * (i & 3))) & 0xff;
+    const int lab = clean_label(raw, n_types, err), typ = (lab + 1) >> 1;
+    const int ptyp = prev > 2 * n_types ? 0 : (prev + 1) >> 1;
+    if (lab != 0 && ((lab & 1) || t0 + i == 0 || ((rs >> i) & 1) || ptyp != typ)) f |= 1u << i;
+    prev = raw;
+  }
+  int total;
+  const int r = wg_exclusive(__popc(f), &total);
+  if (t0 < T) {
+    bits[t0 >> 4] = (uint16_t)f;
+    rank[t0 >> 4] = (uint16_t)r;
+  }
+  if (tid == 0) {
+    counts[blockIdx.x] = total;
+    rec0[blockIdx.x] = first;
+  }
+}
+
+// Spans of a tile (blocks below n_tiles) and the record offsets (the blocks
+// above).  With SCANNED, counts already holds the exclusive prefix over the
+// tiles; else each block sums the counts before its tile (at most
+// kDirectTiles of them), which saves a launch.
+template <bool SCANNED>
+__global__ __launch_bounds__(256) void bio_write_kernel(const uint8_t* __restrict__ labels,
+                                                        const int* __restrict__ tok_off, const int* __restrict__ cu,
+                                                        int B, int T, int n_tiles, const uint16_t* __restrict__ bits,
+                                                        const uint16_t* __restrict__ rank,
+                                                        const int* __restrict__ counts, const int* __restrict__ rec0,
+                                                        anon_span* __restrict__ spans, int span_cap,
+                                                        int* __restrict__ cu_spans, uint32_t* err) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= n_tiles) {
+    // cu_spans[b]: spans opened before the record's first token
+    __shared__ int pre[SCANNED ? 1 : kDirectTiles + 1];
+    if constexpr (!SCANNED) {
+      constexpr int PER = kDirectTiles / 256;
+      int c[PER], s = 0;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        const int k = tid * PER + i;
+        c[i] = k < n_tiles ? counts[k] : 0;
+        s += c[i];
+      }
+      int total;
+      s = wg_exclusive(s, &total);
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        pre[tid * PER + i] = s;
+        s += c[i];
+      }
+      if (tid == 0) pre[kDirectTiles] = total;
+      __syncthreads();
+    }
+    const int b = (blockIdx.x - n_tiles) * 256 + tid;
+    if (b > B) return;
+    const int t = min(max(cu[b], 0), T), tile = t / kTile;
+    int n;
+    if constexpr (SCANNED) n = counts[min(tile, n_tiles)];
+    else n = pre[min(tile, kDirectTiles)];
+    if (t < T) n += rank[t >> 4] + __popc(bits[t >> 4] & ((1u << (t & 15)) - 1));
+    else if (tile < n_tiles) n = SCANNED ? counts[tile + 1] : pre[tile + 1];
+    cu_spans[b] = n;
+    if (b == B && (SCANNED ? counts[n_tiles] : pre[n_tiles]) > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
+    return;
+  }
+  const int base = blockIdx.x * kTile, last = min(base + kTile - 1, T - 1), t0 = base + tid * 16;
+  __shared__ __align__(16) uint8_t lab[kTile];
+  uint32_t f = 0;
+  int idx = 0;
+  if (t0 < T) {
+    f = bits[t0 >> 4];
+    idx = rank[t0 >> 4];
+  }
+  *(uint4*)(lab + tid * 16) = load_labels(labels, t0, T);
+  if constexpr (SCANNED) {
+    idx += counts[blockIdx.x];
+  } else {
+    int s = 0, total;
+    for (int k = tid; k < (int)blockIdx.x; k += 256) s += counts[k];
+    wg_exclusive(s, &total);
+    idx += total;
+  }
+  // the tile's records lie between its first and the next tile's first
+  const int r0 = rec0[blockIdx.x], r1 = (int)blockIdx.x + 1 < n_tiles ? rec0[blockIdx.x + 1] : B - 1;
+  __syncthreads();
+  for (; f; f &= f - 1, ++idx) {
+    if (idx >= span_cap) break;
+    const int t = t0 + __ffs(f) - 1;
+    int a = r0, c = r1;  // the record: largest index of [r0, r1] with cu <= t
+    while (a < c) {
+      const int m = (a + c + 1) >> 1;
+      if (cu[m] <= t) a = m;
+      else c = m - 1;
+    }
+    const int end_tok = min(cu[a + 1], T);
+    const int typ = (lab[t - base] + 1) >> 1, cont = 2 * typ;  // I-typ continues the span
+    int e = t;
+    while (e + 1 < end_tok && (e < last ? lab[e + 1 - base] : labels[e + 1]) == cont) ++e;
+    spans[idx] = anon_span{a, typ, tok_off[2 * t], tok_off[2 * e + 1]};
+  }
 }
 
 }  // namespace
@@ -187,21 +328,33 @@ void launch_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void*
   exclusive_scan<int64_t>(in, out, n, temp, s);
 }
 
-void launch_bio_flags(const uint8_t* labels, const int* cu_seqlens, int B, int T, int n_types, int* flags,
-                      uint32_t* err, hipStream_t s) {
-  if (T <= 0) return;
-  hipLaunchKernelGGL(bio_flags_kernel, dim3(ceil_div(T, 256)), dim3(256), 0, s, labels, cu_seqlens, B, T, n_types,
-                     flags, err);
+size_t bio_layout(int T, Carver& k, BioBuffers& w) {
+  const int tiles = ceil_div(T, kTile);
+  w.bits = k.take<uint16_t>((size_t)tiles * (kTile / 16));
+  w.rank = k.take<uint16_t>((size_t)tiles * (kTile / 16));
+  w.counts = k.take<int>(tiles + 1);
+  w.rec0 = k.take<int>(tiles + 1);
+  return k.used;
 }
 
-void launch_bio_write(const uint8_t* labels, const int* tok_off, const int* cu_seqlens, int B, int T, int n_types,
-                      const int* flags, const int* excl, anon_span* spans, int span_cap, int* cu_spans,
-                      uint32_t* err, hipStream_t s) {
-  if (T > 0)
-    hipLaunchKernelGGL(bio_write_kernel, dim3(ceil_div(T, 256)), dim3(256), 0, s, labels, tok_off, cu_seqlens, B, T,
-                       n_types, flags, excl, spans, span_cap);
-  hipLaunchKernelGGL(cu_spans_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, s, cu_seqlens, B, T, excl, cu_spans,
-                     span_cap, err);
+void launch_scan_counts(int* counts, int n, hipStream_t s) {
+  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, s, counts, n);
+}
+
+void launch_bio(const uint8_t* labels, const int* tok_off, const int* cu_seqlens, int B, int T, int n_types,
+                const BioBuffers& w, anon_span* spans, int span_cap, int* cu_spans, uint32_t* err, hipStream_t s) {
+  const int tiles = ceil_div(T, kTile), grid = tiles + ceil_div(B + 1, 256);
+  if (tiles > 0)
+    hipLaunchKernelGGL(bio_flags_kernel, dim3(tiles), dim3(256), 0, s, labels, cu_seqlens, B, T, n_types, w.bits,
+                       w.rank, w.counts, w.rec0, err);
+  if (tiles > kDirectTiles) {
+    launch_scan_counts(w.counts, tiles, s);
+    hipLaunchKernelGGL(bio_write_kernel<true>, dim3(grid), dim3(256), 0, s, labels, tok_off, cu_seqlens, B, T, tiles,
+                       w.bits, w.rank, w.counts, w.rec0, spans, span_cap, cu_spans, err);
+  } else {
+    hipLaunchKernelGGL(bio_write_kernel<false>, dim3(grid), dim3(256), 0, s, labels, tok_off, cu_seqlens, B, T,
+                       tiles, w.bits, w.rank, w.counts, w.rec0, spans, span_cap, cu_spans, err);
+  }
 }
 
 }  // namespace anon

@@ -94,11 +94,16 @@ void launch_exclusive_scan_i32(const int* in, int* out, int64_t n, void* temp, h
 void launch_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void* temp, hipStream_t s);
 
 // ---- spans ----------------------------------------------------------------
-void launch_bio_flags(const uint8_t* labels, const int* cu_seqlens, int B, int T, int n_types, int* flags,
-                      uint32_t* err, hipStream_t s);
-void launch_bio_write(const uint8_t* labels, const int* tok_off, const int* cu_seqlens, int B, int T, int n_types,
-                      const int* flags, const int* excl, anon_span* spans, int span_cap, int* cu_spans,
-                      uint32_t* err, hipStream_t s);
+struct BioBuffers {
+  uint16_t *bits, *rank;  // per 16 tokens: opening flags, spans opened before them in the tile
+  int *counts, *rec0;     // per tile: spans opened, the record of its first token
+};
+size_t bio_layout(int T, Carver& k, BioBuffers& w);
+// Spans of a labelled batch: spans, cu_spans and the error bits of decode_spans.
+void launch_bio(const uint8_t* labels, const int* tok_off, const int* cu_seqlens, int B, int T, int n_types,
+                const BioBuffers& w, anon_span* spans, int span_cap, int* cu_spans, uint32_t* err, hipStream_t s);
+// counts[0 .. n) -> their exclusive prefix, counts[n] = the total.
+void launch_scan_counts(int* counts, int n, hipStream_t s);
 
 // ---- pseudonyms -----------------------------------------------------------
 struct PcacheDev {

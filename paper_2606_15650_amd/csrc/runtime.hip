@@ -1118,19 +1118,11 @@ anon_status ner_forward_windowed(anon_model* m, const int32_t* d_ids, const int3
 }
 
 // --------------------------------------------------------------- spans ----
-static void dec_layout(int T, Carver& k, int** flags, int** excl, void** temp) {
-  *flags = k.take<int>(std::max(T, 1));
-  *excl = k.take<int>(T + 1);
-  *temp = k.take<uint8_t>(scan_temp_bytes(T));
-}
-
 anon_status anon_decode_workspace_size(int32_t T, int32_t B, size_t* bytes) {
   if (!bytes || T < 0 || B < 0) return set_error(ANON_EINVAL, "bad arguments");
   Carver k(nullptr, SIZE_MAX);
-  int *f, *e;
-  void* t;
-  dec_layout(T, k, &f, &e, &t);
-  *bytes = k.used + 256;
+  BioBuffers w;
+  *bytes = bio_layout(T, k, w) + 256;
   return ANON_OK;
 }
 
@@ -1145,9 +1137,8 @@ anon_status decode_spans(const uint8_t* d_labels, const int32_t* d_tok_off, cons
   if (T > 0 && (!d_labels || !d_tok_off)) return set_error(ANON_EINVAL, "labels/tok_off is NULL");
   if (span_cap > 0 && !d_spans) return set_error(ANON_EINVAL, "spans is NULL");
   Carver k(d_workspace, ws_bytes);
-  int *flags, *excl;
-  void* temp;
-  dec_layout(T, k, &flags, &excl, &temp);
+  BioBuffers w;
+  bio_layout(T, k, w);
   if (!d_workspace || !k.ok()) return set_error(ANON_ECAPACITY, "workspace too small");
   hipStream_t s = (hipStream_t)stream;
   uint32_t* err = error_word_ptr();
@@ -1156,10 +1147,7 @@ anon_status decode_spans(const uint8_t* d_labels, const int32_t* d_tok_off, cons
     ANON_HIP_CHECK(hipGetLastError());
     return ANON_OK;
   }
-  launch_bio_flags(d_labels, d_cu_seqlens, B, T, n_types, flags, err, s);
-  launch_exclusive_scan_i32(flags, excl, T, temp, s);
-  launch_bio_write(d_labels, d_tok_off, d_cu_seqlens, B, T, n_types, flags, excl, d_spans, span_cap, d_cu_spans,
-                   err, s);
+  launch_bio(d_labels, d_tok_off, d_cu_seqlens, B, T, n_types, w, d_spans, span_cap, d_cu_spans, err, s);
   ANON_HIP_CHECK(hipGetLastError());
   return ANON_OK;
 }
