@@ -27,14 +27,26 @@
 // (transitively; spans that only touch stay apart), typed by its longest
 // member, then NER before recognizers (in the order above), then the leftmost.
 //
-// Byte-parallel throughout: one thread per text byte tries the rules; every
-// span adds +1 at its begin and -1 at its end of a delta array and a 64-bit
-// key (length, priority, begin) at its begin.  A scan of the deltas gives, per
-// byte, how many spans cover it; a union starts at a byte where a span begins
-// and no earlier-begun span still covers it, and ends at the first byte after
-// it where again no earlier-begun span covers.  Scans of the start and end
-// flags number the unions; the largest key among a union's begin bytes gives
-// its type.
+// The rules are tried at anchors only: every match holds one byte that few
+// bytes equal, at a place that fixes its start -- the '@' of an e-mail, the
+// first '.' of a hostname or an IPv4 address, the first ':' of a URL, MAC,
+// IPv6 or CPE, the '-' after "CVE", and for a hash the first aligned 16-byte
+// block of hex digits inside it.  A workgroup stages 4096 bytes (16 per
+// thread) with 64 bytes before and 448 after in LDS, lists its anchors (about
+// one byte in forty), and runs the rules on them with the lanes packed.
+//
+// Merge: two bitmaps over the text, S (a span begins here) and J (this byte
+// and the one before it lie in one span).  A union begins where S holds and J
+// does not, and ends at the first byte after it where J does not hold.  The
+// begins are counted per tile, their ranks number the unions, and a 64-bit
+// atomic max per union over its members' keys (length, priority, begin, type)
+// picks its type.
+//
+// Bound by the rules' scans and by launches: a byte costs one read and half a
+// bit of bitmap traffic, where per-byte counters, flags, keys and their
+// three-kernel scans moved about 140 bytes of memory per text byte over 20
+// launches.  4.9 MB of text with its NER spans in 4096 records: 467 ->
+// 56 us (the rules 35).
 #include "kernels.hpp"
 
 namespace anon {
@@ -52,100 +64,157 @@ __device__ __forceinline__ bool is_hex(uint8_t c) {
 }
 __device__ __forceinline__ bool is_space(uint8_t c) { return c == ' ' || (c >= '\t' && c <= '\r'); }
 
-// One record's bytes [lo, hi) of the text; positions are absolute.  Bytes
-// inside the workgroup's staged window [wlo, whi) are read from LDS, the rest
-// (long runs past the window) from global memory.
+constexpr int kTile = 4096;                   // text bytes per match workgroup, 16 per thread
+constexpr int kBefore = 64, kAfter = 448;     // staged before and after the tile
+constexpr int kWin = kBefore + kTile + kAfter;
+constexpr int kWinWords = kWin / 64;
+
+// Byte classes kept as bitmaps of the staged window, a bit per byte: a run's
+// end is then one count of trailing zeros per 64 bytes instead of a load, a
+// range test and a branch per byte.
+enum Class { C_LABEL, C_LOCAL, C_HEX, C_LETTER, C_TEXT /* not a space */, C_COUNT };
+__device__ __forceinline__ bool in_class(uint8_t c, int k) {
+  return k == C_LABEL ? is_label(c) : k == C_LOCAL ? is_local(c) : k == C_HEX ? is_hex(c) : k == C_LETTER ? is_letter(c)
+                                                                                               : !is_space(c);
+}
+
+// One record's bytes [lo, hi) of the text; positions are absolute (texts are
+// below 2^31 bytes).  Bytes inside the workgroup's staged window [wlo, whi)
+// are read from LDS (window position of byte i: i - base), the rest (long
+// runs past the window) from global memory.
 struct Rec {
   const uint8_t* t;
-  int64_t lo, hi;
+  int lo, hi;
   const uint8_t* win;
-  int64_t wlo, whi;
-  __device__ uint8_t at(int64_t i) const { return (i >= wlo && i < whi) ? win[i - wlo] : t[i]; }
-  __device__ bool word_start(int64_t p) const { return is_word(at(p)) && (p == lo || !is_word(at(p - 1))); }
-  __device__ bool word_end(int64_t q) const { return q == hi || !is_word(at(q)); }
-  __device__ bool has(int64_t p, const char* s, int n) const {
-    if (p + n > hi) return false;
-    for (int i = 0; i < n; ++i)
-      if (at(p + i) != (uint8_t)s[i]) return false;
-    return true;
+  const uint64_t (*cls)[kWinWords];
+  int base, wlo, whi;
+  __device__ uint8_t at(int i) const { return (i >= wlo && i < whi) ? win[i - base] : t[i]; }
+  __device__ bool word_start(int p) const { return is_word(at(p)) && (p == lo || !is_word(at(p - 1))); }
+  __device__ bool word_end(int q) const { return q == hi || !is_word(at(q)); }
+  // bytes p .. p + N - 1, p >= lo, are inside the record and pass f(i, byte):
+  // inside the window the loads are independent (no early exit), so they cost
+  // one LDS latency
+  template <int N, typename F>
+  __device__ bool all(int p, F f) const {
+    if (hi - p < N) return false;
+    bool ok = true;
+    if (p >= wlo && whi - p >= N) {
+      const uint8_t* q = win + (p - base);
+#pragma unroll
+      for (int i = 0; i < N; ++i) ok = f(i, q[i]) && ok;
+    } else {
+      for (int i = 0; i < N && ok; ++i) ok = f(i, t[p + i]);
+    }
+    return ok;
+  }
+  template <int N>
+  __device__ bool has(int p, const char (&s)[N]) const {
+    return all<N - 1>(p, [&](int i, uint8_t c) { return c == (uint8_t)s[i]; });
+  }
+  // end of the run of class k from p on, at most hi
+  template <int K>
+  __device__ int run_end(int p) const {
+    const int lim = min(hi, whi);
+    while (p < lim && p >= wlo) {
+      const int o = p - base;
+      const uint64_t stop = ~cls[K][o >> 6] >> (o & 63);
+      if (stop) {
+        p += __ffsll((unsigned long long)stop) - 1;
+        if (p < lim) return p;
+        break;
+      }
+      p += 64 - (o & 63);
+    }
+    p = min(p, hi);
+    while (p < hi && in_class(at(p), K)) ++p;  // past the window
+    return p;
+  }
+  // start of the run of class k that ends before p, at least lo
+  template <int K>
+  __device__ int run_begin(int p) const {
+    const int lim = max(lo, wlo);
+    while (p > lim && p <= whi) {
+      const int o = p - 1 - base;
+      const uint64_t stop = ~cls[K][o >> 6] << (63 - (o & 63));
+      if (stop) {
+        p -= __clzll((long long)stop);
+        if (p > lim) return p;
+        break;
+      }
+      p -= (o & 63) + 1;
+    }
+    p = max(p, lo);
+    while (p > lo && in_class(at(p - 1), K)) --p;
+    return p;
   }
 };
 
-__device__ int64_t match_url(const Rec& r, int64_t p) {
+__device__ int match_url(const Rec& r, int p) {
   if (!r.word_start(p)) return -1;
-  int64_t q;
-  if (r.has(p, "https://", 8)) q = p + 8;
-  else if (r.has(p, "http://", 7)) q = p + 7;
+  int q;
+  if (r.has(p, "https://")) q = p + 8;
+  else if (r.has(p, "http://")) q = p + 7;
   else return -1;
-  int64_t e = q;
-  while (e < r.hi && !is_space(r.at(e))) ++e;
+  const int e = r.run_end<C_TEXT>(q);
   return e > q ? e : -1;
 }
 
-// An all-letter label of >= 2 bytes at s, not followed by a LABEL byte.
-__device__ int64_t top_letters(const Rec& r, int64_t s) {
-  int64_t e = s;
-  while (e < r.hi && is_letter(r.at(e))) ++e;
-  return (e - s >= 2 && (e == r.hi || !is_label(r.at(e)))) ? e : -1;
+// Whether the label [s, e) is one of the eight top labels.
+__device__ bool top_listed(const Rec& r, int s, int e) {
+  switch (e - s) {
+    case 3: return r.has(s, "lan") || r.has(s, "net") || r.has(s, "org");
+    case 4: return r.has(s, "corp");
+    case 5: return r.has(s, "intra") || r.has(s, "local");
+    case 7: return r.has(s, "example");
+    case 8: return r.has(s, "internal");
+    default: return false;
+  }
 }
 
-// One of the eight top labels at s, not followed by a LABEL byte.
-__device__ int64_t top_listed(const Rec& r, int64_t s) {
-  const char* const tops[8] = {"corp", "lan", "intra", "net", "org", "local", "example", "internal"};
-  const int lens[8] = {4, 3, 5, 3, 3, 5, 7, 8};
-  for (int k = 0; k < 8; ++k)
-    if (r.has(s, tops[k], lens[k]) && (s + lens[k] == r.hi || !is_label(r.at(s + lens[k])))) return s + lens[k];
-  return -1;
-}
-
-// Dotted LABEL groups from i on: the top label may start after any group but
-// the first; the longest successful domain is the last success in order.
+// Dotted LABEL groups from i on: the top label (a listed one, or at least two
+// letters) may be any label but the first; the longest successful domain is
+// the last success in order.
 template <bool LISTED>
-__device__ int64_t dotted_domain(const Rec& r, int64_t i) {
-  int64_t best = -1;
-  int groups = 0;
+__device__ int dotted_domain(const Rec& r, int i) {
+  int best = -1;
+  bool first = true;
   while (true) {
-    int64_t j = i;
-    while (j < r.hi && is_label(r.at(j))) ++j;
-    const bool group = j > i && j < r.hi && r.at(j) == '.';
-    if (groups >= 1) {
-      const int64_t e = LISTED ? top_listed(r, i) : top_letters(r, i);
-      if (e >= 0) best = e;
-    }
-    if (!group) return best;
-    ++groups;
+    const int j = r.run_end<C_LABEL>(i);
+    if (!first && (LISTED ? top_listed(r, i, j) : j - i >= 2 && r.run_end<C_LETTER>(i) >= j)) best = j;
+    if (j == i || j >= r.hi || r.at(j) != '.') return best;
+    first = false;
     i = j + 1;
   }
 }
 
-__device__ int64_t match_email(const Rec& r, int64_t p) {
-  if (!is_local(r.at(p)) || (p > r.lo && is_local(r.at(p - 1)))) return -1;
-  int64_t q = p;
-  while (q < r.hi && is_local(r.at(q))) ++q;
+// p: the start of a LOCAL run, maximal to the left
+__device__ int match_email(const Rec& r, int p) {
+  const int q = r.run_end<C_LOCAL>(p);
   if (q == r.hi || r.at(q) != '@') return -1;
   return dotted_domain<false>(r, q + 1);
 }
 
-__device__ int64_t match_hostname(const Rec& r, int64_t p) {
-  if (!is_label(r.at(p)) || (p > r.lo && (is_label(r.at(p - 1)) || r.at(p - 1) == '.'))) return -1;
+// p: the start of a LABEL run, maximal to the left
+__device__ int match_hostname(const Rec& r, int p) {
+  if (p > r.lo && r.at(p - 1) == '.') return -1;
   return dotted_domain<true>(r, p);
 }
 
 // End of a valid octet spanning the whole digit run at i, else -1.
-__device__ int64_t octet(const Rec& r, int64_t i) {
-  int64_t e = i;
+__device__ int octet(const Rec& r, int i) {
+  int e = i;
   int v = 0;
   while (e < r.hi && is_digit(r.at(e)) && e - i < 4) v = v * 10 + (r.at(e++) - '0');
-  const int64_t c = e - i;
+  const int c = e - i;
   if (c < 1 || c > 3 || (c > 1 && r.at(i) == '0') || v > 255) return -1;
   return e;
 }
 
-__device__ int64_t match_ipv4(const Rec& r, int64_t p) {
+__device__ int match_ipv4(const Rec& r, int p) {
   if (!is_digit(r.at(p)) || !r.word_start(p)) return -1;
-  int64_t i = p;
+  int i = p;
   for (int k = 0; k < 4; ++k) {
-    const int64_t e = octet(r, i);
+    const int e = octet(r, i);
     if (e < 0) return -1;
     if (k == 3) return r.word_end(e) ? e : -1;
     if (e == r.hi || r.at(e) != '.') return -1;
@@ -154,31 +223,25 @@ __device__ int64_t match_ipv4(const Rec& r, int64_t p) {
   return -1;
 }
 
-__device__ int64_t match_mac(const Rec& r, int64_t p) {
-  if (!r.word_start(p) || p + 17 > r.hi) return -1;
-  for (int k = 0; k < 17; ++k) {
-    const uint8_t c = r.at(p + k);
-    if (k % 3 == 2 ? c != ':' : !is_hex(c)) return -1;
-  }
+__device__ int match_mac(const Rec& r, int p) {
+  if (!r.word_start(p) || !r.all<17>(p, [](int k, uint8_t c) { return k % 3 == 2 ? c == ':' : is_hex(c); })) return -1;
   return r.word_end(p + 17) ? p + 17 : -1;
 }
 
-__device__ int64_t match_hash(const Rec& r, int64_t p) {
-  if (!is_hex(r.at(p)) || !r.word_start(p)) return -1;
-  int64_t e = p;
-  while (e < r.hi && is_hex(r.at(e)) && e - p < 65) ++e;
-  const int64_t c = e - p;
+__device__ int match_hash(const Rec& r, int p) {
+  if (!r.word_start(p)) return -1;
+  const int e = r.run_end<C_HEX>(p), c = e - p;
   return ((c == 32 || c == 40 || c == 64) && r.word_end(e)) ? e : -1;
 }
 
-__device__ int64_t match_cve(const Rec& r, int64_t p) {
-  if (!r.word_start(p) || p + 9 > r.hi || !r.has(p, "CVE-", 4)) return -1;
+__device__ int match_cve(const Rec& r, int p) {
+  if (!r.word_start(p) || r.hi - p < 9 || !r.has(p, "CVE-")) return -1;
   for (int k = 0; k < 4; ++k)
     if (!is_digit(r.at(p + 4 + k))) return -1;
   if (r.at(p + 8) != '-') return -1;
-  int64_t e = p + 9;
+  int e = p + 9;
   while (e < r.hi && is_digit(r.at(e)) && e - (p + 9) < 8) ++e;
-  const int64_t c = e - (p + 9);
+  const int c = e - (p + 9);
   return (c >= 4 && c <= 7 && r.word_end(e)) ? e : -1;
 }
 
@@ -187,12 +250,12 @@ __device__ __forceinline__ bool is_cpe(uint8_t c) {
          c == '!' || c == '\\' || c == '-';
 }
 
-__device__ int64_t match_cpe(const Rec& r, int64_t p) {
+__device__ int match_cpe(const Rec& r, int p) {
   if (!r.word_start(p)) return -1;
-  int64_t q;
+  int q;
   bool v23;
-  if (r.has(p, "cpe:/", 5)) q = p + 5, v23 = false;
-  else if (r.has(p, "cpe:2.3:", 8)) q = p + 8, v23 = true;
+  if (r.has(p, "cpe:/")) q = p + 5, v23 = false;
+  else if (r.has(p, "cpe:2.3:")) q = p + 8, v23 = true;
   else return -1;
   if (q == r.hi) return -1;
   const uint8_t part = r.at(q);
@@ -204,9 +267,9 @@ __device__ int64_t match_cpe(const Rec& r, int64_t p) {
 }
 
 // Four octets separated by '.', exactly covering [i, end).
-__device__ bool dotted_quad(const Rec& r, int64_t i, int64_t end) {
+__device__ bool dotted_quad(const Rec& r, int i, int end) {
   for (int k = 0; k < 4; ++k) {
-    const int64_t e = octet(r, i);
+    const int e = octet(r, i);
     if (e < 0) return false;
     if (k == 3) return e == end;
     if (e >= end || r.at(e) != '.') return false;
@@ -220,7 +283,7 @@ __device__ bool dotted_quad(const Rec& r, int64_t i, int64_t end) {
 // one zero group, so at most seven written groups), and a dotted quad, worth
 // two groups, only as the text's last group.  An address text is at most 45
 // bytes long, so a longer S is rejected while it is scanned.
-__device__ int64_t match_ipv6(const Rec& r, int64_t p) {
+__device__ int match_ipv6(const Rec& r, int p) {
   const uint8_t c0 = r.at(p);
   if (!is_hex(c0) && c0 != ':') return -1;
   if (p > r.lo) {
@@ -230,7 +293,7 @@ __device__ int64_t match_ipv6(const Rec& r, int64_t p) {
   // The first group has at most 4 hex digits and a ':' follows it (a lone
   // group or a dotted quad alone is no address), so hashes, IPv4 addresses
   // and words are rejected after at most 5 bytes.
-  int64_t e = p, s = p;
+  int e = p, s = p;
   bool colon = false;
   while (e < r.hi) {
     const uint8_t c = r.at(e);
@@ -248,14 +311,14 @@ __device__ int64_t match_ipv6(const Rec& r, int64_t p) {
   if (!colon || !r.word_end(s)) return -1;
   int groups = 0;
   bool dbl = false;
-  int64_t i = p;
+  int i = p;
   if (c0 == ':') {
     if (s - p < 2 || r.at(p + 1) != ':') return -1;
     dbl = true;
     i = p + 2;
   }
   while (i < s) {
-    int64_t j = i;
+    int j = i;
     while (j < s && is_hex(r.at(j))) ++j;
     if (j < s && r.at(j) == '.') {
       if (!dotted_quad(r, i, s)) return -1;
@@ -278,26 +341,28 @@ __device__ int64_t match_ipv6(const Rec& r, int64_t p) {
 }
 
 constexpr int kRecognizers = kNumRecognizers;
-// the IPv6 and CPE rules run in a kernel of their own (rx_extra_kernel)
-constexpr int kIpv6 = 7;
-constexpr int kCpe = 8;
-constexpr int kWin = 1 + 256 + 1024;  // staged bytes per match workgroup (1 before, 1024 ahead)
+constexpr int kTileWords = kTile / 64;
+// matches per tile: an anchor gives at most two, a 16-byte block and a record
+// start one each
+constexpr int kTileEntries = 2 * kTile + kTile / 16;
 struct RecTypes {
   int t[kRecognizers];  // type index per recognizer, 0 = off
 };
 
-// 64-bit union key of a span: longest first, then lowest priority (NER 0,
-// recognizer k -> k+1), then leftmost begin (offset inside the record).
-__device__ __forceinline__ unsigned long long span_key(int64_t len, int prio, int64_t local_begin) {
-  const unsigned long long L = (unsigned long long)min(len, (int64_t)0xFFFFFF);
-  return (L << 40) | ((unsigned long long)(255 - prio) << 32) | (0xFFFFFFFFull - (unsigned long long)local_begin);
+// 60-bit union key of a span: longest first, then lowest priority (NER 0,
+// recognizer k -> k+1), then leftmost begin (offset inside the record); the
+// low byte carries the type.
+__device__ __forceinline__ unsigned long long span_key(int len, int prio, int local_begin, int type) {
+  return ((unsigned long long)min(len, 0xFFFFFF) << 36) | ((unsigned long long)(15 - prio) << 32) |
+         ((unsigned long long)(0xFFFFFF - min(local_begin, 0xFFFFFF)) << 8) | (unsigned long long)type;
 }
 
 // Record b's bytes, clamped to the text [0, n) (a malformed cu_bytes is
 // flagged by rx_check_kernel and cannot send a read outside the text).
-__device__ __forceinline__ void record_bounds(const int64_t* cu, int b, int64_t n, int64_t& lo, int64_t& hi) {
-  lo = min(max(cu[b], (int64_t)0), n);
-  hi = min(max(cu[b + 1], lo), n);
+__device__ __forceinline__ void record_bounds(const int64_t* cu, int b, int64_t n, int& lo, int& hi) {
+  const int64_t l = min(max(cu[b], (int64_t)0), n);
+  lo = (int)l;
+  hi = (int)min(max(cu[b + 1], l), n);
 }
 
 __device__ __forceinline__ int find_record(const int64_t* cu, int B, int64_t p) {
@@ -310,279 +375,366 @@ __device__ __forceinline__ int find_record(const int64_t* cu, int B, int64_t p) 
   return a;
 }
 
-// cu_bytes must rise from 0 to n, and records must be shorter than 16 MiB
-// (the union key holds lengths in 24 bits).
-__global__ __launch_bounds__(256) void rx_check_kernel(const int64_t* __restrict__ cu, int B, int64_t n,
-                                                       uint32_t* err) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b > B) return;
-  if ((b == 0 && cu[0] != 0) || (b == B && cu[B] != n)) raise_error(err, ANON_ERR_TEXT);
-  if (b < B && (cu[b + 1] < cu[b] || cu[b + 1] - cu[b] >= (int64_t(1) << 24))) raise_error(err, ANON_ERR_TEXT);
-}
-
-__global__ __launch_bounds__(256) void rx_clear_kernel(int* delta, int* starts, unsigned long long* key,
-                                                       uint8_t* ner_type, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i <= n; i += (int64_t)gridDim.x * 256) {
-    delta[i] = 0;
-    starts[i] = 0;
-    key[i] = 0;
-    ner_type[i] = 0;
+// Clears the bitmaps and checks cu_bytes: it must rise from 0 to n, and
+// records must be shorter than 16 MiB (the union key holds lengths in 24
+// bits).
+__global__ __launch_bounds__(256) void rx_init_kernel(unsigned long long* maps, int64_t words,
+                                                      const int64_t* __restrict__ cu, int B, int64_t n,
+                                                      uint32_t* err) {
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  for (int64_t i = i0; i < words; i += (int64_t)gridDim.x * 256) maps[i] = 0;
+  for (int64_t b = i0; b <= B; b += (int64_t)gridDim.x * 256) {
+    const int64_t x = cu[b];
+    if ((b == 0 && x != 0) || (b == B && x != n)) raise_error(err, ANON_ERR_TEXT);
+    if (b < B && (cu[b + 1] < x || cu[b + 1] - x >= (int64_t(1) << 24))) raise_error(err, ANON_ERR_TEXT);
   }
 }
 
-// Every enabled rule at p; candidates go into the delta/start/key arrays.
-__device__ void match_all(const Rec& r, int64_t p, const RecTypes& rt, int* delta, int* starts,
-                          unsigned long long* key) {
-  int count = 0;
-  unsigned long long best = 0;
-#pragma unroll
-  for (int k = 0; k < kIpv6; ++k) {
-    if (rt.t[k] == 0) continue;
-    int64_t e;
-    switch (k) {
-      case 0: e = match_url(r, p); break;
-      case 1: e = match_email(r, p); break;
-      case 2: e = match_ipv4(r, p); break;
-      case 3: e = match_mac(r, p); break;
-      case 4: e = match_hash(r, p); break;
-      case 5: e = match_cve(r, p); break;
-      default: e = match_hostname(r, p); break;
-    }
-    if (e < 0) continue;
-    ++count;
-    atomicAdd(&delta[e], -1);
-    const unsigned long long kk = span_key(e - p, 1 + k, p - r.lo);
-    best = kk > best ? kk : best;
-  }
-  if (count) {
-    atomicAdd(&delta[p], count);
-    atomicAdd(&starts[p], count);
-    atomicMax(&key[p], best);
+// Span [b, e), e > b, into the bitmaps.
+__device__ __forceinline__ void mark_span(const RecogBuffers& w, int b, int e) {
+  atomicOr(&w.begins[b >> 6], 1ull << (b & 63));
+  for (int i = b + 1; i < e;) {
+    const int stop = min(e, (i | 63) + 1);
+    const unsigned long long m = (stop - i == 64 ? ~0ull : (1ull << (stop - i)) - 1) << (i & 63);
+    atomicOr(&w.joins[i >> 6], m);
+    i = stop;
   }
 }
 
-__device__ __forceinline__ bool is_alnum(uint8_t c) { return is_digit(c) || is_letter(c); }
-
-
-// A rule can start at p only on a LOCAL byte (URL 'h', IPv4/MAC/hash/CVE
-// word bytes, e-mail LOCAL, hostname LABEL) whose predecessor in the record
-// is not alphanumeric (the word-boundary rules exclude a word byte before
-// it, the e-mail rule a LOCAL byte, the hostname rule a LABEL byte or dot).
-// Each workgroup first collects its 256 bytes that pass this test, then runs
-// the rules on them with the lanes packed: most bytes sit inside words, and
-// trying them all left most lanes of a wave idle behind a few long scans.
-// A record's first byte whose predecessor (the previous record's last byte)
-// is alphanumeric fails the test here and is tried by rx_recstart_kernel.
-__global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict__ text,
-                                                       const int64_t* __restrict__ cu, int B, int64_t n,
-                                                       RecTypes rt, int* delta, int* starts,
-                                                       unsigned long long* key) {
-  // the workgroup's 256 start bytes, the byte before them and 1024 bytes of
-  // lookahead, staged in LDS (coalesced loads)
-  __shared__ uint8_t win[kWin];
-  __shared__ int cand[256];
-  __shared__ int ncand;
-  const int64_t p0 = (int64_t)blockIdx.x * 256;
-  const int64_t wlo = p0 > 0 ? p0 - 1 : 0;
-  const int64_t whi = min(wlo + kWin, n);
-  for (int64_t i = wlo + threadIdx.x; i < whi; i += 256) win[i - wlo] = text[i];
-  if (threadIdx.x == 0) ncand = 0;
-  __syncthreads();
-  const int64_t p = p0 + threadIdx.x;
-  if (p < n && is_local(win[p - wlo]) && !(p > 0 && is_alnum(win[p - 1 - wlo])))
-    cand[atomicAdd(&ncand, 1)] = threadIdx.x;
-  __syncthreads();
-  const int nc = ncand;
-  for (int i = threadIdx.x; i < nc; i += 256) {
-    const int64_t q = p0 + cand[i];
-    const int b = find_record(cu, B, q);
-    int64_t lo, hi;
-    record_bounds(cu, b, n, lo, hi);
-    if (q < lo || q >= hi) continue;  // only with a malformed cu_bytes
-    match_all(Rec{text, lo, hi, win, wlo, whi}, q, rt, delta, starts, key);
-  }
-}
-
-// Record starts whose previous byte is alphanumeric (see rx_match_kernel).
-__global__ __launch_bounds__(256) void rx_recstart_kernel(const uint8_t* __restrict__ text,
-                                                          const int64_t* __restrict__ cu, int B, int64_t n,
-                                                          RecTypes rt, int* delta, int* starts,
-                                                          unsigned long long* key) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= B) return;
-  int64_t lo, hi;
-  record_bounds(cu, b, n, lo, hi);
-  if (hi <= lo || lo == 0 || !is_alnum(text[lo - 1]) || !is_local(text[lo])) return;
-  match_all(Rec{text, lo, hi, nullptr, 0, 0}, lo, rt, delta, starts, key);
-}
-
-// The IPv6 and CPE rules over every byte, in a kernel of their own: inlined
-// beside the other rules, either raises that kernel's register count from
-// 66 to over 110 VGPRs and nearly halves its occupancy.  Each has an exact
-// pre-filter on the staged window, which holds the 7 bytes after every start
-// byte unless the text ends first: an IPv6 address starts with 1-4 hex
-// digits or ':' and has a ':' within its first 5 bytes; a CPE name starts
-// with "cpe:".  The rules then check the record bounds and boundaries.
-// Contributions add to the same delta/start/key arrays with atomics, in any
-// order.
-__global__ __launch_bounds__(256) void rx_extra_kernel(const uint8_t* __restrict__ text,
-                                                       const int64_t* __restrict__ cu, int B, int64_t n, int use_ipv6,
-                                                       int use_cpe, int* delta, int* starts,
-                                                       unsigned long long* key) {
-  // an address is at most 45 bytes: 64 bytes of lookahead hold almost every
-  // candidate's run (reads past the window go to global memory)
-  constexpr int kWin6 = 1 + 256 + 64;
-  __shared__ uint8_t win[kWin6];
-  __shared__ int cand[256];
-  __shared__ int ncand;
-  const int64_t p0 = (int64_t)blockIdx.x * 256;
-  const int64_t wlo = p0 > 0 ? p0 - 1 : 0;
-  const int64_t whi = min(wlo + kWin6, n);
-  for (int64_t i = wlo + threadIdx.x; i < whi; i += 256) win[i - wlo] = text[i];
-  if (threadIdx.x == 0) ncand = 0;
-  __syncthreads();
-  const int64_t p = p0 + threadIdx.x;
-  if (p < n) {
-    bool pass = false;
-    if (use_ipv6) {
-      for (int k = 0; k < 5 && p + k < whi; ++k) {
-        const uint8_t c = win[p + k - wlo];
-        if (c == ':') {
-          pass = true;
-          break;
-        }
-        if (!is_hex(c)) break;
-      }
-    }
-    if (use_cpe && p + 3 < whi)
-      pass = pass || (win[p - wlo] == 'c' && win[p + 1 - wlo] == 'p' && win[p + 2 - wlo] == 'e' &&
-                      win[p + 3 - wlo] == ':');
-    if (pass) cand[atomicAdd(&ncand, 1)] = threadIdx.x;
-  }
-  __syncthreads();
-  const int nc = ncand;
-  for (int i = threadIdx.x; i < nc; i += 256) {
-    const int64_t q = p0 + cand[i];
-    const int b = find_record(cu, B, q);
-    int64_t lo, hi;
-    record_bounds(cu, b, n, lo, hi);
-    if (q < lo || q >= hi) continue;  // only with a malformed cu_bytes
-    const Rec r{text, lo, hi, win, wlo, whi};
-    int count = 0;
-    unsigned long long best = 0;
-    const int64_t e6 = use_ipv6 ? match_ipv6(r, q) : -1;
-    if (e6 >= 0) {
-      ++count;
-      atomicAdd(&delta[e6], -1);
-      best = span_key(e6 - q, 1 + kIpv6, q - lo);
-    }
-    const int64_t ec = use_cpe ? match_cpe(r, q) : -1;
-    if (ec >= 0) {
-      ++count;
-      atomicAdd(&delta[ec], -1);
-      const unsigned long long kk = span_key(ec - q, 1 + kCpe, q - lo);
-      best = kk > best ? kk : best;
-    }
-    if (count) {
-      atomicAdd(&delta[q], count);
-      atomicAdd(&starts[q], count);
-      atomicMax(&key[q], best);
-    }
-  }
-}
-
-// NER spans (record-relative [begin, end)) join the candidates.
-__global__ __launch_bounds__(256) void rx_ner_kernel(const anon_span* __restrict__ spans,
-                                                     const int* __restrict__ ner_cu, int B, int ner_cap,
-                                                     const int64_t* __restrict__ cu, int64_t n, int n_types, int* delta,
-                                                     int* starts, unsigned long long* key, uint8_t* ner_type,
-                                                     uint32_t* err) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= min(ner_cu[B], ner_cap)) return;
-  const anon_span s = spans[i];
+// An NER span's global [b, e); false (and the error bit) outside its record.
+__device__ __forceinline__ bool ner_span(const anon_span& s, const int64_t* cu, int B, int64_t n, int n_types, int& b,
+                                         int& e, uint32_t* err) {
   if (s.record < 0 || s.record >= B || s.type < 1 || s.type > n_types) {
     raise_error(err, ANON_ERR_SPAN);
-    return;
+    return false;
   }
-  int64_t lo, hi;
+  int lo, hi;
   record_bounds(cu, s.record, n, lo, hi);
   if (s.begin < 0 || s.end <= s.begin || s.end > hi - lo) {
     raise_error(err, ANON_ERR_SPAN);
+    return false;
+  }
+  b = lo + (int)s.begin;
+  e = lo + (int)s.end;
+  return true;
+}
+
+// 16 bytes of text from p on (zeros past n)
+__device__ __forceinline__ uint4 text16(const uint8_t* __restrict__ text, int64_t p, int64_t n) {
+  if (n - p >= 16) return load16(text + p);
+  uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if (p + i < n) w[i >> 2] |= (uint32_t)text[p + i] << (8 * (i & 3));
+  return uint4{w[0], w[1], w[2], w[3]};
+}
+
+// Class bits of 16 staged bytes.
+__device__ __forceinline__ void class_bits(const uint4& v, uint32_t (&m)[C_COUNT]) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+  for (int k = 0; k < C_COUNT; ++k) m[k] = 0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint8_t c = (w[i >> 2] >> (8 * (i & 3))) & 0xff;
+#pragma unroll
+    for (int k = 0; k < C_COUNT; ++k) m[k] |= (in_class(c, k) ? 1u : 0u) << i;
+  }
+}
+
+constexpr int kBounds = 64;  // records of a tile whose boundaries are staged
+
+// Blocks below n_tiles: the matches of a tile's anchors, stored in the tile's
+// entry slots and marked in the bitmaps.  The blocks above: the NER spans.
+// Each wave takes rules of its own (hostnames, IPv4, the ':' rules, the
+// others), so that a wave's lanes run one rule's scan: with one list for all,
+// every wave ran every rule's scan in turn (65 us for a lone tile).
+__global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict__ text,
+                                                       const int64_t* __restrict__ cu, int B, int64_t n, RecTypes rt,
+                                                       int n_tiles, const anon_span* __restrict__ ner,
+                                                       const int* __restrict__ ner_cu, int ner_cap, int n_types,
+                                                       RecogBuffers w, uint32_t* err) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if ((int)blockIdx.x >= n_tiles) {
+    const int total = min(ner_cu[B], ner_cap);
+    for (int64_t i = (int64_t)(blockIdx.x - n_tiles) * 256 + tid; i < total; i += (int64_t)(gridDim.x - n_tiles) * 256) {
+      int b, e;
+      if (ner_span(ner[i], cu, B, n, n_types, b, e, err)) mark_span(w, b, e);
+    }
     return;
   }
-  const int64_t gb = lo + s.begin, ge = lo + s.end;
-  atomicAdd(&delta[gb], 1);
-  atomicAdd(&delta[ge], -1);
-  atomicAdd(&starts[gb], 1);
-  atomicMax(&key[gb], span_key(ge - gb, 0, s.begin));
-  ner_type[gb] = (uint8_t)s.type;  // decoded NER spans of a record never share a begin
+  // Anchor lists (offset within the tile, for the last list also the rule's
+  // kind).  Every position is in one list at most, every 16-byte block's start
+  // once more; only a malformed cu_bytes, whose records can start at one
+  // byte, could fill them.
+  enum { L_DOT, L_COLON, L_OTHER, L_COUNT };
+  enum { K_AT, K_DASH, K_HEX, K_REC };
+  constexpr int kDots = kTile / 2 + 1;  // a '.' after a LABEL byte
+  constexpr int kList = kTile + kTile / 16;
+  __shared__ __align__(16) uint8_t win[kWin];
+  __shared__ __align__(16) uint64_t cls[C_COUNT][kWinWords];
+  __shared__ uint16_t list[kDots + 2 * kList];
+  __shared__ int n_list[L_COUNT], n_entries, bound[kBounds + 1];
+  const int64_t p0 = (int64_t)blockIdx.x * kTile;
+  const int base = (int)p0 - kBefore, wlo = max(base, 0), whi = (int)min(p0 + kTile + kAfter, n);
+  auto stage = [&](int piece, const uint4& v) {  // 16 bytes and their class bits
+    uint32_t m[C_COUNT];
+    class_bits(v, m);
+    *(uint4*)(win + piece * 16) = v;
+#pragma unroll
+    for (int k = 0; k < C_COUNT; ++k) ((uint16_t*)cls[k])[piece] = (uint16_t)m[k];
+    return m[C_HEX];
+  };
+  const uint4 mine = text16(text, p0 + tid * 16, n);
+  const uint32_t my_hex = stage(kBefore / 16 + tid, mine);
+  if (tid < kBefore / 16) {
+    stage(tid, p0 > 0 ? load16(text + p0 - kBefore + tid * 16) : uint4{0, 0, 0, 0});
+  } else if (tid >= 64 && tid < 64 + kAfter / 16) {
+    const int k = tid - 64;
+    stage((kBefore + kTile) / 16 + k, text16(text, p0 + kTile + k * 16, n));
+  }
+  if (tid < L_COUNT) n_list[tid] = 0;
+  if (tid == 0) n_entries = 0;
+  const int r0 = wg_find_record(cu, B, p0);
+  const int r1 = r0 + wg_find_record(cu + r0, B - r0, min(p0 + kTile, n) - 1);
+  const bool few = r1 - r0 < kBounds;
+  if (few && tid <= r1 - r0 + 1) bound[tid] = (int)min(max(cu[r0 + tid], (int64_t)0), n);
+  __syncthreads();
+  // anchors, with what their neighbours must be for any rule
+  const uint8_t* me = win + kBefore + tid * 16;
+  const auto first = [](int l) { return l == L_DOT ? 0 : kDots + (l - L_COLON) * kList; };
+  const auto room = [](int l) { return l == L_DOT ? kDots : kList; };
+  auto push = [&](int l, int v) {
+    const int k = atomicAdd(&n_list[l], 1);
+    if (k < room(l)) list[first(l) + k] = (uint16_t)v;
+  };
+  {
+    const uint32_t v[4] = {mine.x, mine.y, mine.z, mine.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint8_t c = (v[i >> 2] >> (8 * (i & 3))) & 0xff;
+      m |= (c == '.' || c == ':' || c == '-' || c == '@' ? 1u : 0u) << i;
+    }
+    for (; m; m &= m - 1) {
+      const int i = __ffs(m) - 1, off = tid * 16 + i;
+      const uint8_t c = me[i], prev = me[i - 1], next = me[i + 1];
+      if (c == '.') {
+        if (is_label(prev)) push(L_DOT, off);
+      } else if (c == '@') {
+        if (is_local(prev)) push(L_OTHER, off | (K_AT << 12));
+      } else if (c == '-') {
+        if (prev == 'E') push(L_OTHER, off | (K_DASH << 12));
+      } else if (is_hex(prev) || next == ':' || ((prev == 'p' || prev == 's') && next == '/')) {
+        push(L_COLON, off);
+      }
+    }
+    if (my_hex == 0xffff && ((const uint16_t*)cls[C_HEX])[kBefore / 16 + tid - 1] != 0xffff)
+      push(L_OTHER, (tid * 16) | (K_HEX << 12));
+  }
+  // record starts: a hash there may follow the last record's hex digits
+  for (int64_t r = r0 + tid; r <= r1; r += 256) {
+    const int64_t x = cu[r];
+    if (x >= p0 && x < min(p0 + kTile, n) && cu[r + 1] > x && is_hex(win[kBefore + (x - p0)]))
+      push(L_OTHER, (int)(x - p0) | (K_REC << 12));
+  }
+  __syncthreads();
+
+  auto record = [&](int a) {  // of the anchor at byte a
+    int x = r0, y = r1;
+    while (x < y) {
+      const int m = (x + y + 1) >> 1;
+      if ((few ? (int64_t)bound[m - r0] : cu[m]) <= a) x = m;
+      else y = m - 1;
+    }
+    int lo, hi;
+    if (few) lo = bound[x - r0], hi = max(bound[x - r0 + 1], lo);
+    else record_bounds(cu, x, n, lo, hi);
+    return Rec{text, lo, hi, win, cls, base, wlo, whi};
+  };
+  auto emit = [&](const Rec& r, int rule, int p, int e) {
+    if (e < 0) return;
+    mark_span(w, p, e);
+    const int slot = atomicAdd(&n_entries, 1);
+    if (slot < kTileEntries)
+      w.entries[(size_t)blockIdx.x * kTileEntries + slot] =
+          RecogEntry{p, 0, span_key(e - p, 1 + rule, p - r.lo, rt.t[rule])};
+  };
+  const int li = wave < 2 ? (int)L_DOT : wave == 2 ? (int)L_COLON : (int)L_OTHER;
+  const int nl = min(n_list[li], room(li));
+  for (int k = lane; k < nl; k += 64) {
+    const int v = list[first(li) + k], a = (int)p0 + (v & 0xfff);
+    const Rec r = record(a);
+    if (a < r.lo || a >= r.hi) continue;  // only with a malformed cu_bytes
+    if (wave == 0) {
+      const int s = r.run_begin<C_LABEL>(a);
+      if (rt.t[6] && s < a) emit(r, 6, s, match_hostname(r, s));
+    } else if (wave == 1) {
+      int s = a;
+      while (s > r.lo && a - s < 4 && is_digit(r.at(s - 1))) --s;
+      if (rt.t[2] && s < a) emit(r, 2, s, match_ipv4(r, s));
+    } else if (wave == 2) {
+      const uint8_t prev = a > r.lo ? r.at(a - 1) : 0;
+      if (rt.t[0] && prev == 'p' && a - r.lo >= 4) emit(r, 0, a - 4, match_url(r, a - 4));
+      if (rt.t[0] && prev == 's' && a - r.lo >= 5) emit(r, 0, a - 5, match_url(r, a - 5));
+      const int mac = a - r.lo >= 2 && is_hex(prev) ? match_mac(r, a - 2) : -1;
+      if (rt.t[3]) emit(r, 3, a - 2, mac);
+      // (six groups not followed by ':' are no address)
+      if (rt.t[7] && !(mac >= 0 && (mac == r.hi || r.at(mac) != ':'))) {
+        int s = a;
+        while (s > r.lo && a - s < 5 && is_hex(r.at(s - 1))) --s;
+        if (a - s < 5) emit(r, 7, s, match_ipv6(r, s));
+      }
+      if (rt.t[8] && prev == 'e' && a - r.lo >= 3) emit(r, 8, a - 3, match_cpe(r, a - 3));
+    } else {
+      const int kind = v >> 12;
+      if (kind == K_AT) {
+        const int s = r.run_begin<C_LOCAL>(a);
+        if (rt.t[1] && s < a) emit(r, 1, s, match_email(r, s));
+      } else if (kind == K_DASH) {
+        if (rt.t[5] && a - r.lo >= 3) emit(r, 5, a - 3, match_cve(r, a - 3));
+      } else if (rt.t[4]) {
+        const int s = kind == K_HEX ? r.run_begin<C_HEX>(a) : r.lo;
+        emit(r, 4, s, match_hash(r, s));
+      }
+    }
+  }
+  __syncthreads();
+  if (tid == 0) w.n_entries[blockIdx.x] = min(n_entries, kTileEntries);
 }
 
-// cover[p] = exclusive scan of delta: spans covering byte p-1 (cover[p+1]
-// covers p).  A union starts at p if a span begins there and no span begun
-// earlier covers p; one ends at q if byte q-1 is covered and no span begun
-// before q covers q.
-__global__ __launch_bounds__(256) void rx_flags_kernel(const int* __restrict__ cover, const int* __restrict__ starts,
-                                                       int64_t n, int* fstart, int* fend) {
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
-    const int cov_p = p < n ? cover[p + 1] : 0;
-    const int carry = cov_p - (p < n ? starts[p] : 0);
-    fstart[p] = (p < n && starts[p] > 0 && carry == 0) ? 1 : 0;
-    fend[p] = (p >= 1 && cover[p] > 0 && carry == 0) ? 1 : 0;
+// A wave per tile: its unions' begins (left in `begins`), their rank within
+// the tile at every 64-byte word, their count, and their keys cleared.
+__global__ __launch_bounds__(256) void rx_count_kernel(RecogBuffers w, int n_tiles, int64_t words) {
+  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (tile >= n_tiles) return;
+  const int64_t i = (int64_t)tile * kTileWords + lane;
+  unsigned long long u = 0;
+  if (i < words) w.begins[i] = u = w.begins[i] & ~w.joins[i];
+  const int c = __popcll(u);
+  int x = c;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (i < words) w.word_rank[i] = (uint16_t)(x - c);
+  const int total = __shfl(x, 63, 64);
+  if (lane == 0) w.tile_count[tile] = total;
+  for (int k = lane; k < total; k += 64) w.keys[(size_t)tile * kTile + k] = 0;
+}
+
+// The key slot of the union that holds byte p: its rank within the tile where
+// it begins, which is p's tile or, for a long union, one before it.
+__device__ __forceinline__ size_t union_slot(const RecogBuffers& w, int p) {
+  int tile = p / kTile;
+  const unsigned long long u = w.begins[p >> 6] & (~0ull >> (63 - (p & 63)));
+  int k = w.word_rank[p >> 6] + __popcll(u);
+  while (k == 0 && tile > 0) k = w.tile_count[--tile];
+  return (size_t)tile * kTile + max(k - 1, 0);
+}
+
+constexpr int kEntryTiles = 64;  // tiles per member workgroup
+
+// Block 0: the prefix of the tiles' union counts.  The next blocks: every
+// match's key into its union, 64 tiles to a workgroup.  The rest: the NER
+// spans' keys.
+__global__ __launch_bounds__(256) void rx_members_kernel(const int64_t* __restrict__ cu, int B, int64_t n, int n_tiles,
+                                                         int entry_blocks, const anon_span* __restrict__ ner,
+                                                         const int* __restrict__ ner_cu, int ner_cap, int n_types,
+                                                         RecogBuffers w) {
+  __shared__ int pre[257];
+  const int tid = threadIdx.x;
+  auto scan = [&](int v) {  // inclusive scan of one value per thread into pre[1..256]
+    pre[tid + 1] = v;
+    if (tid == 0) pre[0] = 0;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+      const int x = tid >= o ? pre[tid + 1 - o] : 0;
+      __syncthreads();
+      pre[tid + 1] += x;
+      __syncthreads();
+    }
+  };
+  if (blockIdx.x == 0) {
+    const int per = (n_tiles + 255) / 256, a = min(n_tiles, tid * per), b = min(n_tiles, a + per);
+    int s = 0;
+    for (int i = a; i < b; ++i) s += w.tile_count[i];
+    scan(s);
+    int run = pre[tid];
+    for (int i = a; i < b; ++i) {
+      w.tile_pre[i] = run;
+      run += w.tile_count[i];
+    }
+    if (tid == 0) w.tile_pre[n_tiles] = pre[256];
+    return;
+  }
+  if ((int)blockIdx.x <= entry_blocks) {
+    const int t0 = (blockIdx.x - 1) * kEntryTiles;
+    scan(tid < kEntryTiles && t0 + tid < n_tiles ? w.n_entries[t0 + tid] : 0);
+    const int total = pre[256];
+    for (int i = tid; i < total; i += 256) {
+      int a = 0, b = kEntryTiles - 1;  // last tile with pre <= i
+      while (a < b) {
+        const int m = (a + b + 1) >> 1;
+        if (pre[m] <= i) a = m;
+        else b = m - 1;
+      }
+      const RecogEntry e = w.entries[(size_t)(t0 + a) * kTileEntries + (i - pre[a])];
+      atomicMax(&w.keys[union_slot(w, e.p)], e.key);
+    }
+    return;
+  }
+  const int total = min(ner_cu[B], ner_cap);
+  const int first = entry_blocks + 1;
+  for (int64_t i = (int64_t)(blockIdx.x - first) * 256 + tid; i < total; i += (int64_t)(gridDim.x - first) * 256) {
+    const anon_span s = ner[i];
+    int b, e;
+    if (ner_span(s, cu, B, n, n_types, b, e, nullptr))
+      atomicMax(&w.keys[union_slot(w, b)], span_key(e - b, 0, (int)s.begin, s.type));
   }
 }
 
-__global__ __launch_bounds__(256) void rx_runs_kernel(const int* __restrict__ fstart, const int* __restrict__ sstart,
-                                                      const int* __restrict__ fend, const int* __restrict__ send,
-                                                      const unsigned long long* __restrict__ key, int64_t n,
-                                                      int64_t* run_begin, int64_t* run_end,
-                                                      unsigned long long* run_key) {
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
-    if (fstart[p]) run_begin[sstart[p]] = p;
-    if (fend[p]) run_end[send[p]] = p;
-    if (p < n && key[p]) atomicMax(&run_key[sstart[p + 1] - 1], key[p]);
-  }
-}
-
-__global__ __launch_bounds__(256) void rx_emit_kernel(const int* __restrict__ n_runs_p, const int64_t* __restrict__ run_begin,
-                                                      const int64_t* __restrict__ run_end,
-                                                      const unsigned long long* __restrict__ run_key,
-                                                      const uint8_t* __restrict__ ner_type, const int64_t* __restrict__ cu,
-                                                      int B, RecTypes rt, anon_span* out, int cap) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= min(*n_runs_p, cap)) return;
-  const int64_t gb = run_begin[i], ge = run_end[i];
-  const int b = find_record(cu, B, gb);
-  const unsigned long long k = run_key[i];
-  const int prio = 255 - (int)((k >> 32) & 0xFF);
-  const int64_t wb = cu[b] + (int64_t)(0xFFFFFFFFull - (k & 0xFFFFFFFFull));
-  const int type = prio == 0 ? (int)ner_type[wb] : rt.t[min(prio, kRecognizers) - 1];
-  out[i] = anon_span{b, type, gb - cu[b], ge - cu[b]};
-}
-
+// A wave per tile writes its unions as spans; the blocks above write
 // cu_spans[b] = unions beginning before record b's first byte.
-__global__ __launch_bounds__(256) void rx_cu_kernel(const int* __restrict__ n_runs_p, const int64_t* __restrict__ run_begin,
-                                                    const int64_t* __restrict__ cu, int B, int cap, int* cu_spans,
-                                                    uint32_t* err) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b > B) return;
-  const int total = *n_runs_p;
-  if (b == B) {
-    cu_spans[B] = total;
-    if (total > cap) raise_error(err, ANON_ERR_SPAN_CAP);
+__global__ __launch_bounds__(256) void rx_emit_kernel(const int64_t* __restrict__ cu, int B, int64_t n, int n_tiles,
+                                                      int tile_blocks, RecogBuffers w, int64_t words, anon_span* out,
+                                                      int cap, int* cu_spans, uint32_t* err) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= tile_blocks) {
+    const int b = (blockIdx.x - tile_blocks) * 256 + tid;
+    if (b > B) return;
+    const int total = w.tile_pre[n_tiles];
+    const int64_t x = b == B ? n : min(max(cu[b], (int64_t)0), n);
+    cu_spans[b] = x == n ? total
+                         : w.tile_pre[x / kTile] + w.word_rank[x >> 6] +
+                               __popcll(w.begins[x >> 6] & ((1ull << (x & 63)) - 1));
+    if (b == B && total > cap) raise_error(err, ANON_ERR_SPAN_CAP);
     return;
   }
-  const int64_t x = cu[b];
-  int a = 0, c = total;  // first run with begin >= x
-  while (a < c) {
-    const int m = (a + c) >> 1;
-    if (run_begin[m] < x) a = m + 1;
-    else c = m;
+  const int tile = blockIdx.x * 4 + (tid >> 6), lane = tid & 63;
+  const int64_t i = (int64_t)tile * kTileWords + lane;
+  if (tile >= n_tiles || i >= words) return;
+  unsigned long long u = w.begins[i];
+  int k = w.word_rank[i];
+  for (; u; u &= u - 1, ++k) {
+    const int idx = w.tile_pre[tile] + k;
+    if (idx >= cap) return;
+    const int p = (int)(i * 64) + __ffsll(u) - 1;
+    // its end: the first byte after p not joined to the one before it
+    int64_t j = (p + 1) >> 6;
+    unsigned long long open = ~w.joins[j] & (~0ull << ((p + 1) & 63));
+    while (open == 0) open = ~w.joins[++j];
+    const int e = (int)(j * 64) + __ffsll(open) - 1;
+    const int b = find_record(cu, B, p);
+    out[idx] = anon_span{b, (int)(w.keys[(size_t)tile * kTile + k] & 0xff), p - cu[b], e - cu[b]};
   }
-  cu_spans[b] = a;
 }
 
 }  // namespace
+
+static int64_t recog_tiles(int64_t n) { return (n + kTile - 1) / kTile; }
+static int64_t recog_words(int64_t n) { return n / 64 + 1; }  // a bit per byte and one past the end
 
 size_t recog_workspace_bytes(int64_t n) {
   Carver k(nullptr, SIZE_MAX);
@@ -591,20 +743,16 @@ size_t recog_workspace_bytes(int64_t n) {
 }
 
 RecogBuffers recog_layout(int64_t n, Carver& k) {
+  const int64_t tiles = recog_tiles(n), words = recog_words(n);
   RecogBuffers w;
-  w.delta = k.take<int>(n + 1);
-  w.starts = k.take<int>(n + 1);
-  w.key = k.take<unsigned long long>(n + 1);
-  w.ner_type = k.take<uint8_t>(n + 1);
-  w.cover = k.take<int>(n + 2);
-  w.fstart = k.take<int>(n + 1);
-  w.fend = k.take<int>(n + 1);
-  w.sstart = k.take<int>(n + 2);
-  w.send = k.take<int>(n + 2);
-  w.run_begin = k.take<int64_t>(n + 1);
-  w.run_end = k.take<int64_t>(n + 1);
-  w.run_key = k.take<unsigned long long>(n + 1);
-  w.temp = k.take<uint8_t>(scan_temp_bytes(n + 1));
+  w.begins = k.take<unsigned long long>(2 * words);
+  w.joins = w.begins + words;
+  w.word_rank = k.take<uint16_t>(words);
+  w.n_entries = k.take<int>(tiles + 1);
+  w.tile_count = k.take<int>(tiles + 1);
+  w.tile_pre = k.take<int>(tiles + 1);
+  w.keys = k.take<unsigned long long>(tiles * kTile);
+  w.entries = k.take<RecogEntry>(tiles * kTileEntries);
   return w;
 }
 
@@ -614,37 +762,24 @@ void launch_recognize(const uint8_t* text, const int64_t* cu_bytes, int B, int64
                       anon_span* out, int cap, int* cu_spans, uint32_t* err, hipStream_t s) {
   RecTypes rt;
   for (int k = 0; k < kRecognizers; ++k) rt.t[k] = rec_types[k];
-  const int g = std::max(1, std::min(ceil_div(n + 2, 256), 8192));
-  hipLaunchKernelGGL(rx_clear_kernel, dim3(g), dim3(256), 0, s, w.delta, w.starts, w.key, w.ner_type, n);
-  // run_key is indexed by union number (at most n); the flag arrays are
-  // written in full by rx_flags_kernel
-  launch_fill_u8((uint8_t*)w.run_key, 0, (n + 1) * (int64_t)sizeof(unsigned long long), s);
-  hipLaunchKernelGGL(rx_check_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, err);
-  if (n > 0) {
-    hipLaunchKernelGGL(rx_match_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, s, text, cu_bytes, B, n, rt, w.delta,
-                       w.starts, w.key);
-    hipLaunchKernelGGL(rx_recstart_kernel, dim3(ceil_div(B, 256)), dim3(256), 0, s, text, cu_bytes, B, n, rt,
-                       w.delta, w.starts, w.key);
-    if (rt.t[kIpv6] != 0 || rt.t[kCpe] != 0)
-      hipLaunchKernelGGL(rx_extra_kernel, dim3(ceil_div(n, 256)), dim3(256), 0, s, text, cu_bytes, B, n,
-                         rt.t[kIpv6] != 0 ? 1 : 0, rt.t[kCpe] != 0 ? 1 : 0, w.delta, w.starts, w.key);
-  }
-  if (ner && ner_cu && ner_cap > 0)
-    hipLaunchKernelGGL(rx_ner_kernel, dim3(ceil_div(ner_cap, 256)), dim3(256), 0, s, ner, ner_cu, B, ner_cap,
-                       cu_bytes, n, n_types, w.delta, w.starts, w.key, w.ner_type, err);
-  launch_exclusive_scan_i32(w.delta, w.cover, n + 1, w.temp, s);
-  hipLaunchKernelGGL(rx_flags_kernel, dim3(g), dim3(256), 0, s, w.cover, w.starts, n, w.fstart, w.fend);
-  launch_exclusive_scan_i32(w.fstart, w.sstart, n + 1, w.temp, s);
-  launch_exclusive_scan_i32(w.fend, w.send, n + 1, w.temp, s);
-  hipLaunchKernelGGL(rx_runs_kernel, dim3(g), dim3(256), 0, s, w.fstart, w.sstart, w.fend, w.send, w.key, n,
-                     w.run_begin, w.run_end, w.run_key);
-  // the number of unions is sstart[n + 1]
-  const int* n_runs = w.sstart + (n + 1);
-  if (cap > 0)
-    hipLaunchKernelGGL(rx_emit_kernel, dim3(ceil_div(cap, 256)), dim3(256), 0, s, n_runs, w.run_begin, w.run_end,
-                       w.run_key, w.ner_type, cu_bytes, B, rt, out, cap);
-  hipLaunchKernelGGL(rx_cu_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, s, n_runs, w.run_begin, cu_bytes, B,
-                     cap, cu_spans, err);
+  const int tiles = (int)recog_tiles(n);
+  const int64_t words = recog_words(n);
+  const bool have_ner = ner && ner_cu && ner_cap > 0;
+  // the NER spans' count is on the device: enough blocks for it in a few
+  // rounds, and none that idles in its thousands when the capacity is large
+  const int ner_blocks = have_ner ? std::min(ceil_div(ner_cap, 256), 1024) : 0;
+  const int entry_blocks = ceil_div(tiles, kEntryTiles), tile_blocks = ceil_div(tiles, 4);
+  hipLaunchKernelGGL(rx_init_kernel, dim3(std::max(1, std::min(ceil_div(std::max<int64_t>(2 * words, B + 1), 256), 2048))),
+                     dim3(256), 0, s, w.begins, 2 * words, cu_bytes, B, n, err);
+  if (tiles + ner_blocks > 0)
+    hipLaunchKernelGGL(rx_match_kernel, dim3(tiles + ner_blocks), dim3(256), 0, s, text, cu_bytes, B, n, rt, tiles,
+                       ner, ner_cu, ner_cap, n_types, w, err);
+  if (tiles > 0)
+    hipLaunchKernelGGL(rx_count_kernel, dim3(tile_blocks), dim3(256), 0, s, w, tiles, words);
+  hipLaunchKernelGGL(rx_members_kernel, dim3(1 + entry_blocks + (tiles > 0 ? ner_blocks : 0)), dim3(256), 0, s,
+                     cu_bytes, B, n, tiles, entry_blocks, ner, ner_cu, ner_cap, n_types, w);
+  hipLaunchKernelGGL(rx_emit_kernel, dim3(tile_blocks + ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, tiles,
+                     tile_blocks, w, words, out, cap, cu_spans, err);
 }
 
 }  // namespace anon

@@ -145,12 +145,16 @@ void launch_fill_u8(uint8_t* p, uint8_t v, int64_t n, hipStream_t s);
 void launch_fill_random(void* p, ElemType t, int64_t n, uint32_t seed, hipStream_t s);
 
 // ---- pattern recognizers and overlap resolution ---------------------------
+struct RecogEntry {  // a match: its first byte and its union key
+  int p, pad;
+  unsigned long long key;
+};
 struct RecogBuffers {
-  int *delta, *starts, *cover, *fstart, *fend, *sstart, *send;
-  unsigned long long *key, *run_key;
-  uint8_t* ner_type;
-  int64_t *run_begin, *run_end;
-  void* temp;
+  unsigned long long *begins, *joins;  // bitmaps over the text
+  uint16_t* word_rank;                 // per 64 bytes: unions begun before them in the tile
+  int *n_entries, *tile_count, *tile_pre;
+  unsigned long long* keys;            // per union, at its rank in its tile
+  RecogEntry* entries;
 };
 RecogBuffers recog_layout(int64_t n_bytes, Carver& k);
 size_t recog_workspace_bytes(int64_t n_bytes);
