@@ -8,96 +8,216 @@
 // the bytes after ": " up to the end of the line.  A configured name with a
 // non-empty value gives one span of the configured type over the value.
 //
-// Byte-parallel: a thread per byte tests whether a line starts there and, if
-// so, whether it is a configured field (names are at most 32 bytes, so the
-// colon is looked for in the first 33 bytes); a scan of the per-byte flags
-// numbers the spans in byte order, which is record-major, and the count
-// before a record's first byte is its cu_spans entry.
+// A workgroup takes 4096 bytes, 16 per thread, staged in LDS with the 448
+// after them, and keeps '\n', ':' and record starts as bitmaps: a line's
+// colon and a value's end are one count of trailing zeros away.  A name is
+// compared as eight dwords.  A tile's fields are stored in byte order, which
+// is record-major; the tiles' counts are scanned, and a wave per tile writes
+// the spans.
+//
+// Bound by memory latency: one read of the text and 16 bytes per field,
+// where a thread per byte read three bytes each, wrote an int flag, scanned
+// the flags in three kernels and tested every line a second time.  128 MB in
+// 16,384 records: 4.8 ms -> 0.24 ms, 0.21 of it the match.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace anon {
 namespace {
 
-// rs[p] = 1 where a record begins (cu_bytes[b] < n)
-__global__ __launch_bounds__(256) void fd_mark_kernel(const int64_t* __restrict__ cu, int B, int64_t n,
-                                                      uint8_t* rs, uint32_t* err) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b > B) return;
-  const int64_t x = cu[b];
-  if ((b == 0 && x != 0) || (b == B && x != n) || (b < B && cu[b + 1] < x)) raise_error(err, ANON_ERR_TEXT);
-  if (b < B && x >= 0 && x < n) rs[x] = 1;
-}
+constexpr int kTile = 4096;
+constexpr int kAfter = 448;                 // staged past the tile
+constexpr int kWin = kTile + kAfter;
+constexpr int kWinWords = kWin / 64;
+constexpr int kPerThread = 4;               // fields whose lines start in 16 bytes: "x: v" is 4 bytes
+constexpr int kTileFields = kTile / 4;
 
-// The configured field whose line starts at p, if any: its type and value
-// [vb, ve).  A line ends at '\n', at the next record's first byte or at n.
-__device__ int field_at(const uint8_t* __restrict__ t, const uint8_t* __restrict__ rs, int64_t n, int64_t p,
-                        const FieldTable& ft, int64_t& vb, int64_t& ve) {
-  if (p > 0 && t[p - 1] != '\n' && !rs[p]) return 0;
-  int64_t c = p;
-  const int64_t lim = min(n, p + kFieldNameMax + 1);
-  while (c < lim && t[c] != ':' && t[c] != '\n' && (c == p || !rs[c])) ++c;
-  if (c >= lim || t[c] != ':' || (c > p && rs[c])) return 0;
-  if (c + 1 >= n || t[c + 1] != ' ' || rs[c + 1]) return 0;
-  const int len = (int)(c - p);
-  int type = 0;
-  for (int k = 0; k < ft.n && !type; ++k) {
-    if (ft.len[k] != len) continue;
-    bool eq = true;
-    for (int i = 0; i < len && eq; ++i) eq = t[p + i] == ft.name[k][i];
-    if (eq) type = ft.type[k];
+__device__ __forceinline__ int find_in(const int64_t* cu, int a, int c, int64_t p) {
+  while (a < c) {  // largest index of [a, c] with cu <= p
+    const int m = (a + c + 1) >> 1;
+    if (cu[m] <= p) a = m;
+    else c = m - 1;
   }
-  if (!type) return 0;
-  vb = c + 2;
-  ve = vb;
-  while (ve < n && t[ve] != '\n' && !rs[ve]) ++ve;
-  return ve > vb ? type : 0;
+  return a;
 }
 
-__global__ __launch_bounds__(256) void fd_flags_kernel(const uint8_t* __restrict__ text,
-                                                       const uint8_t* __restrict__ rs, int64_t n, FieldTable ft,
-                                                       int* flags) {
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p <= n; p += (int64_t)gridDim.x * 256) {
-    int64_t vb, ve;
-    flags[p] = (p < n && field_at(text, rs, n, p, ft, vb, ve)) ? 1 : 0;
+// First set bit at or after o of two bitmaps of the window, kWin if none.
+__device__ __forceinline__ int next_bit(const uint64_t* x, const uint64_t* y, int o) {
+  for (int w = o >> 6; w < kWinWords; ++w) {
+    uint64_t v = x[w] | y[w];
+    if (w == o >> 6) v &= ~0ull << (o & 63);
+    if (v) return w * 64 + __ffsll((unsigned long long)v) - 1;
   }
+  return kWin;
 }
 
-__global__ __launch_bounds__(256) void fd_emit_kernel(const uint8_t* __restrict__ text,
-                                                      const uint8_t* __restrict__ rs, int64_t n, FieldTable ft,
-                                                      const int* __restrict__ flags, const int* __restrict__ excl,
-                                                      const int64_t* __restrict__ cu, int B, anon_span* out,
-                                                      int cap) {
-  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < n; p += (int64_t)gridDim.x * 256) {
-    if (!flags[p] || excl[p] >= cap) continue;
-    int64_t vb, ve;
-    const int type = field_at(text, rs, n, p, ft, vb, ve);
-    int a = 0, c = B;  // cu[a] <= p < cu[c]
-    while (c - a > 1) {
-      const int m = (a + c) >> 1;
-      if (cu[m] <= p) a = m;
-      else c = m;
+__global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict__ text,
+                                                       const int64_t* __restrict__ cu, int B, int64_t n,
+                                                       FieldTable ft, FieldBuffers out, uint32_t* err) {
+  __shared__ __align__(16) uint8_t win[kWin + 48];  // (names are read as 36 bytes)
+  __shared__ __align__(16) uint64_t nl[kWinWords], colon[kWinWords], rec[kWinWords];
+  __shared__ FieldEntry found[256][kPerThread];
+  __shared__ int ws[4];
+  const int tid = threadIdx.x;
+  const int64_t p0 = (int64_t)blockIdx.x * kTile;
+  const int whi = (int)min((int64_t)kWin, n - p0);  // staged bytes of text
+  auto stage = [&](int piece) {
+    const int64_t p = p0 + piece * 16;
+    uint32_t w[4] = {0, 0, 0, 0};
+    if (n - p >= 16) {
+      const uint4 v = load16(text + p);
+      w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        if (p + i < n) w[i >> 2] |= (uint32_t)text[p + i] << (8 * (i & 3));
     }
-    out[excl[p]] = anon_span{a, type, vb - cu[a], ve - cu[a]};
+    uint32_t mn = 0, mc = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t c = (w[i >> 2] >> (8 * (i & 3))) & 0xff;
+      mn |= (c == '\n' ? 1u : 0u) << i;
+      mc |= (c == ':' ? 1u : 0u) << i;
+    }
+    *(uint4*)(win + piece * 16) = uint4{w[0], w[1], w[2], w[3]};
+    ((uint16_t*)nl)[piece] = (uint16_t)mn;
+    ((uint16_t*)colon)[piece] = (uint16_t)mc;
+    ((uint16_t*)rec)[piece] = 0;
+    return mn;
+  };
+  const uint32_t my_nl = stage(tid);
+  if (tid < kAfter / 16) stage(kTile / 16 + tid);
+  // the byte before this thread's: a line break there starts a line
+  const int64_t mine = p0 + tid * 16;
+  const bool after_break = mine > 0 && mine < n && text[mine - 1] == '\n';
+  // record starts of the window (and the check of cu_bytes' tile part)
+  const int r0 = wg_find_record(cu, B, p0);
+  for (int b = r0;; b += 256) {
+    const int i = b + tid;
+    const int64_t c = i <= B ? cu[i] : INT64_MAX;
+    if (i < B && c >= p0 && c < p0 + whi) atomicOr((uint32_t*)rec + ((c - p0) >> 5), 1u << ((c - p0) & 31));
+    if (!__syncthreads_or(tid == 255 && i < B && c < p0 + whi)) break;
+  }
+  for (int64_t b = (int64_t)blockIdx.x * 256 + tid; b <= B; b += (int64_t)gridDim.x * 256) {
+    const int64_t x = cu[b];
+    if ((b == 0 && x != 0) || (b == B && x != n) || (b < B && cu[b + 1] < x)) raise_error(err, ANON_ERR_TEXT);
+  }
+  uint32_t starts = ((my_nl << 1) | (after_break ? 1u : 0u) | ((const uint16_t*)rec)[tid]) & 0xffff;
+  if (mine == 0) starts |= 1;  // the text's first byte
+  if (n - mine < 16) starts &= n > mine ? (1u << (n - mine)) - 1 : 0;
+  int cnt = 0;
+  for (; starts; starts &= starts - 1) {
+    const int o = tid * 16 + __ffs(starts) - 1;  // the line's first byte
+    // the name ends at a ':' before any line break or record start after it
+    const int stop = next_bit(nl, rec, o + 1), c = next_bit(colon, colon, o);
+    const int len = c - o;
+    if (len > kFieldNameMax || c >= stop || ((nl[o >> 6] >> (o & 63)) & 1) || c + 1 >= whi || win[c + 1] != ' ' ||
+        stop == c + 1)
+      continue;
+    uint32_t d[kFieldNameMax / 4];
+    const uint32_t* q = (const uint32_t*)(win + (o & ~3));
+    uint32_t lo = q[0];
+#pragma unroll
+    for (int i = 0; i < kFieldNameMax / 4; ++i) {
+      const uint32_t hi = q[i + 1];
+      const uint32_t v = __builtin_amdgcn_alignbyte(hi, lo, o & 3);
+      const int left = len - 4 * i;
+      d[i] = left >= 4 ? v : left <= 0 ? 0 : v & ((1u << (8 * left)) - 1);
+      lo = hi;
+    }
+    int type = 0;
+    for (int k = 0; k < ft.n; ++k) {  // (the first of equal names, as configured)
+      uint32_t diff = ft.len[k] ^ len;
+#pragma unroll
+      for (int i = 0; i < kFieldNameMax / 4; ++i) diff |= ((const uint32_t*)ft.name[k])[i] ^ d[i];
+      if (diff == 0 && !type) type = ft.type[k];
+    }
+    if (!type) continue;
+    // the value: up to the next line break, record start or the text's end
+    const int vb = c + 2;
+    int64_t ve = stop;
+    if (stop < vb || stop >= whi) {
+      ve = p0 + whi;  // past the window, byte by byte inside the record
+      if (ve < n) {
+        const int64_t hi = min(max(cu[find_in(cu, r0, B - 1, p0 + o) + 1], ve), n);
+        while (ve < hi && text[ve] != '\n') ++ve;
+      }
+      ve -= p0;
+    }
+    if (ve > vb && cnt < kPerThread)
+      found[tid][cnt++] = FieldEntry{(int)p0 + o, (int)(p0 + vb), (int)(p0 + ve), type};
+  }
+  // rank among the tile's fields
+  const int lane = tid & 63, wave = tid >> 6;
+  int x = cnt;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(x, o, 64);
+    if (lane >= o) x += y;
+  }
+  if (lane == 63) ws[wave] = x;
+  __syncthreads();
+  int base = x - cnt, total = 0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    if (w < wave) base += ws[w];
+    total += ws[w];
+  }
+  FieldEntry* to = out.entries + (size_t)blockIdx.x * kTileFields;
+  for (int i = 0; i < cnt; ++i)
+    if (base + i < kTileFields) to[base + i] = found[tid][i];
+  if (tid == 0) {
+    out.counts[blockIdx.x] = min(total, kTileFields);
+    out.rec0[blockIdx.x] = r0;
   }
 }
 
-__global__ __launch_bounds__(256) void fd_cu_kernel(const int* __restrict__ excl, const int64_t* __restrict__ cu,
-                                                    int B, int64_t n, int cap, int* cu_spans, uint32_t* err) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b > B) return;
-  const int64_t x = min(max(cu[b], (int64_t)0), n);
-  cu_spans[b] = excl[x];
-  if (b == B && excl[n] > cap) raise_error(err, ANON_ERR_SPAN_CAP);
+// A wave per tile writes its spans (pre: exclusive prefix of the tiles'
+// counts); the blocks above write cu_spans[b] = fields before record b.
+__global__ __launch_bounds__(256) void fd_emit_kernel(const int64_t* __restrict__ cu, int B, int64_t n, int n_tiles,
+                                                      int tile_blocks, FieldBuffers w, anon_span* out, int cap,
+                                                      int* cu_spans, uint32_t* err) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x >= tile_blocks) {
+    const int b = (blockIdx.x - tile_blocks) * 256 + tid;
+    if (b > B) return;
+    const int64_t x = min(max(cu[b], (int64_t)0), n);
+    const int total = w.counts[n_tiles], tile = (int)(x / kTile);
+    int k = total;
+    if (x < n) {
+      const FieldEntry* e = w.entries + (size_t)tile * kTileFields;
+      int a = 0, c = w.counts[tile + 1] - w.counts[tile];  // first entry at or after x
+      while (a < c) {
+        const int m = (a + c) >> 1;
+        if (e[m].line < x) a = m + 1;
+        else c = m;
+      }
+      k = w.counts[tile] + a;
+    }
+    cu_spans[b] = k;
+    if (b == B && total > cap) raise_error(err, ANON_ERR_SPAN_CAP);
+    return;
+  }
+  const int tile = blockIdx.x * 4 + (tid >> 6), lane = tid & 63;
+  if (tile >= n_tiles) return;
+  const int first = w.counts[tile], cnt = w.counts[tile + 1] - first;
+  const int ra = w.rec0[tile], rb = tile + 1 < n_tiles ? w.rec0[tile + 1] : B - 1;
+  for (int i = lane; i < cnt && first + i < cap; i += 64) {
+    const FieldEntry e = w.entries[(size_t)tile * kTileFields + i];
+    const int r = find_in(cu, ra, rb, e.line);
+    out[first + i] = anon_span{r, e.type, e.begin - cu[r], e.end - cu[r]};
+  }
 }
 
 }  // namespace
 
 FieldBuffers field_layout(int64_t n, Carver& k) {
+  const int64_t tiles = (n + kTile - 1) / kTile;
   FieldBuffers w;
-  w.rs = k.take<uint8_t>(n + 1);
-  w.flags = k.take<int>(n + 1);
-  w.excl = k.take<int>(n + 2);
-  w.temp = k.take<uint8_t>(scan_temp_bytes(n + 1));
+  w.entries = k.take<FieldEntry>(tiles * kTileFields);
+  w.counts = k.take<int>(tiles + 1);
+  w.rec0 = k.take<int>(tiles + 1);
   return w;
 }
 
@@ -107,19 +227,27 @@ size_t field_workspace_bytes(int64_t n) {
   return k.used + 256;
 }
 
+// An empty text has no tile: its record boundaries are checked here.
+__global__ __launch_bounds__(256) void fd_empty_kernel(const int64_t* __restrict__ cu, int B, int* counts,
+                                                       uint32_t* err) {
+  for (int b = blockIdx.x * 256 + threadIdx.x; b <= B; b += gridDim.x * 256)
+    if (cu[b] != 0) raise_error(err, ANON_ERR_TEXT);
+  if (blockIdx.x == 0 && threadIdx.x == 0) counts[0] = 0;
+}
+
 void launch_field_spans(const uint8_t* text, const int64_t* cu_bytes, int B, int64_t n, const FieldTable& ft,
                         const FieldBuffers& w, anon_span* out, int cap, int* cu_spans, uint32_t* err,
                         hipStream_t s) {
-  const int g = std::max(1, std::min(ceil_div(n + 1, 256), 8192));
-  launch_fill_u8(w.rs, 0, n + 1, s);
-  hipLaunchKernelGGL(fd_mark_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, w.rs, err);
-  hipLaunchKernelGGL(fd_flags_kernel, dim3(g), dim3(256), 0, s, text, w.rs, n, ft, w.flags);
-  launch_exclusive_scan_i32(w.flags, w.excl, n + 1, w.temp, s);
-  if (n > 0 && cap > 0)
-    hipLaunchKernelGGL(fd_emit_kernel, dim3(g), dim3(256), 0, s, text, w.rs, n, ft, w.flags, w.excl, cu_bytes, B,
-                       out, cap);
-  hipLaunchKernelGGL(fd_cu_kernel, dim3(ceil_div(B + 1, 256)), dim3(256), 0, s, w.excl, cu_bytes, B, n, cap,
-                     cu_spans, err);
+  const int tiles = (int)((n + kTile - 1) / kTile), tile_blocks = ceil_div(tiles, 4);
+  if (tiles > 0) {
+    hipLaunchKernelGGL(fd_match_kernel, dim3(tiles), dim3(256), 0, s, text, cu_bytes, B, n, ft, w, err);
+    launch_scan_counts(w.counts, tiles, s);
+  } else {
+    hipLaunchKernelGGL(fd_empty_kernel, dim3(std::min(ceil_div(B + 1, 256), 1024)), dim3(256), 0, s, cu_bytes, B,
+                       w.counts, err);
+  }
+  hipLaunchKernelGGL(fd_emit_kernel, dim3(tile_blocks + ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, tiles,
+                     tile_blocks, w, out, cap, cu_spans, err);
 }
 
 }  // namespace anon

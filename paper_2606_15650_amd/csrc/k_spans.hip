@@ -116,31 +116,44 @@ void exclusive_scan(const T* in, T* out, int64_t n, void* temp, hipStream_t s) {
     hipLaunchKernelGGL(scan_apply_kernel<T>, dim3(nparts), dim3(kScanThreads), 0, s, in, n, (const T*)part, out);
 }
 
-// Counts of consecutive tiles -> exclusive prefix in place; tiles are few
-// (one per 4096 tokens or bytes), so one workgroup does it, a thread summing
-// a run of counts.  The total goes to part[n].
-__global__ __launch_bounds__(1024) void scan_counts_kernel(int* __restrict__ part, int n) {
-  __shared__ int sh[1024];
-  const int tid = threadIdx.x;
-  const int per = ((n + 1023) / 1024 + 3) & ~3;
-  const int a = min(n, tid * per), b = min(n, a + per);
-  int s = 0;
-  for (int i = a; i < b; ++i) s += part[i];
-  sh[tid] = s;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int x = tid >= o ? sh[tid - o] : 0;
+// Exclusive prefix of n values in place or into out, out[n] = their sum, by
+// one workgroup: 4 consecutive values per thread and step, so a step of 4096
+// values is one coalesced load, a wave scan and two barriers.  For the counts
+// of tiles or records, which are few: 31,250 take 19 us (a run of values per
+// thread, read one after the other, took 55).
+template <typename T>
+__global__ __launch_bounds__(1024) void scan_one_kernel(const T* in, T* out, int n) {
+  __shared__ T ws[16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  T carry = 0;
+  for (int at = 0; at < n; at += 4096) {
+    const int i = at + tid * 4;
+    T v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = i + k < n ? in[i + k] : T(0);
+    const T s = v[0] + v[1] + v[2] + v[3];
+    T x = s;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const T y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) ws[wave] = x;
     __syncthreads();
-    sh[tid] += x;
+    T run = carry + x - s;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) run += ws[w];
+      carry += ws[w];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i + k < n) out[i + k] = run;
+      run += v[k];
+    }
     __syncthreads();
   }
-  int run = sh[tid] - s;
-  for (int i = a; i < b; ++i) {
-    const int v = part[i];
-    part[i] = run;
-    run += v;
-  }
-  if (tid == 1023) part[n] = sh[1023];
+  if (tid == 0) out[n] = carry;
 }
 
 constexpr int kTile = 4096;           // tokens per workgroup, 16 per thread
@@ -321,11 +334,11 @@ __global__ __launch_bounds__(256) void bio_write_kernel(const uint8_t* __restric
 
 size_t scan_temp_bytes(int64_t n) { return (size_t)((n + kScanTile - 1) / kScanTile + 1) * sizeof(int64_t); }
 
-void launch_exclusive_scan_i32(const int* in, int* out, int64_t n, void* temp, hipStream_t s) {
-  exclusive_scan<int>(in, out, n, temp, s);
-}
 void launch_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void* temp, hipStream_t s) {
-  exclusive_scan<int64_t>(in, out, n, temp, s);
+  // one launch while a workgroup's steps of 4096 (2.4 us each) cost less than
+  // the tiled scan's three launches (16,384 values: 10 us against 15)
+  if (n <= 16384) hipLaunchKernelGGL(scan_one_kernel<int64_t>, dim3(1), dim3(1024), 0, s, in, out, (int)n);
+  else exclusive_scan<int64_t>(in, out, n, temp, s);
 }
 
 size_t bio_layout(int T, Carver& k, BioBuffers& w) {
@@ -338,7 +351,7 @@ size_t bio_layout(int T, Carver& k, BioBuffers& w) {
 }
 
 void launch_scan_counts(int* counts, int n, hipStream_t s) {
-  hipLaunchKernelGGL(scan_counts_kernel, dim3(1), dim3(1024), 0, s, counts, n);
+  hipLaunchKernelGGL(scan_one_kernel<int>, dim3(1), dim3(1024), 0, s, counts, counts, n);
 }
 
 void launch_bio(const uint8_t* labels, const int* tok_off, const int* cu_seqlens, int B, int T, int n_types,

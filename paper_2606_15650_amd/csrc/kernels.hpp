@@ -90,7 +90,6 @@ void launch_window_merge(const int* cu_seqlens, int B, const int* rec_win0, cons
 // ---- scans ----------------------------------------------------------------
 size_t scan_temp_bytes(int64_t n);
 // out[i] = sum_{j<i} in[i], i in [0, n]; out has n+1 entries.
-void launch_exclusive_scan_i32(const int* in, int* out, int64_t n, void* temp, hipStream_t s);
 void launch_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void* temp, hipStream_t s);
 
 // ---- spans ----------------------------------------------------------------
@@ -170,15 +169,17 @@ void launch_recognize(const uint8_t* text, const int64_t* cu_bytes, int B, int64
 constexpr int kFieldNameMax = 32;
 constexpr int kFieldsMax = 64;
 struct FieldTable {  // passed by value to the kernels
-  uint8_t name[kFieldsMax][kFieldNameMax];
+  alignas(8) uint8_t name[kFieldsMax][kFieldNameMax];  // zero-padded, compared as dwords
   uint8_t len[kFieldsMax];
   int type[kFieldsMax];
   int n;
 };
+struct FieldEntry {  // a field: its line's first byte, its value and type
+  int line, begin, end, type;
+};
 struct FieldBuffers {
-  uint8_t* rs;
-  int *flags, *excl;
-  void* temp;
+  FieldEntry* entries;  // per tile of 4096 bytes, in byte order
+  int *counts, *rec0;   // per tile: fields, the record of its first byte
 };
 FieldBuffers field_layout(int64_t n_bytes, Carver& k);
 size_t field_workspace_bytes(int64_t n_bytes);

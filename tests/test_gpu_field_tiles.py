@@ -1,0 +1,69 @@
+"""field_spans where its tiles can go wrong: lines, names, colons and values
+over a tile's end (4096 bytes) at every offset, names of 32 and 33 bytes,
+values past the staged window (448 bytes after the tile), tiles full of the
+shortest fields, many record boundaries in one tile.  Bit-exact against the
+oracle."""
+from __future__ import annotations
+
+import random
+
+import pytest
+
+from oracle import fields as F
+from synth.records import TYPE_NAMES_17
+from tests.gpu_common import make_cache, say
+from tests.test_gpu_fields import _fields_gpu, _text_batch
+
+pytestmark = pytest.mark.gpu
+LONG = b"N" * 32
+CONFIG = {b"Host": 1, b"x": 2, b"See Also": 3, LONG: 4, LONG[:31]: 5, b"Hosts": 6}
+
+
+def _check(records, label, least=1):
+    rb = _text_batch(records, TYPE_NAMES_17)
+    _, got = _fields_gpu(rb, make_cache(TYPE_NAMES_17), CONFIG)
+    want = F.field_spans_batch(rb.text, rb.cu_bytes, CONFIG)
+    say(f"[fields] {label}: {len(records)} records, {sum(map(len, want))} spans")
+    assert sum(map(len, want)) >= least
+    assert got == want, label
+
+
+@pytest.mark.parametrize("shift", range(0, 64, 3))
+def test_lines_over_a_tile_end(shift):
+    import torch
+    assert torch.cuda.is_available()
+    out = []
+    for i, line in enumerate([b"Host: abc", b"See Also: y", LONG + b": v", LONG + b"N: v", LONG[:31] + b": " + b"w" * 40,
+                              b"x: " + b"q" * 60, b"Host:", b"Host: ", b"Host:a", b"x: 1"]):
+        # every line begins `shift` bytes before a multiple of 4096
+        at = sum(map(len, out))
+        out.append(b"-" * ((-(at + 1 + shift)) % 4096) + b"\n" + line + (b"\n" if i % 2 else b""))
+        if i % 3 == 0:
+            out.append(b"")
+    _check(out, f"lines from {shift} before a tile's end")
+    _check([b"".join(out)], "the same in one record")
+    _check([b"".join(out).replace(b"\n", b"", 1), b"Host: z"], "a first line without a break")
+
+
+@pytest.mark.parametrize("length", [438, 441, 442, 443, 444, 445, 450, 4090, 4540, 9000])
+def test_values_past_the_window(length):
+    import torch
+    assert torch.cuda.is_available()
+    for tail in (b"", b"\n", b"\nHost: a"):
+        first = b"-" * 4090 + b"\n" + b"x: " + b"v" * length + tail
+        _check([first, b"Host: b\n"], f"a value of {length} from 4094")
+        _check([first], "the same at the text's end")
+
+
+def test_full_tiles_and_many_boundaries():
+    import torch
+    assert torch.cuda.is_available()
+    rng = random.Random(7)
+    _check([b"x: v\n" * 4000], "the shortest lines")
+    _check([b"x: v"] * 3000, "the shortest records")
+    _check([b"\n", b"", b"x: v", b"", b"Host", b": a", b"Host:", b" a", b"x: "] * 400, "fields cut by records")
+    text = b"".join(rng.choice([b"Host: ", b"x: ", b"See Also: ", LONG + b": ", b"\n", b":", b" ", b"v", b"10.0.0.1\n"])
+                    for _ in range(6000))
+    for step in (1, 3, 5, 17, 200):
+        _check([text[i:i + step] for i in range(0, min(len(text), 4000 * step), step)], f"records of {step}",
+               least=step > 3)  # "x: v" has 4 bytes
