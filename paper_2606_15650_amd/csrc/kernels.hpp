@@ -105,6 +105,7 @@ void launch_bio(const uint8_t* labels, const int* tok_off, const int* cu_seqlens
 void launch_scan_counts(int* counts, int n, hipStream_t s);
 
 // ---- pseudonyms -----------------------------------------------------------
+constexpr int kCounterSlots = 64;
 struct PcacheDev {
   uint8_t* table;         // capacity entries
   uint64_t mask;          // capacity - 1
@@ -113,7 +114,7 @@ struct PcacheDev {
   int n_types;
   const uint8_t* names;   // concatenated type names
   const int* name_off;    // [n_types + 1]
-  unsigned long long* counters;  // [0] lookups, [1] hits, [2] inserts
+  unsigned long long* counters;  // kCounterSlots x [lookups, hits, inserts, unused x 5], summed by the reader
   int enabled;
   uint32_t preserve[4];   // bit t: spans of type t are left as they are
   uint32_t call;          // number of this pseudonymize call on the cache (1-based)

@@ -1324,7 +1324,7 @@ anon_status anon_pcache_create(const uint8_t* h_key, size_t key_len, int32_t slu
   lay.take<uint8_t>(cap * pcache_entry_bytes());
   lay.take<uint8_t>(names.size());
   lay.take<int>(offs.size());
-  lay.take<unsigned long long>(4);
+  lay.take<unsigned long long>(8 * kCounterSlots);
   if (hipMalloc(&p->mem, lay.used) != hipSuccess) {
     delete p;
     return set_error(ANON_ENOMEM, "cannot allocate the pseudonym table");
@@ -1333,7 +1333,7 @@ anon_status anon_pcache_create(const uint8_t* h_key, size_t key_len, int32_t slu
   p->dev.table = k.take<uint8_t>(cap * pcache_entry_bytes());
   uint8_t* dn = k.take<uint8_t>(names.size());
   int* doff = k.take<int>(offs.size());
-  p->dev.counters = k.take<unsigned long long>(4);
+  p->dev.counters = k.take<unsigned long long>(8 * kCounterSlots);
   p->dev.mask = (uint64_t)cap - 1;
   p->dev.slug = slug_hex;
   p->dev.n_types = n_types;
@@ -1365,7 +1365,7 @@ anon_status anon_pcache_clear(anon_pcache* p, void* stream) {
   ANON_HIP_CHECK(hipSetDevice(p->device));
   hipStream_t s = (hipStream_t)stream;
   launch_fill_u8(p->dev.table, 0, p->capacity * (int64_t)pcache_entry_bytes(), s);
-  launch_fill_u8((uint8_t*)p->dev.counters, 0, 4 * sizeof(unsigned long long), s);
+  launch_fill_u8((uint8_t*)p->dev.counters, 0, 8 * kCounterSlots * sizeof(unsigned long long), s);
   ANON_HIP_CHECK(hipGetLastError());
   p->calls = 0;
   return ANON_OK;
@@ -1442,8 +1442,10 @@ anon_status anon_pcache_stats(anon_pcache* p, int64_t* lookups, int64_t* hits, i
   if (!p) return set_error(ANON_EINVAL, "cache is NULL");
   ANON_HIP_CHECK(hipSetDevice(p->device));
   ANON_HIP_CHECK(hipDeviceSynchronize());
-  unsigned long long c[4];
-  ANON_HIP_CHECK(hipMemcpy(c, p->dev.counters, sizeof(c), hipMemcpyDeviceToHost));
+  unsigned long long slots[8 * kCounterSlots], c[3] = {0, 0, 0};
+  ANON_HIP_CHECK(hipMemcpy(slots, p->dev.counters, sizeof(slots), hipMemcpyDeviceToHost));
+  for (int i = 0; i < kCounterSlots; ++i)
+    for (int k = 0; k < 3; ++k) c[k] += slots[8 * i + k];
   if (lookups) *lookups = (int64_t)c[0];
   if (hits) *hits = (int64_t)c[1];
   if (entries) *entries = (int64_t)c[2];
