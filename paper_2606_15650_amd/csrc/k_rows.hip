@@ -11,6 +11,7 @@
 // rows of the batch.  The classifier runs on the FP32 matrix cores, 32
 // tokens per wave.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 
@@ -28,6 +29,20 @@ __device__ __forceinline__ int find_record(const int* cu, int B, int t) {
     const int mid = (lo + hi + 1) >> 1;
     if (cu[mid] <= t) lo = mid;
     else hi = mid - 1;
+  }
+  return lo;
+}
+
+// The same by a whole wave for a wave-uniform t: 64 boundaries a step, so two
+// dependent reads for up to 4096 records instead of twelve.
+__device__ __forceinline__ int wave_find_record(const int* cu, int B, int t, int lane) {
+  int lo = 0, n = B;
+  while (n > 1) {
+    const int step = (n + 63) / 64, i = lane * step;
+    const uint64_t below = __ballot(lane == 0 || (i < n && cu[lo + i] <= t));
+    const int k = 63 - __clzll((long long)below);
+    lo += k * step;
+    n = min(step, n - k * step);
   }
   return lo;
 }
@@ -122,6 +137,10 @@ __device__ __forceinline__ void ln_store(float (&v)[NPL], const float (&gv)[NPL]
   }
 }
 
+// A wave takes one token: its table row is requested before its record is
+// looked for, by the whole wave.  Bound by the gathered table rows and the
+// output: 855,000 rows of 768, 802 -> 696 us (5.6 TB/s); two or four rows a
+// wave, with one search, took 754 and 891.
 template <int NPL>
 __global__ __launch_bounds__(256) void embed_ln_kernel(const int* __restrict__ ids, const int* __restrict__ cu,
                                                        int B, int T_cap, const float* __restrict__ tok,
@@ -139,11 +158,11 @@ __global__ __launch_bounds__(256) void embed_ln_kernel(const int* __restrict__ i
     if (lane == 0) raise_error(err, ANON_ERR_TOKEN_ID);
     id = 0;
   }
-  const int r = find_record(cu, B, t);
-  const int p = min(max(t - cu[r], 0), max_pos - 1);
-  if (pos_out && lane == 0) pos_out[t] = p;
   float v[NPL];
   load_row<NPL>(tok + (size_t)id * h, lane, v);
+  const int r = wave_find_record(cu, B, t, lane);
+  const int p = min(max(t - cu[r], 0), max_pos - 1);
+  if (pos_out && lane == 0) pos_out[t] = p;
   if (pos) {  // learned absolute positions (no table: positions enter elsewhere)
     float w[NPL];
     load_row<NPL>(pos + (size_t)p * h, lane, w);
@@ -179,80 +198,146 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const TY* __restrict__ y
     if (row0 + k < rows) ln_store<NPL>(v[k], gv, bv, eps, h, lane, row0 + k, out, out_t, out_q, q_inv_scale);
 }
 
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (N > 0) {
+    static_for<N - 1>(f);
+    f(std::integral_constant<int, N - 1>());
+  }
+}
+
 constexpr int kMaxLabels = 64;
 #ifndef ANON_LN_RPW
 #define ANON_LN_RPW 2
 #endif
 
-// Token classifier on the FP32 matrix cores (C <= 32 labels): one wave forms
-// z^T = Wc x^T for 32 tokens with v_mfma_f32_32x32x2_f32, exact products of
-// the FP32 head and the (bf16 or FP32) hidden state, FP32 sums.  Lane half hh
-// feeds the k-index hh of every MFMA from its own 16-element slice of each
-// 32-column chunk.  Then lane l holds the logits of token (l & 31) for
-// classes (r/4)*8 + hh*4 + r%4 of register r; the two halves merge their
-// top-2 with one exchange (ties to the lowest class index).
-template <typename TX, int H>
-__global__ __launch_bounds__(256) void classifier_mfma_kernel(const TX* __restrict__ x, const float* __restrict__ wc,
-                                                              const float* __restrict__ bc, int T_cap, int C,
-                                                              uint8_t* __restrict__ labels,
-                                                              float* __restrict__ logits, float* __restrict__ margin,
-                                                              const int* t_dev) {
-  const int lane = threadIdx.x & 63;
+// Token classifier on the FP32 matrix cores (C <= 16 NB labels): a wave forms
+// z^T = Wc x^T for 16 tokens with v_mfma_f32_16x16x4_f32, exact products of
+// the FP32 head and the (bf16 or FP32) hidden state, FP32 sums.  Lane group q
+// (16 lanes) feeds k-index q of every MFMA from the 16-element slice q & 1 of
+// each 32-column chunk, its elements 2e + (q >> 1).  Then lane l holds the
+// logits of token (l & 15) for classes n*16 + (l/16)*4 + r; the four groups
+// merge their top-2 with two exchanges (ties to the lowest class).
+//
+// The head is laid out in LDS once per workgroup in the order in which lanes
+// read it (every read 1 KB without conflicts); the hidden state comes straight
+// from memory, kAheadX pairs of chunks in flight.  Bound by latency for a
+// small batch (137 tokens of 768: 32 -> 17 us; 32x32x2 MFMAs with each
+// chunk's loads waited for before) and by the MFMAs for a large one (162,000
+// tokens: 112 -> 108 us).
+constexpr int kClsWaves = 8;
+template <typename TX, int H, int NB>
+__global__ __launch_bounds__(kClsWaves * 64) void classifier_mfma_kernel(
+    const TX* __restrict__ x, const float* __restrict__ wc, const float* __restrict__ bc, int T_cap, int C,
+    uint8_t* __restrict__ labels, float* __restrict__ logits, float* __restrict__ margin, const int* t_dev) {
+  constexpr int kPairs = H / 64, kAheadX = kPairs < 4 ? kPairs : 4;
+  static_assert(kPairs % kAheadX == 0, "the ring divides the chunks");
+  __shared__ floatx4 head[kPairs * 2 * NB * 2 * 64];  // [chunk][n][half][lane] of 4 values
+  const int tid = threadIdx.x, lane = tid & 63;
   const int T = live_rows(T_cap, t_dev);
-  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-  if (t0 >= T) return;
-  const int hh = lane >> 5, r32 = lane & 31;
-  const int tok = min(t0 + r32, T - 1);  // rows past T re-read row T-1, never stored
-  const bool cvalid = r32 < C;
-  const TX* xr = x + (size_t)tok * H + hh * 16;
-  const float* wr = wc + (size_t)(cvalid ? r32 : 0) * H + hh * 16;
-  floatx16 acc;
+  const int tiles = (T + 15) / 16;
+  const int q = lane >> 4, r16 = lane & 15, slice = (q & 1) * 16;
+  const bool odd_k = q >> 1;
+  typedef TX vec8 __attribute__((ext_vector_type(8)));
+  vec8 xv[kAheadX][4];  // pairs of chunks of 16 elements
+  auto row = [&](int tile) {  // rows past T re-read row T-1, never stored
+    return x + (size_t)max(min(tile * 16 + r16, T - 1), 0) * H + slice;
+  };
+  auto load = [&](auto slot, const TX* xr, int p) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  for (int kc = 0; kc < H / 32; ++kc) {
-    float xv[16], wv[16];
+    for (int e = 0; e < 4; ++e) xv[decltype(slot)::value][e] = *(const vec8*)(xr + p * 64 + (e >> 1) * 32 + (e & 1) * 8);
+  };
+  int tile = blockIdx.x + gridDim.x * (tid >> 6);
+  const TX* xr = row(tile);
+  static_for<kAheadX>([&](auto d) { load(d, xr, decltype(d)::value); });
+  for (int i = tid; i < NB * 16 * (H / 4); i += kClsWaves * 64) {
+    const int c = (i & 15) + i / (16 * (H / 4)) * 16;  // class (16 to a wave: their places' banks differ)
+    const int k = (i >> 4) % (H / 4) * 4;              // columns k..k+3
+    const floatx4 v = c < C ? *(const floatx4*)(wc + (size_t)c * H + k) : floatx4{0.f, 0.f, 0.f, 0.f};
+    const int chunk = k >> 5, in = k & 15, sl = (k >> 4) & 1;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) xv[e] = ldf(xr + kc * 32 + e);
-#pragma unroll
-    for (int e = 0; e < 16; e += 4) {
-      const floatx4 w4 = *(const floatx4*)(wr + kc * 32 + e);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) wv[e + k] = cvalid ? w4[k] : 0.f;
+    for (int j = 0; j < 4; ++j) {  // element in + j: half (in+j)/8, place (in+j)/2 % 4, of group sl or 2 + sl
+      const int e = (in + j) >> 1, group = sl + 2 * (j & 1);
+      ((float*)(head + ((chunk * NB + (c >> 4)) * 2 + (e >> 2)) * 64 + group * 16 + (c & 15)))[e & 3] = v[j];
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(wv[e], xv[e], acc, 0, 0, 0);
   }
-  float best = -INFINITY, second = -INFINITY;
-  int arg = 0;
+  __syncthreads();
+  floatx4 wv[2][NB][2];  // of this chunk and the next
+  auto read = [&](floatx4 (&w)[NB][2], int chunk) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int c = (r >> 2) * 8 + hh * 4 + (r & 3);  // increasing in r
-    if (c < C) {
-      const float z = acc[r] + bc[c];
-      if (logits && t0 + r32 < T) logits[(size_t)(t0 + r32) * C + c] = z;
-      if (z > best) {
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int f = 0; f < 2; ++f) w[n][f] = head[((chunk * NB + n) * 2 + f) * 64 + lane];
+  };
+  read(wv[0], 0);
+  for (; tile < tiles; tile += gridDim.x * kClsWaves) {
+    const int t0 = tile * 16;
+    floatx4 acc[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) acc[n] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int p0 = 0; p0 < kPairs; p0 += kAheadX) {
+      static_for<kAheadX>([&](auto slot) {
+        constexpr int D = decltype(slot)::value;
+        const int p = p0 + D;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          const int next = p * 2 + c + 1 < kPairs * 2 ? p * 2 + c + 1 : 0;  // (chunk 0 for the next tile)
+          read(wv[1 - c], next);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float x0 = static_cast<float>(xv[D][2 * c + (e >> 2)][(2 * e) & 7]);
+            const float x1 = static_cast<float>(xv[D][2 * c + (e >> 2)][(2 * e + 1) & 7]);
+            const float xe = odd_k ? x1 : x0;
+#pragma unroll
+            for (int n = 0; n < NB; ++n)
+              acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[c][n][e >> 2][e & 3], xe, acc[n], 0, 0, 0);
+          }
+        }
+        if (p + kAheadX < kPairs) load(slot, xr, p + kAheadX);
+        __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the next MFMAs)
+      });
+    }
+    xr = row(tile + gridDim.x * kClsWaves);
+    static_for<kAheadX>([&](auto d) { load(d, xr, decltype(d)::value); });
+    float best = -INFINITY, second = -INFINITY;
+    int arg = 0;
+#pragma unroll
+    for (int n = 0; n < NB; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int c = n * 16 + q * 4 + r;  // increasing
+        if (c < C) {
+          const float z = acc[n][r] + bc[c];
+          if (logits && t0 + r16 < T) logits[(size_t)(t0 + r16) * C + c] = z;
+          if (z > best) {
+            second = best;
+            best = z;
+            arg = c;
+          } else if (z > second) {
+            second = z;
+          }
+        }
+      }
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+      const float ob = __shfl_xor(best, o, 64), os = __shfl_xor(second, o, 64);
+      const int oa = __shfl_xor(arg, o, 64);
+      if (best > ob) {
+        second = fmaxf(second, ob);
+      } else if (ob > best) {
+        second = fmaxf(os, best);
+        best = ob;
+        arg = oa;
+      } else {
+        arg = min(arg, oa);
         second = best;
-        best = z;
-        arg = c;
-      } else if (z > second) {
-        second = z;
       }
     }
-  }
-  const float ob = __shfl_xor(best, 32, 64), os = __shfl_xor(second, 32, 64);
-  const int oa = __shfl_xor(arg, 32, 64);
-  if (hh == 0 && t0 + r32 < T) {
-    float b1, b2;
-    int a1;
-    if (best > ob) {
-      b1 = best, a1 = arg, b2 = fmaxf(second, ob);
-    } else if (ob > best) {
-      b1 = ob, a1 = oa, b2 = fmaxf(os, best);
-    } else {
-      b1 = best, a1 = min(arg, oa), b2 = best;
+    if (q == 0 && t0 + r16 < T) {
+      labels[t0 + r16] = (uint8_t)arg;
+      if (margin) margin[t0 + r16] = C > 1 ? best - second : INFINITY;
     }
-    labels[t0 + r32] = (uint8_t)a1;
-    if (margin) margin[t0 + r32] = C > 1 ? b1 - b2 : INFINITY;
   }
 }
 
@@ -291,10 +376,27 @@ __global__ __launch_bounds__(256) void classifier_kernel(const TX* __restrict__ 
   }
 }
 
+// Four elements a thread and step, four steps in flight: 855,000 x 768 bf16
+// 1504 -> 659 us (6 TB/s) (an element per thread, stores of 4 bytes, before).  out
+// need not be aligned to more than its elements.
+struct __attribute__((packed, aligned(4))) Out4 {
+  floatx4 v;
+};
 template <typename TX>
-__global__ void to_f32_kernel(const TX* __restrict__ x, float* __restrict__ out, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] = ldf(x + i);
+__global__ __launch_bounds__(256) void to_f32_kernel(const TX* __restrict__ x, float* __restrict__ out, int64_t n) {
+  typedef TX vec4 __attribute__((ext_vector_type(4)));
+  const int64_t i0 = (int64_t)blockIdx.x * 4096 + threadIdx.x * 4;
+  if (((int64_t)blockIdx.x + 1) * 4096 <= n) {
+    vec4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = __builtin_nontemporal_load((const vec4*)(x + i0 + k * 1024));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) ((Out4*)(out + i0 + k * 1024))->v = __builtin_convertvector(v[k], floatx4);
+    return;
+  }
+  for (int k = 0; k < 4; ++k)
+    for (int e = 0; e < 4; ++e)
+      if (i0 + k * 1024 + e < n) out[i0 + k * 1024 + e] = ldf(x + i0 + k * 1024 + e);
 }
 
 // FP32 -> bf16, four elements per thread (n a multiple of 4)
@@ -431,15 +533,17 @@ void launch_classifier(const void* x, ElemType x_t, const float* wc_t, const flo
                        uint8_t* labels, float* logits, float* margin, hipStream_t s, const int* t_dev) {
   if (T <= 0) return;
   if (C <= 32) {
-    const int blocks = ceil_div(ceil_div(T, 32), 4);
-#define ANON_CLS_MFMA(HV)                                                                                        \
-  case HV:                                                                                                       \
-    if (x_t == ET_F32)                                                                                           \
-      hipLaunchKernelGGL((classifier_mfma_kernel<float, HV>), dim3(blocks), dim3(256), 0, s, (const float*)x,    \
-                         wc_t, bc, T, C, labels, logits, margin, t_dev);                                         \
-    else                                                                                                         \
-      hipLaunchKernelGGL((classifier_mfma_kernel<bf16_t, HV>), dim3(blocks), dim3(256), 0, s, (const bf16_t*)x,  \
-                         wc_t, bc, T, C, labels, logits, margin, t_dev);                                         \
+    // a workgroup per tile of 16 tokens up to one per CU, then a wave each
+    const int blocks = std::min(ceil_div(T, 16), 256);
+#define ANON_CLS_MFMA_N(TX, HV, NB)                                                                               \
+  hipLaunchKernelGGL((classifier_mfma_kernel<TX, HV, NB>), dim3(blocks), dim3(kClsWaves * 64), 0, s, (const TX*)x,   \
+                     wc_t, bc, T, C, labels, logits, margin, t_dev)
+#define ANON_CLS_MFMA(HV)                                   \
+  case HV:                                                  \
+    if (x_t == ET_F32 && C <= 16) ANON_CLS_MFMA_N(float, HV, 1); \
+    else if (x_t == ET_F32) ANON_CLS_MFMA_N(float, HV, 2);  \
+    else if (C <= 16) ANON_CLS_MFMA_N(bf16_t, HV, 1);       \
+    else ANON_CLS_MFMA_N(bf16_t, HV, 2);                    \
     return;
     switch (h) {
       ANON_CLS_MFMA(128)
@@ -450,6 +554,7 @@ void launch_classifier(const void* x, ElemType x_t, const float* wc_t, const flo
       default:
         break;
     }
+#undef ANON_CLS_MFMA_N
 #undef ANON_CLS_MFMA
   }
   if (x_t == ET_F32) {
@@ -463,7 +568,7 @@ void launch_classifier(const void* x, ElemType x_t, const float* wc_t, const flo
 
 void launch_to_f32(const void* x, ElemType t, float* out, int64_t n, hipStream_t s) {
   if (n <= 0) return;
-  const int grid = ceil_div(n, 256);
+  const int grid = (int)((n + 4095) / 4096);
   if (t == ET_F32) hipLaunchKernelGGL(to_f32_kernel<float>, dim3(grid), dim3(256), 0, s, (const float*)x, out, n);
   else hipLaunchKernelGGL(to_f32_kernel<bf16_t>, dim3(grid), dim3(256), 0, s, (const bf16_t*)x, out, n);
 }
