@@ -8,17 +8,20 @@
 // the bytes after ": " up to the end of the line.  A configured name with a
 // non-empty value gives one span of the configured type over the value.
 //
-// A workgroup takes 4096 bytes, 16 per thread, staged in LDS with the 448
+// A workgroup takes 8192 bytes, 32 per thread, staged in LDS with the 448
 // after them, and keeps '\n', ':' and record starts as bitmaps: a line's
-// colon and a value's end are one count of trailing zeros away.  A name is
-// compared as eight dwords.  A tile's fields are stored in byte order, which
-// is record-major; the tiles' counts are scanned, and a wave per tile writes
-// the spans.
+// colon and a value's end are one count of trailing zeros away.  The lines
+// are listed, so that whole waves of them are looked at, and a name is looked
+// up by a key of its eight dwords.  A tile's fields are stored in byte order,
+// which is record-major; the tiles' counts are scanned, and a wave per tile
+// writes the spans.
 //
-// Bound by memory latency: one read of the text and 16 bytes per field,
-// where a thread per byte read three bytes each, wrote an int flag, scanned
-// the flags in three kernels and tested every line a second time.  128 MB in
-// 16,384 records: 4.8 ms -> 0.24 ms, 0.21 of it the match.
+// Bound by instructions (three quarters of the match's time is vector issue):
+// one read of the text and 16 bytes per field, where a thread per byte read
+// three bytes each, wrote an int flag, scanned the flags in three kernels and
+// tested every line a second time.  128 MB in 16,384 records: 4.8 ms -> 0.12
+// ms, 95 us of it the match (16 bytes a thread, lines taken where they began
+// and every name compared in full: 215).
 #include <algorithm>
 
 #include "kernels.hpp"
@@ -26,12 +29,11 @@
 namespace anon {
 namespace {
 
-constexpr int kTile = 4096;
+constexpr int kTile = 8192;
 constexpr int kAfter = 448;                 // staged past the tile
 constexpr int kWin = kTile + kAfter;
 constexpr int kWinWords = kWin / 64;
-constexpr int kPerThread = 4;               // fields whose lines start in 16 bytes: "x: v" is 4 bytes
-constexpr int kTileFields = kTile / 4;
+constexpr int kTileFields = kTile / 4;      // "x: v" is 4 bytes
 
 __device__ __forceinline__ int find_in(const int64_t* cu, int a, int c, int64_t p) {
   while (a < c) {  // largest index of [a, c] with cu <= p
@@ -40,6 +42,14 @@ __device__ __forceinline__ int find_in(const int64_t* cu, int a, int c, int64_t 
     else c = m - 1;
   }
   return a;
+}
+
+// A bit per byte of w equal to c (given four times): the bytes of w ^ cccc
+// that are zero, exactly, their flags gathered by a multiplication.
+__device__ __forceinline__ uint32_t match4(uint32_t w, uint32_t cccc) {
+  const uint32_t x = w ^ cccc;
+  const uint32_t zero = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+  return (zero >> 7) * 0x10204080u >> 28;
 }
 
 // First set bit at or after o of two bitmaps of the window, kWin if none.
@@ -57,28 +67,27 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
                                                        FieldTable ft, FieldBuffers out, uint32_t* err) {
   __shared__ __align__(16) uint8_t win[kWin + 48];  // (names are read as 36 bytes)
   __shared__ __align__(16) uint64_t nl[kWinWords], colon[kWinWords], rec[kWinWords];
-  __shared__ FieldEntry found[256][kPerThread];
+  __shared__ uint16_t lines[kTile];
   __shared__ int ws[4];
   const int tid = threadIdx.x;
   const int64_t p0 = (int64_t)blockIdx.x * kTile;
   const int whi = (int)min((int64_t)kWin, n - p0);  // staged bytes of text
-  auto stage = [&](int piece) {
+  auto load = [&](int piece) {
     const int64_t p = p0 + piece * 16;
+    if (n - p >= 16) return load16(text + p);
     uint32_t w[4] = {0, 0, 0, 0};
-    if (n - p >= 16) {
-      const uint4 v = load16(text + p);
-      w[0] = v.x, w[1] = v.y, w[2] = v.z, w[3] = v.w;
-    } else {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        if (p + i < n) w[i >> 2] |= (uint32_t)text[p + i] << (8 * (i & 3));
-    }
+    for (int i = 0; i < 16; ++i)
+      if (p + i < n) w[i >> 2] |= (uint32_t)text[p + i] << (8 * (i & 3));
+    return uint4{w[0], w[1], w[2], w[3]};
+  };
+  auto stage = [&](int piece, uint4 v) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     uint32_t mn = 0, mc = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint32_t c = (w[i >> 2] >> (8 * (i & 3))) & 0xff;
-      mn |= (c == '\n' ? 1u : 0u) << i;
-      mc |= (c == ':' ? 1u : 0u) << i;
+    for (int i = 0; i < 4; ++i) {
+      mn |= match4(w[i], 0x0a0a0a0au) << (4 * i);
+      mc |= match4(w[i], 0x3a3a3a3au) << (4 * i);
     }
     *(uint4*)(win + piece * 16) = uint4{w[0], w[1], w[2], w[3]};
     ((uint16_t*)nl)[piece] = (uint16_t)mn;
@@ -86,13 +95,19 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
     ((uint16_t*)rec)[piece] = 0;
     return mn;
   };
-  const uint32_t my_nl = stage(tid);
-  if (tid < kAfter / 16) stage(kTile / 16 + tid);
-  // the byte before this thread's: a line break there starts a line
-  const int64_t mine = p0 + tid * 16;
-  const bool after_break = mine > 0 && mine < n && text[mine - 1] == '\n';
-  // record starts of the window (and the check of cu_bytes' tile part)
+  // the text and the byte before this thread's (a line break there starts a
+  // line) travel while the record of the tile's first byte is looked for
+  const int64_t mine = p0 + tid * 32;
+  const uint4 v0 = load(2 * tid), v1 = load(2 * tid + 1);
+  const uint4 v2 = tid < kAfter / 16 ? load(kTile / 16 + tid) : uint4{0, 0, 0, 0};
+  const uint8_t before = mine > 0 && mine < n ? text[mine - 1] : 0;
   const int r0 = wg_find_record(cu, B, p0);
+  uint32_t my_nl = stage(2 * tid, v0);
+  my_nl |= stage(2 * tid + 1, v1) << 16;
+  if (tid < kAfter / 16) stage(kTile / 16 + tid, v2);
+  const bool after_break = before == '\n';
+  __syncthreads();
+  // record starts of the window (and the check of cu_bytes' tile part)
   for (int b = r0;; b += 256) {
     const int i = b + tid;
     const int64_t c = i <= B ? cu[i] : INT64_MAX;
@@ -103,18 +118,19 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
     const int64_t x = cu[b];
     if ((b == 0 && x != 0) || (b == B && x != n) || (b < B && cu[b + 1] < x)) raise_error(err, ANON_ERR_TEXT);
   }
-  uint32_t starts = ((my_nl << 1) | (after_break ? 1u : 0u) | ((const uint16_t*)rec)[tid]) & 0xffff;
+  uint32_t starts = (my_nl << 1) | (after_break ? 1u : 0u) | ((const uint32_t*)rec)[tid];
   if (mine == 0) starts |= 1;  // the text's first byte
-  if (n - mine < 16) starts &= n > mine ? (1u << (n - mine)) - 1 : 0;
-  int cnt = 0;
-  for (; starts; starts &= starts - 1) {
-    const int o = tid * 16 + __ffs(starts) - 1;  // the line's first byte
+  starts &= ~my_nl;            // (an empty line)
+  if (n - mine < 32) starts &= n > mine ? (1u << (n - mine)) - 1 : 0;
+  // the field of the line that begins at byte o of the tile (type 0: none)
+  auto field_of = [&](int o) {
+    const FieldEntry none{0, 0, 0, 0};
     // the name ends at a ':' before any line break or record start after it
     const int stop = next_bit(nl, rec, o + 1), c = next_bit(colon, colon, o);
     const int len = c - o;
-    if (len > kFieldNameMax || c >= stop || ((nl[o >> 6] >> (o & 63)) & 1) || c + 1 >= whi || win[c + 1] != ' ' ||
+    if (len > kFieldNameMax || c >= stop || c + 1 >= whi || win[c + 1] != ' ' ||
         stop == c + 1)
-      continue;
+      return none;
     uint32_t d[kFieldNameMax / 4];
     const uint32_t* q = (const uint32_t*)(win + (o & ~3));
     uint32_t lo = q[0];
@@ -126,14 +142,22 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
       d[i] = left >= 4 ? v : left <= 0 ? 0 : v & ((1u << (8 * left)) - 1);
       lo = hi;
     }
+    // the first of equal names, as configured: by the names' keys, the whole
+    // name only where a key is equal (another name's key: the next equal one)
+    const uint32_t key = field_key(d, len);
     int type = 0;
-    for (int k = 0; k < ft.n; ++k) {  // (the first of equal names, as configured)
-      uint32_t diff = ft.len[k] ^ len;
+    for (int from = 0; from < ft.n && !type;) {
+      int hit = kFieldsMax;
+      for (int k = ft.n - 1; k >= 0; --k)
+        if (ft.key[k] == key && k >= from) hit = k;
+      if (hit == kFieldsMax) break;
+      uint32_t diff = ft.len[hit] ^ len;
 #pragma unroll
-      for (int i = 0; i < kFieldNameMax / 4; ++i) diff |= ((const uint32_t*)ft.name[k])[i] ^ d[i];
-      if (diff == 0 && !type) type = ft.type[k];
+      for (int i = 0; i < kFieldNameMax / 4; ++i) diff |= ((const uint32_t*)ft.name[hit])[i] ^ d[i];
+      if (diff == 0) type = ft.type[hit];
+      from = hit + 1;
     }
-    if (!type) continue;
+    if (!type) return none;
     // the value: up to the next line break, record start or the text's end
     const int vb = c + 2;
     int64_t ve = stop;
@@ -145,28 +169,46 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
       }
       ve -= p0;
     }
-    if (ve > vb && cnt < kPerThread)
-      found[tid][cnt++] = FieldEntry{(int)p0 + o, (int)(p0 + vb), (int)(p0 + ve), type};
-  }
-  // rank among the tile's fields
+    if (ve <= vb) return none;
+    return FieldEntry{(int)p0 + o, (int)(p0 + vb), (int)(p0 + ve), type};
+  };
+  // the lines' first bytes, in order
   const int lane = tid & 63, wave = tid >> 6;
-  int x = cnt;
+  {
+    const int own = __popc(starts);
+    int x = own;
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
-    if (lane >= o) x += y;
-  }
-  if (lane == 63) ws[wave] = x;
-  __syncthreads();
-  int base = x - cnt, total = 0;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int y = __shfl_up(x, o, 64);
+      if (lane >= o) x += y;
+    }
+    if (lane == 63) ws[wave] = x;
+    __syncthreads();
+    int at = x - own;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    if (w < wave) base += ws[w];
-    total += ws[w];
+    for (int w = 0; w < 4; ++w)
+      if (w < wave) at += ws[w];
+    for (; starts; starts &= starts - 1) lines[at++] = (uint16_t)(tid * 32 + __ffs(starts) - 1);
   }
+  const int n_lines = ws[0] + ws[1] + ws[2] + ws[3];
+  int total = 0;  // fields found so far
   FieldEntry* to = out.entries + (size_t)blockIdx.x * kTileFields;
-  for (int i = 0; i < cnt; ++i)
-    if (base + i < kTileFields) to[base + i] = found[tid][i];
+  __syncthreads();
+  for (int l0 = 0; l0 < n_lines; l0 += 256) {
+    FieldEntry f{0, 0, 0, 0};
+    if (l0 + tid < n_lines) f = field_of(lines[l0 + tid]);
+    const uint64_t some = __ballot(f.type > 0);
+    if (lane == 0) ws[wave] = __popcll((unsigned long long)some);
+    __syncthreads();
+    int at = total + __popcll((unsigned long long)(some & ((1ull << lane) - 1)));
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      if (w < wave) at += ws[w];
+      total += ws[w];
+    }
+    if (f.type > 0 && at < kTileFields) to[at] = f;
+    __syncthreads();
+  }
   if (tid == 0) {
     out.counts[blockIdx.x] = min(total, kTileFields);
     out.rec0[blockIdx.x] = r0;

@@ -442,14 +442,15 @@ __global__ __launch_bounds__(256) void ps_hash_kernel(PcacheDev pc, const uint8_
     atomicAdd(&pc.counters[8 * (blockIdx.x % kCounterSlots) + threadIdx.x], (unsigned long long)tally[threadIdx.x]);
 }
 
-// Record blockIdx.x's output, every gridDim.y-th block of 256 16-byte chunks
+// Record blockIdx.x's output, every gridDim.y-th block of kChunks 16-byte chunks
 // (chunks are aligned in memory).  A chunk that lies in copied text is one
 // unaligned 16-byte load and one store; the others (a span begins or ends in
 // them, or the record does) are listed and done a byte per thread, so that
 // they do not hold up the copying lanes.  The record's spans are searched in
 // LDS (if at most kStaged; else in memory).  128 MB in 16,384 records: 730 ->
-// 117 us (2.2 TB/s read and written) against a byte and a search per thread.
+// 105 us (2.4 TB/s read and written) against a byte and a search per thread.
 constexpr int kStaged = 512;
+constexpr int kChunks = 512;  // a step of a workgroup: two chunks a thread, both in flight
 
 __global__ __launch_bounds__(256) void ps_write_kernel(PcacheDev pc, const uint8_t* __restrict__ text,
                                                        const int64_t* __restrict__ cu_bytes,
@@ -463,12 +464,12 @@ __global__ __launch_bounds__(256) void ps_write_kernel(PcacheDev pc, const uint8
                                                        int64_t out_cap, uint32_t* err) {
   __shared__ int64_t l_out[kStaged], l_end[kStaged];
   __shared__ int l_plen[kStaged];
-  __shared__ int list[256], n_list;
+  __shared__ int list[kChunks], n_list;
   const int b = blockIdx.x, tid = threadIdx.x;
   const int64_t o0 = cu_out[b], n_out = cu_out[b + 1] - o0;
   const int lead = (int)((uintptr_t)(out + o0) & 15);  // bytes of the first chunk before the record
   const int64_t chunks = n_out > 0 ? (n_out + lead + 15) / 16 : 0;
-  if ((int64_t)blockIdx.y * 256 >= chunks) return;
+  if ((int64_t)blockIdx.y * kChunks >= chunks) return;
   if (tid == 0 && o0 + n_out > out_cap) raise_error(err, ANON_ERR_OUT_CAP);
   const int64_t room = min(n_out, out_cap - o0);  // bytes of the record that are written
   const int s0 = min(max(cu_spans[b], 0), span_cap);
@@ -492,28 +493,35 @@ __global__ __launch_bounds__(256) void ps_write_kernel(PcacheDev pc, const uint8
     }
     return sel;
   };
-  for (int64_t c0 = (int64_t)blockIdx.y * 256; c0 < chunks; c0 += (int64_t)gridDim.y * 256) {
+  for (int64_t c0 = (int64_t)blockIdx.y * kChunks; c0 < chunks; c0 += (int64_t)gridDim.y * kChunks) {
     if (tid == 0) n_list = 0;
     __syncthreads();
-    const int64_t c = c0 + tid, j0 = c * 16 - lead;
-    if (c < chunks && j0 < room) {
-      bool copied = false;
-      if (j0 >= 0 && j0 + 16 <= room) {
-        const int sel = last_at(j0);
-        const int64_t stop = sel + 1 < ns ? pos(sel + 1) : n_out;
-        int64_t src = j0;
-        bool gap = true;
-        if (sel >= 0) {
-          const int64_t k = j0 - pos(sel) - (staged ? l_plen[sel] : sp_plen[s0 + sel]);
-          gap = k >= 0;
-          src = (staged ? l_end[sel] : sp_in_end[s0 + sel]) + k;
-        }
-        if (gap && stop - j0 >= 16 && in_len - src >= 16) {
-          *(uint4*)(out + o0 + j0) = load16(in + src);
-          copied = true;
-        }
+    int64_t src[kChunks / 256];  // where the thread's chunks are copied from, -1: not, -2: listed
+#pragma unroll
+    for (int k = 0; k < kChunks / 256; ++k) {
+      const int64_t c = c0 + k * 256 + tid, j0 = c * 16 - lead;
+      src[k] = c < chunks && j0 < room ? -2 : -1;
+      if (src[k] == -1 || j0 < 0 || j0 + 16 > room) continue;
+      const int sel = last_at(j0);
+      const int64_t stop = sel + 1 < ns ? pos(sel + 1) : n_out;
+      int64_t from = j0;
+      bool gap = true;
+      if (sel >= 0) {
+        const int64_t past = j0 - pos(sel) - (staged ? l_plen[sel] : sp_plen[s0 + sel]);
+        gap = past >= 0;
+        from = (staged ? l_end[sel] : sp_in_end[s0 + sel]) + past;
       }
-      if (!copied) list[atomicAdd(&n_list, 1)] = tid;
+      if (gap && stop - j0 >= 16 && in_len - from >= 16) src[k] = from;
+    }
+    uint4 v[kChunks / 256];
+#pragma unroll
+    for (int k = 0; k < kChunks / 256; ++k)
+      if (src[k] >= 0) v[k] = load16(in + src[k]);
+#pragma unroll
+    for (int k = 0; k < kChunks / 256; ++k) {
+      const int c = k * 256 + tid;
+      if (src[k] >= 0) *(uint4*)(out + o0 + (c0 + c) * 16 - lead) = v[k];
+      else if (src[k] == -2) list[atomicAdd(&n_list, 1)] = c;
     }
     __syncthreads();
     const int todo = n_list * 16;

@@ -171,15 +171,26 @@ constexpr int kFieldNameMax = 32;
 constexpr int kFieldsMax = 64;
 struct FieldTable {  // passed by value to the kernels
   alignas(8) uint8_t name[kFieldsMax][kFieldNameMax];  // zero-padded, compared as dwords
+  uint32_t key[kFieldsMax];  // field_key of each name
   uint8_t len[kFieldsMax];
   int type[kFieldsMax];
   int n;
 };
+// A 32-bit mix of a name's zero-padded dwords and length, by which the fields
+// a line could be are found.
+__host__ __device__ inline uint32_t field_key(const uint32_t (&d)[kFieldNameMax / 4], int len) {
+  uint32_t h = (uint32_t)len * 0x9e3779b1u;
+  for (int i = 0; i < kFieldNameMax / 4; ++i) {
+    h = (h ^ d[i]) * 0x85ebca6bu;
+    h ^= h >> 15;
+  }
+  return h;
+}
 struct FieldEntry {  // a field: its line's first byte, its value and type
   int line, begin, end, type;
 };
 struct FieldBuffers {
-  FieldEntry* entries;  // per tile of 4096 bytes, in byte order
+  FieldEntry* entries;  // per tile of 8192 bytes, in byte order
   int *counts, *rec0;   // per tile: fields, the record of its first byte
 };
 FieldBuffers field_layout(int64_t n_bytes, Carver& k);

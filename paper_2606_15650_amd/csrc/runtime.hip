@@ -1258,6 +1258,9 @@ anon_status field_spans(const uint8_t* d_text, const int64_t* d_cu_bytes, int32_
     if (h_field_types[k] < 1 || h_field_types[k] > n_types) return set_error(ANON_EINVAL, "field type outside [1, n_types]");
     memcpy(ft.name[k], nm, L);
     ft.len[k] = (uint8_t)L;
+    uint32_t d[kFieldNameMax / 4];
+    memcpy(d, ft.name[k], sizeof(d));
+    ft.key[k] = field_key(d, (int)L);
     ft.type[k] = h_field_types[k];
   }
   if (!d_cu_spans || !d_cu_bytes) return set_error(ANON_EINVAL, "cu arrays are NULL");

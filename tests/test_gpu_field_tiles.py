@@ -1,5 +1,5 @@
 """field_spans where its tiles can go wrong: lines, names, colons and values
-over a tile's end (4096 bytes) at every offset, names of 32 and 33 bytes,
+over a tile's end (8192 bytes) at every offset, names of 32 and 33 bytes,
 values past the staged window (448 bytes after the tile), tiles full of the
 shortest fields, many record boundaries in one tile.  Bit-exact against the
 oracle."""
@@ -35,9 +35,9 @@ def test_lines_over_a_tile_end(shift):
     out = []
     for i, line in enumerate([b"Host: abc", b"See Also: y", LONG + b": v", LONG + b"N: v", LONG[:31] + b": " + b"w" * 40,
                               b"x: " + b"q" * 60, b"Host:", b"Host: ", b"Host:a", b"x: 1"]):
-        # every line begins `shift` bytes before a multiple of 4096
+        # every line begins `shift` bytes before a multiple of 8192
         at = sum(map(len, out))
-        out.append(b"-" * ((-(at + 1 + shift)) % 4096) + b"\n" + line + (b"\n" if i % 2 else b""))
+        out.append(b"-" * ((-(at + 1 + shift)) % 8192) + b"\n" + line + (b"\n" if i % 2 else b""))
         if i % 3 == 0:
             out.append(b"")
     _check(out, f"lines from {shift} before a tile's end")
@@ -45,13 +45,13 @@ def test_lines_over_a_tile_end(shift):
     _check([b"".join(out).replace(b"\n", b"", 1), b"Host: z"], "a first line without a break")
 
 
-@pytest.mark.parametrize("length", [438, 441, 442, 443, 444, 445, 450, 4090, 4540, 9000])
+@pytest.mark.parametrize("length", [438, 441, 442, 443, 444, 445, 450, 8180, 8640, 17000])
 def test_values_past_the_window(length):
     import torch
     assert torch.cuda.is_available()
     for tail in (b"", b"\n", b"\nHost: a"):
-        first = b"-" * 4090 + b"\n" + b"x: " + b"v" * length + tail
-        _check([first, b"Host: b\n"], f"a value of {length} from 4094")
+        first = b"-" * 8186 + b"\n" + b"x: " + b"v" * length + tail
+        _check([first, b"Host: b\n"], f"a value of {length} from 8190")
         _check([first], "the same at the text's end")
 
 
@@ -67,3 +67,29 @@ def test_full_tiles_and_many_boundaries():
     for step in (1, 3, 5, 17, 200):
         _check([text[i:i + step] for i in range(0, min(len(text), 4000 * step), step)], f"records of {step}",
                least=step > 3)  # "x: v" has 4 bytes
+
+
+def _key(name):
+    """The library's key of a name (its zero-padded dwords and length)."""
+    h = len(name) * 0x9E3779B1 & 0xFFFFFFFF
+    for i in range(0, 32, 4):
+        h = (h ^ int.from_bytes(name[i:i + 4].ljust(4, b"\0"), "little")) * 0x85EBCA6B & 0xFFFFFFFF
+        h ^= h >> 15
+    return h
+
+
+def test_names_of_one_key():
+    seen, pairs = {}, []
+    for i in range(400000):
+        name = b"f%x" % (i * 2654435761 % (1 << 40))
+        other = seen.setdefault(_key(name), name)
+        if other != name:
+            pairs.append((other, name))
+    assert len(pairs) >= 5
+    text = b"".join(a + b": 1\n" + b + b": two\n" for a, b in pairs)
+    for which in ((0,), (1,), (0, 1), (1, 0)):
+        config = {p[k]: 1 + (2 * i + k) % 8 for i, p in enumerate(pairs[:16]) for k in which}
+        rb = _text_batch([text, text[5:]], TYPE_NAMES_17)
+        _, got = _fields_gpu(rb, make_cache(TYPE_NAMES_17), config)
+        assert got == F.field_spans_batch(rb.text, rb.cu_bytes, config)
+        assert sum(map(len, got)) > 0
