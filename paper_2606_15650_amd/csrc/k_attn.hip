@@ -23,30 +23,19 @@
 // end.  The MFMA k-index of P^T is a permutation of the 16 keys of a step; V
 // is read transposed from LDS (ds_read_b64_tr_b16) in the same order.
 //
-// FP32 operands (attn_kernel, the plain FP32 path): work item = (q-block of
-// 32*WAVES rows of one record, head); the block streams the record's keys in
-// tiles of 64, K rows and V^T staged in LDS, in two passes: the first finds
-// each row's exact maximum, the second forms p = exp(s - max) (FP32, base-2
-// exponentials), sums it and accumulates O^T += V^T P^T.
+// FP32 operands (attn_f32_kernel): a workgroup per item of 128 query rows and
+// head, a wave per 32 rows; the keys in tiles of 64 through registers (the
+// next tile on its way while one is used) into LDS, rows as they are.  The
+// same running reference makes it one pass.
 #include <algorithm>
+#include <type_traits>
 
 #include "kernels.hpp"
 
 namespace anon {
 namespace {
 
-template <typename T>
-struct AMfma;
-template <>
-struct AMfma<float> {
-  typedef float frag;
-  static constexpr int KI = 2, KPL = 1;
-  __device__ static floatx16 mma(frag a, frag b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct AMfma<bf16_t> {
+struct AMfma {
   typedef bf16x8 frag;
   static constexpr int KI = 16, KPL = 8;
   __device__ static floatx16 mma(frag a, frag b, floatx16 c) {
@@ -65,19 +54,6 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 
 constexpr int D = 64;    // head dim
 constexpr int KT = 64;   // keys per LDS tile
-
-// V^T fragment of PV step `st` in key block `kb` for lane half hh.
-__device__ __forceinline__ float vfrag(const float* vrow, int kb, int st, int hh) {
-  const int r = st;  // KPL = 1
-  return vrow[kb * 32 + (r >> 2) * 8 + hh * 4 + (r & 3)];
-}
-__device__ __forceinline__ bf16x8 vfrag(const bf16_t* vrow, int kb, int st, int hh) {
-  // registers 8*st .. 8*st+7 hold keys kb*32 + 16*st + hh*4 + {0..3} and
-  // kb*32 + 16*st + 8 + hh*4 + {0..3}
-  const bf16x4 lo = *(const bf16x4*)(vrow + kb * 32 + 16 * st + hh * 4);
-  const bf16x4 hi = *(const bf16x4*)(vrow + kb * 32 + 16 * st + 8 + hh * 4);
-  return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-}
 
 // V^T fragments of the record-resident kernel, read transposed from V kept
 // row-major in LDS (64 elements per row; in rows with bit 1 set, bit 5 of the
@@ -107,170 +83,157 @@ __device__ __forceinline__ bf16x8 vfrag_tr(const bf16_t* vl, int kb, int st) {
   return bf16x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
 }
 
-template <typename T>
-__device__ __forceinline__ typename AMfma<T>::frag pfrag(const floatx16& s, int st);
-template <>
-__device__ __forceinline__ float pfrag<float>(const floatx16& s, int st) {
-  return s[st];
-}
-template <>
-__device__ __forceinline__ bf16x8 pfrag<bf16_t>(const floatx16& s, int st) {
+__device__ __forceinline__ bf16x8 pfrag(const floatx16& s, int st) {
   bf16x8 f;
 #pragma unroll
   for (int j = 0; j < 8; ++j) f[j] = static_cast<bf16_t>(s[st * 8 + j]);
   return f;
 }
 
-template <typename T, typename TO, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) void attn_kernel(const T* __restrict__ qkv, TO* __restrict__ out,
-                                                          const int4* __restrict__ qblocks,
-                                                          const int* __restrict__ n_qblocks, int hidden,
-                                                          float out_inv_scale, int window) {
-  typedef AMfma<T> MF;
-  typedef typename MF::frag frag;
-  constexpr int NT = WAVES * 64;
-  constexpr int EPC = 16 / (int)sizeof(T);
-  constexpr int PAD = EPC;
+// ---- FP32 kernel ------------------------------------------------------------
+// S^T = K Q^T with v_mfma_f32_32x32x2_f32: an MFMA's two k-indices are column
+// e of the lane half's four of each eight, so K is read 16 bytes at a time (a
+// row of 68 floats puts 16 lanes on 16 bank groups); V is read by column (72
+// floats a row: the half-waves' rows, four apart, fall on the other 32
+// banks).  21,608 tokens of the base width: 481 -> 299 us against two passes
+// over the keys (a third more MFMAs), V transposed into LDS and every tile
+// waited for.  Bound by the MFMAs, rows of a record's last 32 and keys of its
+// last 32 included.
+constexpr int kWaves = 4;
+constexpr int kBQ = 32 * kWaves;
+
+__global__ __launch_bounds__(kWaves * 64, 3) void attn_f32_kernel(const float* __restrict__ qkv,
+                                                                  float* __restrict__ out,
+                                                                  const int4* __restrict__ items,
+                                                                  const int* __restrict__ n_items, int hidden,
+                                                                  int window) {
+  constexpr int NT = kWaves * 64, LK = D + 4, LV = D + 8;
+  constexpr int LPT = KT * D / 4 / NT;  // 16-byte loads per thread, tile and matrix
   constexpr float LOG2E = 1.4426950408889634f;
-
-  const int qb = blockIdx.x;
-  if (qb >= *n_qblocks) return;
+  if ((int)blockIdx.x >= *n_items) return;
   const int head = blockIdx.y;
-  const int4 desc = qblocks[qb];  // (first token, length, first query row, -)
-  const int base = desc.x, L = desc.y, q0 = desc.z;
+  const int4 item = items[blockIdx.x];  // (first token, length, first query row, -)
+  const int base = item.x, L = item.y, q0 = item.z;
   const int ld = 3 * hidden;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5;
-  const int qw = q0 + wave * 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hh = lane >> 5, r32 = lane & 31;
+  const int qw = q0 + wave * 32, qrow = qw + r32;
   const bool active = qw < L;
+  __shared__ __align__(16) float Ks[KT * LK];
+  __shared__ __align__(16) float Vs[KT * LV];
 
-  __shared__ T Ks[KT * (D + PAD)];
-  __shared__ T Vt[D * (KT + PAD)];
-
-  frag qf[D / MF::KI];
-  const int qrow = qw + (lane & 31);
+  floatx4 qf[D / 8];
 #pragma unroll
-  for (int kk = 0; kk < D / MF::KI; ++kk) {
-    if (qrow < L) {
-      qf[kk] = *(const frag*)(qkv + (size_t)(base + qrow) * ld + head * D + kk * MF::KI + hh * MF::KPL);
-    } else {
-      qf[kk] = frag{};
-    }
+  for (int c = 0; c < D / 8; ++c) {
+    qf[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (qrow < L) qf[c] = *(const floatx4*)(qkv + (size_t)(base + qrow) * ld + head * D + c * 8 + hh * 4);
   }
-
+  // keys that some row of the item sees
+  const int t_begin = window > 0 ? max(q0 - window, 0) / KT * KT : 0;
+  const int t_end = window > 0 ? (int)min((int64_t)L, (int64_t)q0 + kBQ + window) : L;
+  floatx4 kv[LPT], vv[LPT];
+  auto gload = [&](int t0) {
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) {
+      const int c = tid + i * NT, r = c / (D / 4), cc = c % (D / 4);
+      kv[i] = vv[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (t0 + r < L) {
+        const float* src = qkv + (size_t)(base + t0 + r) * ld + head * D + cc * 4;
+        kv[i] = *(const floatx4*)(src + hidden);
+        vv[i] = *(const floatx4*)(src + 2 * hidden);
+      }
+    }
+  };
   floatx16 o[2];
 #pragma unroll
   for (int r = 0; r < 16; ++r) o[0][r] = o[1][r] = 0.f;
-  float m = -INFINITY, lsum = 0.f;
-
-  constexpr int CPR = D / EPC;  // 16-byte chunks per K/V row
-  // scores of the current 64-key tile, base-2 scaled, -inf for missing keys
-  auto scores = [&](floatx16 (&s)[2], int t0k, int nk) {
+  float ref = -INFINITY, lsum = 0.f;
+  gload(t_begin);
+  for (int t0 = t_begin; t0 < t_end; t0 += KT) {
+    __syncthreads();
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-#pragma unroll
-      for (int kk = 0; kk < D / MF::KI; ++kk) {
-        const frag a = *(const frag*)&Ks[(kb * 32 + (lane & 31)) * (D + PAD) + kk * MF::KI + hh * MF::KPL];
-        s[kb] = MF::mma(a, qf[kk], s[kb]);
-      }
+    for (int i = 0; i < LPT; ++i) {
+      const int c = tid + i * NT, r = c / (D / 4), cc = c % (D / 4);
+      *(floatx4*)&Ks[r * LK + cc * 4] = kv[i];
+      *(floatx4*)&Vs[r * LV + cc * 4] = vv[i];
     }
-    float mloc = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = kb * 32 + (r >> 2) * 8 + hh * 4 + (r & 3);
-        const int dk = qrow - (t0k + key);
-        const bool seen = key < nk && (window <= 0 || (dk <= window && dk >= -window));
-        const float v = seen ? s[kb][r] * LOG2E : -INFINITY;
-        s[kb][r] = v;
-        mloc = fmaxf(mloc, v);
-      }
-    return fmaxf(mloc, __shfl_xor(mloc, 32, 64));
-  };
-  auto load_tile = [&](int t0, int nk, bool with_v) {
-    for (int c = tid; c < KT * CPR; c += NT) {
-      const int r = c / CPR, cc = c % CPR;
-      intx4 kv = {0, 0, 0, 0}, vv = {0, 0, 0, 0};
-      if (r < nk) {
-        const T* src = qkv + (size_t)(base + t0 + r) * ld + head * D + cc * EPC;
-        kv = *(const intx4*)(src + hidden);
-        if (with_v) vv = *(const intx4*)(src + 2 * hidden);
-      }
-      *(intx4*)&Ks[r * (D + PAD) + cc * EPC] = kv;
-      if (with_v) {
-        const T* ve = (const T*)&vv;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) Vt[(cc * EPC + e) * (KT + PAD) + r] = ve[e];
-      }
-    }
-  };
-
-  // Pass 1 (records longer than one tile): the exact row maximum, so that
-  // the probabilities below are formed and rounded once, relative to it.
-  const int ntiles = (L + KT - 1) / KT;
-  if (ntiles > 1) {
-    for (int t0 = 0; t0 < L; t0 += KT) {
-      const int nk = min(KT, L - t0);
-      __syncthreads();
-      load_tile(t0, nk, false);
-      __syncthreads();
-      if (active) {
-        floatx16 s[2];
-        m = fmaxf(m, scores(s, t0, nk));
-      }
-    }
-  }
-  // Pass 2: p = exp(s - max), row sums in FP32, O^T += V^T P^T.
-  for (int t0 = 0; t0 < L; t0 += KT) {
+    __syncthreads();
+    if (t0 + KT < t_end) gload(t0 + KT);
+    if (!active) continue;
     const int nk = min(KT, L - t0);
-    __syncthreads();
-    load_tile(t0, nk, true);
-    __syncthreads();
-    if (active) {
-      floatx16 s[2];
-      const float mt = scores(s, t0, nk);
-      if (ntiles == 1) m = mt;
-      float ps = 0.f;
+    // one or two blocks of 32 keys
+    auto block = [&](auto nb) {
+      constexpr int NB = decltype(nb)::value;
+      floatx16 s[NB];
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
+      for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+      for (int c = 0; c < D / 8; ++c) {
+        floatx4 kf[NB];
+#pragma unroll
+        for (int kb = 0; kb < NB; ++kb) kf[kb] = *(const floatx4*)&Ks[(kb * 32 + r32) * LK + c * 8 + hh * 4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int kb = 0; kb < NB; ++kb)
+            s[kb] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[kb][e], qf[c][e], s[kb], 0, 0, 0);
+      }
+      // base-2 scaled, -inf for keys that are not there or not seen
+      float top = -INFINITY;
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float pv = exp2_fast(s[kb][r] - m);
-          s[kb][r] = pv;
-          ps += pv;
+          const int key = kb * 32 + (r >> 2) * 8 + hh * 4 + (r & 3);
+          const int dk = qrow - (t0 + key);
+          const bool seen = key < nk && (window <= 0 || (dk <= window && dk >= -window));
+          s[kb][r] = seen ? s[kb][r] * LOG2E : -INFINITY;
+          top = fmaxf(top, s[kb][r]);
+        }
+      top = fmaxf(top, __shfl_xor(top, 32, 64));
+      const float now = fmaxf(ref, ceilf(top));
+      const float sub = now == -INFINITY ? 0.f : now;  // (no key seen yet: every p is 0)
+      if (__any(now > ref)) {
+        const float scale = exp2_fast(ref - sub);  // an exact power of two
+        lsum *= scale;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          o[0][r] *= scale;
+          o[1][r] *= scale;
+        }
+        ref = now;
+      }
+      float ps = 0.f;
+#pragma unroll
+      for (int kb = 0; kb < NB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          s[kb][r] = exp2_fast(s[kb][r] - sub);
+          ps += s[kb][r];
         }
       lsum += ps;
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int stp = 0; stp < 32 / MF::KI; ++stp) {
-          const frag pb = pfrag<T>(s[kb], stp);
-#pragma unroll
-          for (int db = 0; db < 2; ++db) {
-            const frag va = vfrag(&Vt[(db * 32 + (lane & 31)) * (KT + PAD)], kb, stp, hh);
-            o[db] = MF::mma(va, pb, o[db]);
-          }
-        }
-    }
-  }
-  if (active) {
-    const float ltot = lsum + __shfl_xor(lsum, 32, 64);
-    const float inv = 1.0f / ltot;
-    if (qrow < L) {
-      TO* dst = out + (size_t)(base + qrow) * hidden + head * D;
-#pragma unroll
-      for (int db = 0; db < 2; ++db)
+      for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          float v = o[db][r] * inv;
-          // FP8 output: round to bf16 (the stored attention output), then
-          // scale and round to E4M3
-          if (sizeof(TO) == 1) v = static_cast<float>(static_cast<bf16_t>(v)) * out_inv_scale;
-          st(dst + db * 32 + (r >> 2) * 8 + hh * 4 + (r & 3), v);
+          const float* v = &Vs[(kb * 32 + (r >> 2) * 8 + hh * 4 + (r & 3)) * LV + r32];
+          o[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[0], s[kb][r], o[0], 0, 0, 0);
+          o[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[32], s[kb][r], o[1], 0, 0, 0);
         }
-    }
+    };
+    if (nk > 32) block(std::integral_constant<int, 2>());
+    else block(std::integral_constant<int, 1>());
+  }
+  if (active && qrow < L) {
+    const float inv = 1.0f / (lsum + __shfl_xor(lsum, 32, 64));
+    float* dst = out + (size_t)(base + qrow) * hidden + head * D + hh * 4;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *(floatx4*)(dst + db * 32 + q * 8) =
+            floatx4{o[db][4 * q] * inv, o[db][4 * q + 1] * inv, o[db][4 * q + 2] * inv, o[db][4 * q + 3] * inv};
   }
 }
 
@@ -320,7 +283,7 @@ __global__ __launch_bounds__(W * 64, WPE) void attn_stream_kernel(const bf16_t* 
                                                                   const int4* __restrict__ items,
                                                                   const int* __restrict__ n_items, int n_heads,
                                                                   int hidden, float out_inv_scale, int window) {
-  typedef AMfma<bf16_t> MF;
+  typedef AMfma MF;
   typedef bf16x8 frag;
   constexpr float LOG2E = 1.4426950408889634f;
   constexpr int TILE = KT * kRowBytes;   // bytes of the K (or V) rows of one tile
@@ -546,7 +509,7 @@ __global__ __launch_bounds__(W * 64, WPE) void attn_stream_kernel(const bf16_t* 
           }
 #pragma unroll
           for (int stp = 0; stp < 2; ++stp) {
-            const frag pb = pfrag<bf16_t>(s[b], stp);
+            const frag pb = pfrag(s[b], stp);
             const int kb = h64 * 2 + b;
             const bf16_t* v0 = (const bf16_t*)(smem + ST * STAGE + vl_off0);
             const bf16_t* v1 = (const bf16_t*)(smem + ST * STAGE + vl_off1);
@@ -660,9 +623,6 @@ __global__ __launch_bounds__(W * 64, WPE) void attn_stream_kernel(const bf16_t* 
   while (step(std::integral_constant<int, 0>()) && step(std::integral_constant<int, 1>())) {
   }
 }
-
-constexpr int kWaves = 4;
-constexpr int kBQ = 32 * kWaves;
 
 // One workgroup: validates cu_seqlens and lists the work items (first token,
 // length, first query row, record), bq query rows each, longest records first:
@@ -825,17 +785,8 @@ void launch_attention(const void* qkv, void* out, const int4* items, int max_ite
                       out_inv_scale, window, grid, s);
     return;
   }
-  dim3 grid(max_items, n_heads);
-  if (t == ET_F32) {
-    hipLaunchKernelGGL((attn_kernel<float, float, kWaves>), grid, dim3(kWaves * 64), 0, s, (const float*)qkv,
-                       (float*)out, items, n_items, hidden, out_inv_scale, window);
-  } else if (out_t == ET_FP8) {
-    hipLaunchKernelGGL((attn_kernel<bf16_t, fp8_t, kWaves>), grid, dim3(kWaves * 64), 0, s, (const bf16_t*)qkv,
-                       (fp8_t*)out, items, n_items, hidden, out_inv_scale, window);
-  } else {
-    hipLaunchKernelGGL((attn_kernel<bf16_t, bf16_t, kWaves>), grid, dim3(kWaves * 64), 0, s, (const bf16_t*)qkv,
-                       (bf16_t*)out, items, n_items, hidden, out_inv_scale, window);
-  }
+  hipLaunchKernelGGL(attn_f32_kernel, dim3(max_items, n_heads), dim3(kWaves * 64), 0, s, (const float*)qkv,
+                     (float*)out, items, n_items, hidden, window);
 }
 
 }  // namespace anon

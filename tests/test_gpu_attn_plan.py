@@ -50,3 +50,23 @@ def test_every_record_is_listed_once(max_pos, precision):
         want = np.concatenate([_hidden(pl, ids[L[:i].sum():L[:i + step].sum()], L[i:i + step])
                                for i in range(0, len(L), step) if L[i:i + step].sum()])
         np.testing.assert_array_equal(got, want)
+
+
+@pytest.mark.parametrize("lengths", [EDGES, [513, 95, 1, 640]])
+def test_fp32_attention_at_block_edges(lengths):
+    """One layer against the float64 oracle: records around blocks of 32 keys,
+    tiles of 64 and items of 128 rows, a longer one whose running reference
+    grows."""
+    from dataclasses import replace
+
+    from oracle import encoder
+    from paper_2606_15650_amd.pipeline import Pipeline
+    from synth.configs import TINY
+    cfg = replace(TINY, n_layers=1, max_pos=700)
+    W, m = make_model(cfg, "fp32", 0)
+    rng = np.random.default_rng(len(lengths))
+    ids = rng.integers(0, cfg.vocab, sum(lengths)).astype(np.int32)
+    got = _hidden(Pipeline(m), ids, lengths)
+    ref = encoder.hidden_states(W, cfg, ids, np.concatenate([[0], np.cumsum(lengths)]), n_layers=1)
+    # the bound of the repository's layer-by-layer FP32 test
+    assert np.abs(got - ref).max() < 2e-5 * max(1.0, np.abs(ref).max())
