@@ -1007,15 +1007,17 @@ bool gemm_config_serves(const GemmParams& g, int config) {
 
 // Estimated time (us) of the tiles worth choosing, fitted to launches of the
 // base and large encoders' GEMMs at 16 to 50,000 rows on all 256 CUs (bf16 K
-// 768 and 3072, FP8 K 1024 and 4096).  With kt = 128-byte steps of K:
+// 768 and 3072, FP8 K 1024 and 4096, FP32 K 768 and 3072).  With kt = 128-byte steps of K:
 //   f0 + f1 kt  a launch whose tiles all start at once (latency of one tile)
 //   g0 + g1 kt  each further tile per CU, all CUs busy
 //   gelu        added to both by the GELU epilogue
 // Whole: tiles of one workgroup per CU, so a last, partly filled round costs
 // between the first and the second figure.  Pair: at most two per CU, whose
 // second tile costs a round as soon as one CU has it.  Fine: tiles so small
-// that the CUs' loads even out.
-enum TileFill { kWhole, kPair, kFine };
+// that the CUs' loads even out.  Step: each further tile on any CU costs a
+// round.  Both: two tiles of a CU share its matrix cores to the end, so a
+// third starts with the fourth.
+enum TileFill { kWhole, kPair, kFine, kStep, kBoth };
 struct TileCost {
   int config;
   float f0, f1, g0, g1, gelu;
@@ -1034,6 +1036,12 @@ const TileCost kCostFP8[] = {
     {11, 3.1f, 0.19f, 0.34f, 0.2f, 0.3f, kFine},
 };
 
+const TileCost kCostF32[] = {
+    {0, 5.0f, 2.13f, 3.7f, 1.91f, 0.5f, kBoth},
+    {1, 3.5f, 0.73f, 0.53f, 0.578f, 0.3f, kStep},
+    {2, 5.0f, 2.29f, 6.0f, 1.83f, 0.5f, kStep},
+};
+
 static float tile_cost(const TileCost& t, const Cfg& c, const GemmParams& g) {
   const float kt = (float)g.K * elem_bytes(g.in) / 128.f;
   const float ge = g.epi == EPI_GELU || g.epi == EPI_GEGLU ? t.gelu : 0.f;
@@ -1045,6 +1053,8 @@ static float tile_cost(const TileCost& t, const Cfg& c, const GemmParams& g) {
   }
   if (r <= 1.f) return one;
   if (t.fill == kFine) return one + (r - 1.f) * more;
+  if (t.fill == kStep) return one + (ceilf(r) - 1.f) * more;
+  if (t.fill == kBoth) return ceilf(r / 2.f) * 2.f * more;
   return one + (r < 2.f ? 1.f : ceilf(2.f * r) * 0.5f - 1.f) * more;
 }
 
@@ -1057,7 +1067,9 @@ int default_gemm_config(const GemmParams& g) {
   // here take 5.3, 5.4, 5.8 and 12.1 us, and at 2,094 rows 13, 7, 17 and 22
   // instead of 21, 21, 27 and 63.  At 8,192 rows and above the choice is
   // worth 0-25% (the last round of 256x256 tiles), from 21,608 rows on it is
-  // mostly the 256x256 tile.
+  // mostly the 256x256 tile.  FP32: 137 rows 56, 56, 57 and 210 us with
+  // 128x128 tiles alone, 21, 21, 22 and 74 with 64x64; 4,096 rows 192, 58, 197
+  // and 209 -> 135, 47, 154 and 175; 21,608 rows keep 128x128.
   const int n = gemm_num_configs(g.in);
   int nc;
   const Cfg* cs = cfgs(g.in, &nc);
@@ -1072,6 +1084,8 @@ int default_gemm_config(const GemmParams& g) {
     for (const TileCost& t : kCostBF16) consider(t);
   else if (g.in == ET_FP8)
     for (const TileCost& t : kCostFP8) consider(t);
+  else
+    for (const TileCost& t : kCostF32) consider(t);
   if (best >= 0) return best;
   for (int c = 0; c < n; ++c)
     if (gemm_config_serves(g, c)) return c;

@@ -1,5 +1,6 @@
 """GEMM tiles chosen by row count: whatever tile the library picks for a batch,
-a record's hidden state has the bits that one forced 256x256 tile gives it
+a record's hidden state has the bits that one forced 256x256 (FP32:
+256x128) tile gives it
 (every tile forms an output with the same MFMA sequence, so the tolerance is
 zero).  Row counts lie on both sides of the tile edges (32, 64, 128, 192, 256)
 and of the points where the choice changes."""
@@ -34,7 +35,7 @@ def _lengths(T):
     return np.asarray(L, np.int64)
 
 
-@pytest.mark.parametrize("size,precision", [("base", "bf16"), ("large", "bf16"), ("large", "fp8")])
+@pytest.mark.parametrize("size,precision", [("base", "bf16"), ("large", "bf16"), ("large", "fp8"), ("base", "fp32")])
 def test_default_tiles_equal_the_widest_tile(torch_dev, size, precision):
     import torch
     from paper_2606_15650_amd import api
@@ -42,8 +43,8 @@ def test_default_tiles_equal_the_widest_tile(torch_dev, size, precision):
     cfg = replace(BASE if size == "base" else LARGE, n_layers=1, vocab=2000)
     scales = np.full(4, 2.0 ** -6, np.float32) if precision == "fp8" else None
     _, m = make_model(cfg, precision, 0, act_scales=scales)
-    wide = {"bf16": 11, "fp8": 7}[precision]
-    assert "256x256" in m.tile_configs()[wide]
+    wide, name = {"bf16": (11, "256x256"), "fp8": (7, "256x256"), "fp32": (3, "256x128")}[precision]
+    assert name in m.tile_configs()[wide]
     pl = Pipeline(m)
     rng = np.random.default_rng(3)
     for T in (1, 31, 33, 64, 65, 129, 257, 300, 449, 700, 1100, 2094, 3111, 4097, 6150, 9000, 12289, 16385):
