@@ -491,6 +491,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // LDS but has nothing to run while its one wave per SIMD waits: 3.06 / 1.29 /
 // 4.80 / 3.59 ms with the same ring, not kept.
 //
+// kTileRegs: for batches so small that a CU has one tile and what counts is
+// how long one K tile takes.  With one or four 32x32 blocks in a workgroup a
+// k-step is a single MFMA, too short to cover the LDS reads of the next, and
+// one or two waves do not issue copies fast enough.  So the fragments of a
+// whole K tile are read under the MFMAs of the tile before, eight waves share
+// the copies, and a tile costs one barrier and no other wait.  137 rows of the
+// base encoder: 5.2, 5.4, 5.8 and 12.1 us -> 4.8, 4.6, 5.3 and 8.7 for the four
+// GEMMs of a layer (a K tile of 128 530 clocks instead of 900); deeper rings
+// change nothing.
+//
 // LDS layout: rows of BK elements, unpadded, with the 16-byte chunks of a
 // row XOR-permuted by a function of the row (chunk c of row r sits in slot
 // c ^ swz(r)): a 16-lane group reading the same logical chunk of 16
@@ -563,13 +573,18 @@ __device__ __forceinline__ void sched_step() {
 // "Ring stages" of the ring that runs A two K tiles and W one K tile ahead
 // (see gemm_dma_kernel).
 constexpr int kAhead = -1;
+// A ring of ST - kTileRegs stages for a few tiles on an empty chip (see
+// gemm_dma_kernel): kLoaders waves load, WGM x WGN of them multiply.
+constexpr int kTileRegs = 100;
+constexpr int kLoaders = 8;
 
 template <typename TI, typename TO, typename TR, int EPI, int BM, int BN, int BK, int WGM, int WGN, int ST,
           int OCC>
-__global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams p) {
+__global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams p) {
   typedef Mfma<TI> MF;
   typedef typename MF::frag frag;
-  constexpr int NW = WGM * WGN;
+  constexpr int NC = WGM * WGN;  // waves that multiply; NW: that load
+  constexpr int NW = ST >= kTileRegs ? kLoaders : NC;
   constexpr int WTM = BM / WGM, WTN = BN / WGN;
   constexpr int TM = WTM / 32, TN = WTN / 32;
   constexpr int EPC = 16 / (int)sizeof(TI);    // elements per 16-byte chunk
@@ -584,9 +599,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
   constexpr int CPS = MF::KI / EPC;            // chunks per k-step
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile/waves mismatch");
   static_assert(TM >= 1 && TN >= 1 && BK % MF::KI == 0 && (ST >= 2 || ST == kAhead), "bad tile");
-  static_assert(ST == kAhead || (ST - 1) * LPT < 64, "vmcnt range");
-  constexpr bool AHEAD = ST == kAhead;
-  constexpr int SMEM = AHEAD ? 3 * A_BYTES + 2 * (STAGE - A_BYTES) : ST * STAGE;
+  constexpr bool AHEAD = ST == kAhead, WHOLE = ST >= kTileRegs;
+  constexpr int SL = WHOLE ? ST - kTileRegs : ST;  // stages
+  static_assert(AHEAD || (SL - 1) * LPT < 64, "vmcnt range");
+  constexpr int SMEM = AHEAD ? 3 * A_BYTES + 2 * (STAGE - A_BYTES) : SL * STAGE;
   static_assert(SMEM <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
   __shared__ __align__(1024) char smem[SMEM];
 
@@ -670,7 +686,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
 
   const int KT = K / BK;
   // The ring holds up to ST tiles in flight or resident.
-  if constexpr (!AHEAD) {
+  if constexpr (!AHEAD && !WHOLE) {
 #pragma unroll
     for (int s = 0; s < ST; ++s)
       if (s < KT) issue(s, s);
@@ -762,6 +778,68 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
     if (kt + 2 < KT) body(kt++, std::integral_constant<int, 2>());
     if (kt + 1 < KT) body(kt++, std::integral_constant<int, 1>());
     body(kt, std::integral_constant<int, 0>());
+  } else if constexpr (WHOLE) {
+    const char* const ua = uniform_ptr(abase);
+    const char* const ub = uniform_ptr(bbase);
+    auto refill = [&](int kt, int slot) {
+      char* l = smem + slot * STAGE;
+#pragma unroll
+      for (int i = 0; i < A_INS; ++i)
+        buf16(ua, ga[i], kt * BK * (int)sizeof(TI), l + (wave * A_INS + i) * 1024);
+#pragma unroll
+      for (int i = 0; i < B_INS; ++i)
+        buf16(ub, gb[i], kt * BK * (int)sizeof(TI), l + A_BYTES + (wave * B_INS + i) * 1024);
+    };
+    frag fa[2][NKS][TM], fb[2][NKS][TN];
+    const bool computes = wave < NC;
+    auto read = [&](auto set, int slot) {
+      if (!computes) return;
+      const char* base = smem + slot * STAGE;
+#pragma unroll
+      for (int ks = 0; ks < NKS; ++ks) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[decltype(set)::value][ks][i] = rdfrag(base, aoff[ks], i);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[decltype(set)::value][ks][j] = rdfrag(base, boff[ks], j);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < SL - 1; ++s)
+      if (s < KT) refill(s, s);
+    wait_tiles<SL - 2, LPT>(KT - 1);
+    __builtin_amdgcn_s_barrier();
+    read(std::integral_constant<int, 0>(), 0);
+    int slot = 0;
+    // tile kt, its fragments in set P or on their way there
+    auto body = [&](int kt, auto set) {
+      constexpr int P = decltype(set)::value;
+      const int next = slot + 1 == SL ? 0 : slot + 1;
+      // this wave has used tile kt-1 and its part of tile kt+1 has landed;
+      // after the barrier that is so for every wave: tile kt-1's slot is free
+      __builtin_amdgcn_sched_barrier(0);
+      if (kt + 1 < KT) {
+        wait_tiles<SL - 3, LPT>(KT - 2 - kt);
+        __builtin_amdgcn_s_barrier();
+        if (kt + SL - 1 < KT) refill(kt + SL - 1, slot == 0 ? SL - 1 : slot - 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (computes) {
+        // (past the last tile the reads find an older one and are not used)
+        read(std::integral_constant<int, P ^ 1>(), next);
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks)
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fb[P][ks][j], fa[P][ks][i], acc[i][j]);
+        sched_step<NKS * TM * TN, NKS * (TM + TN) * NCH, 0>();
+      }
+      slot = next;
+    };
+    for (int kt = 0; kt < KT; kt += 2) {
+      body(kt, std::integral_constant<int, 0>());
+      if (kt + 1 < KT) body(kt + 1, std::integral_constant<int, 1>());
+    }
   } else {
   // Fragments are double-buffered across k-steps, also across tiles: the
   // buffer of a k-step is the parity of its global k-step index, a
@@ -824,7 +902,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams 
   // no refill is in flight (the last tiles issue none); every wave must have
   // finished reading the ring before the staging below reuses it
   __syncthreads();
-  epilogue<TO, TR, EPI, TM, TN, NW, SMEM>(p, acc, smem, wave, lane, m0 + wm * WTM, n0 + wn * WTN);
+  if (wave >= NC) return;
+  epilogue<TO, TR, EPI, TM, TN, NC, SMEM>(p, acc, smem, wave, lane, m0 + wm * WTM, n0 + wn * WTN);
 }
 
 struct Cfg {
@@ -838,7 +917,7 @@ struct Cfg {
 constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, int in_bytes, int out_bytes, int epi) {
   const int tn = bn / wgn / 32;
   if ((epi == EPI_ROPE || epi == EPI_GEGLU) && tn % 2 != 0) return false;
-  const int smem = st == kAhead ? (3 * bm + 2 * bn) * bk * in_bytes : st == 0 ? 2 * (bm + bn) * (bk + 16 / in_bytes) * in_bytes : st * (bm + bn) * bk * in_bytes;
+  const int smem = st >= kTileRegs ? (st - kTileRegs) * (bm + bn) * bk * in_bytes : st == kAhead ? (3 * bm + 2 * bn) * bk * in_bytes : st == 0 ? 2 * (bm + bn) * (bk + 16 / in_bytes) * in_bytes : st * (bm + bn) * bk * in_bytes;
   const int otn = epi == EPI_GEGLU ? tn / 2 : tn;
   return smem >= wgm * wgn * 32 * otn * 32 * out_bytes;
 }
@@ -866,7 +945,10 @@ constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, in
   X(16, 64, 64, 64, 2, 2, kAhead, 4, "bf16_64x64x64_w2x2_a")     \
   X(17, 64, 64, 128, 2, 2, kAhead, 2, "bf16_64x64x128_w2x2_a")   \
   X(18, 32, 64, 128, 1, 2, kAhead, 2, "bf16_32x64x128_w1x2_a")   \
-  X(19, 64, 64, 64, 2, 1, kAhead, 2, "bf16_64x64x64_w2x1_a")
+  X(19, 64, 64, 64, 2, 1, kAhead, 2, "bf16_64x64x64_w2x1_a") \
+  X(20, 32, 64, 128, 1, 2, kTileRegs + 4, 1, "bf16_32x64x128_w1x2_r4") \
+  X(21, 32, 32, 128, 1, 1, kTileRegs + 3, 1, "bf16_32x32x128_w1x1_r3") \
+  X(22, 64, 64, 128, 2, 2, kTileRegs + 4, 1, "bf16_64x64x128_w2x2_r4")
 #define ANON_F32_CFGS(X)                                 \
   X(0, 128, 128, 32, 2, 2, 0, 2, "f32_128x128x32_w2x2") \
   X(1, 64, 64, 32, 2, 2, 0, 2, "f32_64x64x32_w2x2")     \
@@ -884,7 +966,9 @@ constexpr bool staging_fits(int bm, int bn, int bk, int wgm, int wgn, int st, in
   X(8, 128, 256, 128, 2, 4, kAhead, 1, "fp8_128x256x128_w2x4_a") \
   X(9, 128, 128, 128, 2, 2, kAhead, 2, "fp8_128x128x128_w2x2_a") \
   X(10, 64, 128, 128, 2, 2, kAhead, 2, "fp8_64x128x128_w2x2_a")  \
-  X(11, 64, 64, 128, 2, 2, kAhead, 4, "fp8_64x64x128_w2x2_a")
+  X(11, 64, 64, 128, 2, 2, kAhead, 4, "fp8_64x64x128_w2x2_a")    \
+  X(12, 32, 64, 256, 1, 2, kTileRegs + 4, 1, "fp8_32x64x256_w1x2_r4") \
+  X(13, 32, 32, 256, 1, 1, kTileRegs + 3, 1, "fp8_32x32x256_w1x1_r3")
 
 #define ANON_CFG_ROW(i, bm, bn, bk, wgm, wgn, st, occ, name) {bm, bn, bk, wgm, wgn, st, occ, name},
 const Cfg kCfgBF16[] = {ANON_BF16_CFGS(ANON_CFG_ROW)};
@@ -922,7 +1006,7 @@ bool run(const GemmParams& g, hipStream_t s) {
   } else {
     static_assert(sizeof(TI) <= 2, "the LDS ring kernel serves BF16 and FP8 operands");
     hipLaunchKernelGGL((gemm_dma_kernel<TI, TO, TR, EPI, BM, BN, BK, WGM, WGN, ST, OCC>), dim3(tiles),
-                       dim3(WGM * WGN * 64), 0, s, p);
+                       dim3((ST >= kTileRegs ? kLoaders : WGM * WGN) * 64), 0, s, p);
   }
   return true;
   }
@@ -1028,12 +1112,14 @@ const TileCost kCostBF16[] = {
     {13, 1.4f, 0.825f, 2.7f, 1.03f, 3.0f, kWhole}, {14, 2.7f, 0.506f, 0.7f, 0.53f, 1.0f, kPair},
     {15, 0.6f, 0.508f, 1.27f, 0.303f, 0.6f, kPair}, {16, 0.5f, 0.406f, 0.3f, 0.19f, 0.4f, kFine},
     {17, 2.5f, 0.261f, 0.65f, 0.2f, 0.4f, kFine},  {18, 2.9f, 0.2f, 0.96f, 0.134f, 0.4f, kFine},
-    {19, 0.5f, 0.46f, 0.3f, 0.25f, 0.4f, kFine},
+    {19, 0.5f, 0.46f, 0.3f, 0.25f, 0.4f, kFine},   {20, 3.27f, 0.128f, 1.8f, 0.15f, 0.3f, kStep},
+    {21, 3.25f, 0.114f, 0.74f, 0.13f, 0.3f, kStep}, {22, 3.45f, 0.14f, 0.2f, 0.3f, 0.3f, kStep},
 };
 const TileCost kCostFP8[] = {
     {7, 6.3f, 1.02f, 8.0f, 1.25f, 9.0f, kWhole},   {8, 2.0f, 0.875f, 3.2f, 0.9f, 3.5f, kWhole},
     {9, 3.1f, 0.53f, 0.7f, 0.54f, 1.1f, kPair},    {10, 3.7f, 0.25f, 0.7f, 0.34f, 0.5f, kFine},
-    {11, 3.1f, 0.19f, 0.34f, 0.2f, 0.3f, kFine},
+    {11, 3.1f, 0.19f, 0.34f, 0.2f, 0.3f, kFine},   {12, 3.25f, 0.14f, 1.5f, 0.167f, 0.3f, kStep},
+    {13, 3.23f, 0.121f, 0.93f, 0.121f, 0.3f, kStep},
 };
 
 const TileCost kCostF32[] = {
@@ -1064,7 +1150,7 @@ int default_gemm_config(const GemmParams& g) {
   // for every size leaves most CUs idle on a small batch: with 256x256 tiles
   // alone, a record of 137 tokens runs its four GEMMs of a layer on 3 to 12
   // workgroups (20, 20, 25 and 61 us on the base shapes); the tiles chosen
-  // here take 5.3, 5.4, 5.8 and 12.1 us, and at 2,094 rows 13, 7, 17 and 22
+  // here take 4.8, 4.6, 5.3 and 8.7 us, and at 2,094 rows 13, 7, 17 and 22
   // instead of 21, 21, 27 and 63.  At 8,192 rows and above the choice is
   // worth 0-25% (the last round of 256x256 tiles), from 21,608 rows on it is
   // mostly the 256x256 tile.  FP32: 137 rows 56, 56, 57 and 210 us with
