@@ -188,27 +188,31 @@ __device__ __forceinline__ void st4(fp8_t* p, const float (&v)[4]) {
   *(int*)p = w;
 }
 
+// Bias of a lane's columns (loaded before any store).
+template <int TN>
+__device__ __forceinline__ void load_bias(const DevParams& p, int lane, int wcol0, floatx4 (&bias)[TN][4]) {
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bias[j][q] = *(const floatx4*)(p.bias + wcol0 + j * 32 + q * 8 + (lane >> 5) * 4);
+}
+
 // Applies the epilogue to a wave's (TM*32) x (TN*32) accumulator block whose
 // top-left output element is (wrow0, wcol0).
 template <typename TO, typename TR, int EPI, int TM, int TN, int NW, int SMEM>
 __device__ __forceinline__ void epilogue(const DevParams& p, floatx16 (&acc)[TM][TN], char* smem, int wave, int lane,
-                                         int wrow0, int wcol0) {
+                                         int M, int wrow0, int wcol0,
+                                         const floatx4 (&bias)[TN][4]) {
   typedef Staging<TO, EPI, TM, TN, NW, SMEM> SG;
   constexpr int ROWB = SG::ROWB, CPR = SG::CPR, SWZ = SG::SWZ, NS = SG::NS;
-  const int M = live_rows(p.M, p.m_dev), N = p.N;
+  const int N = p.N;
   constexpr bool PAIRED = EPI == EPI_ROPE || EPI == EPI_GEGLU;
   static_assert(!PAIRED || TN % 2 == 0, "paired epilogues need whole 64-column blocks per wave");
   static_assert(EPI != EPI_GEGLU || sizeof(TO) >= 2, "the gated epilogue writes bf16 or fp32");
   // where this wave's outputs start in a row of C
   const int ocol0 = EPI == EPI_GEGLU ? wcol0 / 2 : wcol0;
-  char* stg = smem + wave * NS * SG::STRIP;
+  char* stg = smem + wave * (SMEM / NW / 1024 * 1024);
   const int lrow = lane & 31, lq = (lane >> 5) * 4;
-  // bias of the lane's columns (loaded before any store)
-  floatx4 bias[TN][4];
-#pragma unroll
-  for (int j = 0; j < TN; ++j)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) bias[j][q] = *(const floatx4*)(p.bias + wcol0 + j * 32 + q * 8 + lq);
 #pragma unroll
   for (int i0 = 0; i0 < TM; i0 += NS) {
     if constexpr (EPI == EPI_RESID) {
@@ -462,7 +466,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
     if (kt + 1 < KT) lstore(buf ^ 1);
     __syncthreads();
   }
-  epilogue<TO, TR, EPI, TM, TN, WGM * WGN, OPND_BYTES>(p, acc, smem, wave, lane, m0 + wm * WTM, n0 + wn * WTN);
+  floatx4 bias[TN][4];
+  load_bias(p, lane, n0 + wn * WTN, bias);
+  epilogue<TO, TR, EPI, TM, TN, WGM * WGN, OPND_BYTES>(p, acc, smem, wave, lane, M, m0 + wm * WTM, n0 + wn * WTN, bias);
 }
 
 // LDS-ring kernel (BF16 / FP8 operands).  Each K tile travels from global
@@ -490,6 +496,15 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // waves of 128x128 with its accumulators pinned in AGPRs reads a third less
 // LDS but has nothing to run while its one wave per SIMD waits: 3.06 / 1.29 /
 // 4.80 / 3.59 ms with the same ring, not kept.
+//
+// Where the epilogue stages no more than a wave's own part of A's third slot
+// (BF16 256x256, all but the residual epilogue), a workgroup keeps its CU for
+// every 256th tile: the next tile's first copies, all but those into that
+// slot, travel during the epilogue.  855,055 rows: FFN1 4.71 -> 4.54 ms, QKV
+// 2.76 -> 2.72; the epilogue itself (the GELU is 92 of its clocks per element
+// and wave) still runs with the matrix pipe idle, and two workgroups of 128x256
+// tiles per CU, which overlap it, lose more in the main loop (QKV of 200,000
+// rows 644 us against 789, FFN1 1037 against 1087).  FP8 spills with it.
 //
 // kTileRegs: for batches so small that a CU has one tile and what counts is
 // how long one K tile takes.  With one or four 32x32 blocks in a workgroup a
@@ -602,6 +617,10 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
   constexpr bool AHEAD = ST == kAhead, WHOLE = ST >= kTileRegs;
   constexpr int SL = WHOLE ? ST - kTileRegs : ST;  // stages
   static_assert(AHEAD || (SL - 1) * LPT < 64, "vmcnt range");
+  // a workgroup stays for several tiles where the epilogue needs no more than
+  // A's third slot (see kAhead above)
+  constexpr bool PERSIST =
+      AHEAD && OCC == 1 && sizeof(TI) == 2 && EPI != EPI_RESID && A_BYTES >= NW * Staging<TO, EPI, TM, TN, NW, 1 << 20>::STRIP;
   constexpr int SMEM = AHEAD ? 3 * A_BYTES + 2 * (STAGE - A_BYTES) : SL * STAGE;
   static_assert(SMEM <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
   __shared__ __align__(1024) char smem[SMEM];
@@ -617,18 +636,19 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
   const int ntn = N / BN;
   const int ntm = (M + BM - 1) / BM;
   if ((int)blockIdx.x >= ntm * ntn) return;
-  int mb, nb;
-  group_tile(xcd_remap(blockIdx.x, ntm * ntn), ntm, ntn, p.group_m, mb, nb);
-  const int m0 = mb * BM, n0 = nb * BN;
-
   // this lane's source of each load instruction, as a byte offset from the
   // tile's first row at k = 0 (uniform bases stay in scalar registers; rows
   // past M, in the last row block only, re-read row M-1: never stored, no
   // branch)
-  const char* const abase = (const char*)p.A + (size_t)m0 * K * sizeof(TI);
-  const char* const bbase = (const char*)p.W + (size_t)n0 * K * sizeof(TI);
+  int m0, n0;
+  const char *abase, *bbase;
   uint32_t ga[A_INS], gb[B_INS];
-  {
+  auto go_to = [&](int tile) {
+    int mb, nb;
+    group_tile(xcd_remap(tile, ntm * ntn), ntm, ntn, p.group_m, mb, nb);
+    m0 = mb * BM, n0 = nb * BN;
+    abase = (const char*)p.A + (size_t)m0 * K * sizeof(TI);
+    bbase = (const char*)p.W + (size_t)n0 * K * sizeof(TI);
     const int rl = lane / CPR, slot = lane % CPR;
 #pragma unroll
     for (int i = 0; i < A_INS; ++i) {
@@ -640,7 +660,8 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
       const int r = (wave * B_INS + i) * RPI + rl;
       gb[i] = (uint32_t)(r * K + (slot ^ lds_swz<CPR>(r)) * EPC) * (uint32_t)sizeof(TI);
     }
-  }
+  };
+  go_to(blockIdx.x);
   auto issue = [&](int kt, int stage) {
     char* sa = smem + stage * STAGE + wave * A_INS * 1024;
     char* sb = smem + stage * STAGE + A_BYTES + wave * B_INS * 1024;
@@ -677,12 +698,15 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
   };
 
   floatx16 acc[TM][TN];
+  auto clear = [&] {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  };
+  clear();
 
   const int KT = K / BK;
   // The ring holds up to ST tiles in flight or resident.
@@ -700,8 +724,7 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
     // kt+2 and A of tile kt+3.
     static_assert(NKS % 2 == 0, "the fragment buffers of a k-step are the same in every tile");
     constexpr int B0 = 3 * A_BYTES, B_BYTES = BN * ROWB;
-    const char* const ua = uniform_ptr(abase);
-    const char* const ub = uniform_ptr(bbase);
+    const char *ua, *ub;
     auto issue_a = [&](int kt, int slot) {
 #pragma unroll
       for (int i = 0; i < A_INS; ++i)
@@ -712,72 +735,99 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
       for (int i = 0; i < B_INS; ++i)
         buf16(ub, gb[i], kt * BK * (int)sizeof(TI), smem + B0 + slot * B_BYTES + (wave * B_INS + i) * 1024);
     };
-    issue_b(0, 0);
-    issue_a(0, 0);
-    if (KT > 2) {
-      issue_b(1, 1);
-      issue_a(1, 1);
-      issue_a(2, 2);
-      wait_vmcnt<2 * A_INS + B_INS>();
-    } else if (KT > 1) {
-      issue_b(1, 1);
-      issue_a(1, 1);
-      wait_vmcnt<A_INS + B_INS>();
-    } else {
-      wait_vmcnt<0>();
-    }
-    __builtin_amdgcn_s_barrier();
-    frag fa[2][TM], fb[2][TN];
-    auto read_a = [&](int set, int slot, int ks) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[set][i] = rdfrag(smem + slot * A_BYTES, aoff[ks], i);
-    };
-    auto read_b = [&](int set, int slot, int ks) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j) fb[set][j] = rdfrag(smem + B0 - A_BYTES + slot * B_BYTES, boff[ks], j);
-    };
-    read_a(0, 0, 0);
-    read_b(0, 0, 0);
-    int sa = 0, sb = 0;  // this tile's slots
-    // one tile with LEFT tiles after it (3: three or more)
-    auto body = [&](int kt, auto leftc) {
-      constexpr int LEFT = decltype(leftc)::value;
-      constexpr int NRD = (TM + TN) * NCH;
-      const int na = sa == 2 ? 0 : sa + 1;
-#pragma unroll
-      for (int ks = 0; ks < NKS; ++ks) {
-        const int cur = ks & 1;
-        if (ks + 1 < NKS) {
-          read_a(cur ^ 1, sa, ks + 1 < NKS ? ks + 1 : 0);
-          read_b(cur ^ 1, sb, ks + 1 < NKS ? ks + 1 : 0);
-        } else if constexpr (LEFT > 0) {
-          // this wave's reads of the tile have returned and tile kt+1 has
-          // landed (of the later issues only A of kt+2 may be in flight);
-          // after the barrier both hold for every wave
-          __builtin_amdgcn_sched_barrier(0);
-          __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) (vmcnt, expcnt at maxima)
-          wait_vmcnt<(LEFT > 1 ? A_INS : 0)>();
-          __builtin_amdgcn_s_barrier();
-          read_a(cur ^ 1, na, 0);
-          read_b(cur ^ 1, sb ^ 1, 0);
-          if constexpr (LEFT > 1) issue_b(kt + 2, sb);
-          if constexpr (LEFT > 2) issue_a(kt + 3, sa);
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fb[cur][j], fa[cur][i], acc[i][j]);
-        if (ks + 1 < NKS) sched_step<TM * TN, NRD, 0>();
-        else sched_step<TM * TN, (LEFT > 0 ? NRD : 0), (LEFT > 2 ? LPT : LEFT > 1 ? B_INS : 0)>();
+    auto start = [&] {  // all of a tile's first copies but those into A's third slot
+      ua = uniform_ptr(abase);
+      ub = uniform_ptr(bbase);
+      issue_b(0, 0);
+      issue_a(0, 0);
+      if (KT > 1) {
+        issue_b(1, 1);
+        issue_a(1, 1);
       }
-      sa = na;
-      sb ^= 1;
     };
-    int kt = 0;
-    for (; kt + 3 < KT; ++kt) body(kt, std::integral_constant<int, 3>());
-    if (kt + 2 < KT) body(kt++, std::integral_constant<int, 2>());
-    if (kt + 1 < KT) body(kt++, std::integral_constant<int, 1>());
-    body(kt, std::integral_constant<int, 0>());
+    start();
+    int tile = blockIdx.x;
+    for (;;) {
+      if (KT > 2) {
+        issue_a(2, 2);
+        wait_vmcnt<2 * A_INS + B_INS>();
+      } else if (KT > 1) {
+        wait_vmcnt<A_INS + B_INS>();
+      } else {
+        wait_vmcnt<0>();
+      }
+      __builtin_amdgcn_s_barrier();
+      frag fa[2][TM], fb[2][TN];
+      auto read_a = [&](int set, int slot, int ks) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) fa[set][i] = rdfrag(smem + slot * A_BYTES, aoff[ks], i);
+      };
+      auto read_b = [&](int set, int slot, int ks) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) fb[set][j] = rdfrag(smem + B0 - A_BYTES + slot * B_BYTES, boff[ks], j);
+      };
+      read_a(0, 0, 0);
+      read_b(0, 0, 0);
+      int sa = 0, sb = 0;  // this tile's slots
+      // one tile with LEFT tiles after it (3: three or more)
+      auto body = [&](int kt, auto leftc) {
+        constexpr int LEFT = decltype(leftc)::value;
+        constexpr int NRD = (TM + TN) * NCH;
+        const int na = sa == 2 ? 0 : sa + 1;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+          const int cur = ks & 1;
+          if (ks + 1 < NKS) {
+            read_a(cur ^ 1, sa, ks + 1 < NKS ? ks + 1 : 0);
+            read_b(cur ^ 1, sb, ks + 1 < NKS ? ks + 1 : 0);
+          } else if constexpr (LEFT > 0) {
+            // this wave's reads of the tile have returned and tile kt+1 has
+            // landed (of the later issues only A of kt+2 may be in flight);
+            // after the barrier both hold for every wave
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) (vmcnt, expcnt at maxima)
+            wait_vmcnt<(LEFT > 1 ? A_INS : 0)>();
+            __builtin_amdgcn_s_barrier();
+            read_a(cur ^ 1, na, 0);
+            read_b(cur ^ 1, sb ^ 1, 0);
+            if constexpr (LEFT > 1) issue_b(kt + 2, sb);
+            if constexpr (LEFT > 2) issue_a(kt + 3, sa);
+          }
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = MF::mma(fb[cur][j], fa[cur][i], acc[i][j]);
+          if (ks + 1 < NKS) sched_step<TM * TN, NRD, 0>();
+          else sched_step<TM * TN, (LEFT > 0 ? NRD : 0), (LEFT > 2 ? LPT : LEFT > 1 ? B_INS : 0)>();
+        }
+        sa = na;
+        sb ^= 1;
+      };
+      int kt = 0;
+      for (; kt + 3 < KT; ++kt) body(kt, std::integral_constant<int, 3>());
+      if (kt + 2 < KT) body(kt++, std::integral_constant<int, 2>());
+      if (kt + 1 < KT) body(kt++, std::integral_constant<int, 1>());
+      if constexpr (PERSIST) {
+        const int row0 = m0 + wm * WTM, col0 = n0 + wn * WTN;
+        floatx4 bias[TN][4];
+        load_bias(p, lane, col0, bias);  // (there before the copies below, which it would wait for)
+        body(kt, std::integral_constant<int, 0>());
+        wait_vmcnt<0>();
+        __syncthreads();  // every wave has read the ring to its end
+        tile += gridDim.x;
+        const bool more = tile < ntm * ntn;
+        if (more) {
+          go_to(tile);
+          start();
+        }
+        epilogue<TO, TR, EPI, TM, TN, NW, A_BYTES>(p, acc, smem + 2 * A_BYTES, wave, lane, M, row0, col0, bias);
+        if (!more) return;
+        clear();
+      } else {
+        body(kt, std::integral_constant<int, 0>());
+        break;
+      }
+    }
   } else if constexpr (WHOLE) {
     const char* const ua = uniform_ptr(abase);
     const char* const ub = uniform_ptr(bbase);
@@ -903,7 +953,9 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
   // finished reading the ring before the staging below reuses it
   __syncthreads();
   if (wave >= NC) return;
-  epilogue<TO, TR, EPI, TM, TN, NC, SMEM>(p, acc, smem, wave, lane, m0 + wm * WTM, n0 + wn * WTN);
+  floatx4 bias[TN][4];
+  load_bias(p, lane, n0 + wn * WTN, bias);
+  epilogue<TO, TR, EPI, TM, TN, NC, SMEM>(p, acc, smem, wave, lane, M, m0 + wm * WTM, n0 + wn * WTN, bias);
 }
 
 struct Cfg {
@@ -1000,12 +1052,16 @@ bool run(const GemmParams& g, hipStream_t s) {
   DevParams p{g.A, g.W, g.bias, g.resid, g.C, g.M, g.N, g.K, g.qscale, g.qcols, g.acc_scale, g.out_inv_scale, gm,
               g.ldc > 0 ? g.ldc : (g.epi == EPI_GEGLU ? g.N / 2 : g.N), g.pos, g.rope, g.rope_cols, g.m_dev};
   const int tiles = ((g.M + BM - 1) / BM) * (g.N / BN);
+  // (a workgroup of the persistent kernel has a CU to itself)
+  constexpr bool PERSIST = ST == kAhead && OCC == 1 && sizeof(TI) == 2 && EPI != EPI_RESID &&
+                           BM * BK * (int)sizeof(TI) >= WGM * WGN * Staging<TO, EPI, BM / WGM / 32, BN / WGN / 32, WGM * WGN, 1 << 20>::STRIP;
   if constexpr (ST == 0) {
     hipLaunchKernelGGL((gemm_kernel<TI, TO, TR, EPI, BM, BN, BK, WGM, WGN, OCC>), dim3(tiles),
                        dim3(WGM * WGN * 64), 0, s, p);
   } else {
     static_assert(sizeof(TI) <= 2, "the LDS ring kernel serves BF16 and FP8 operands");
-    hipLaunchKernelGGL((gemm_dma_kernel<TI, TO, TR, EPI, BM, BN, BK, WGM, WGN, ST, OCC>), dim3(tiles),
+    hipLaunchKernelGGL((gemm_dma_kernel<TI, TO, TR, EPI, BM, BN, BK, WGM, WGN, ST, OCC>),
+                       dim3(PERSIST ? std::min(tiles, 256) : tiles),
                        dim3((ST >= kTileRegs ? kLoaders : WGM * WGN) * 64), 0, s, p);
   }
   return true;

@@ -66,3 +66,63 @@ def test_default_tiles_equal_the_widest_tile(torch_dev, size, precision):
         assert torch.equal(got, want), f"{T} rows"
     assert api.device_errors() == 0
     m.close()
+
+
+def _hidden_with(m, pl, db, tiles):
+    import torch
+    m.set_tiles(tiles)
+    h = pl.hidden(db, 1)
+    torch.cuda.synchronize()
+    return h
+
+
+@pytest.mark.parametrize("hidden,ffn,T", [(64, 256, 66001), (128, 256, 70001), (256, 1024, 30011)])
+def test_several_tiles_per_workgroup(torch_dev, hidden, ffn, T):
+    """256x256 tiles of more than 256 per GEMM (a workgroup then takes several),
+    one, two and four K tiles long, a ragged last row block: the bits of 128x128
+    tiles, which are a workgroup each."""
+    import torch
+    from paper_2606_15650_amd.pipeline import Pipeline
+    cfg = replace(BASE, n_layers=1, vocab=2000, hidden=hidden, n_heads=hidden // 64, ffn=ffn)
+    _, m = make_model(cfg, "bf16", 0)
+    names = m.tile_configs()
+    assert "256x256x64" in names[11] and "128x128x64" in names[14]
+    L = _lengths(T)
+    cu = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+
+    class Batch:
+        B, h_cu = len(L), cu
+    db = Batch()
+    db.T = T
+    db.ids = torch.from_numpy(np.random.default_rng(hidden).integers(0, cfg.vocab, T).astype(np.int32)).cuda()
+    db.cu = torch.from_numpy(cu).cuda()
+    say(f"[gemm] {T} rows, hidden {hidden}, ffn {ffn}")
+    pl = Pipeline(m)
+    want = _hidden_with(m, pl, db, [-1, -1, 14, -1])
+    got = _hidden_with(m, pl, db, [11 if 3 * hidden % 256 == 0 else -1, -1, 11, -1])
+    assert torch.equal(got, want)
+    m.close()
+
+
+def test_several_tiles_per_workgroup_rotary_and_gated(torch_dev):
+    import torch
+    from paper_2606_15650_amd import api
+    from paper_2606_15650_amd.pipeline import Pipeline
+    from synth.configs import MODERN_TINY
+    cfg = replace(MODERN_TINY, n_layers=1, vocab=2000, hidden=256, n_heads=4, intermediate=512)
+    m = api.ModernModel(cfg, synth.weights_blob(cfg, synth.make_weights(cfg, 0, None)), "bf16")
+    T = 30011
+    L = _lengths(T)
+    cu = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+    ids = torch.from_numpy(np.random.default_rng(1).integers(0, cfg.vocab, T).astype(np.int32)).cuda()
+    d_cu = torch.from_numpy(cu).cuda()
+    n = m.workspace_size(T, len(L))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    outs = []
+    for t in (14, 11):
+        m.set_tiles([t, -1, t, -1, -1])
+        out = torch.empty((T, cfg.hidden), dtype=torch.float32, device="cuda")
+        m.hidden(ids, d_cu, len(L), T, 1, out, ws, n)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
