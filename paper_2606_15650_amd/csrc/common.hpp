@@ -97,6 +97,36 @@ __device__ __forceinline__ int wg_find_record(const T* cu, int B, T p) {
   return lo;
 }
 
+// The records of two positions p <= q by the same steps.
+template <typename T>
+__device__ __forceinline__ int2 wg_find_records(const T* cu, int B, T p, T q) {
+  const int nt = blockDim.x, tid = threadIdx.x;
+  int lo = 0, n = B, lo2 = 0, n2 = B;
+  while (n > 1 || n2 > 1) {
+    const int step = (n + nt - 1) / nt, at = tid * step, step2 = (n2 + nt - 1) / nt, at2 = tid * step2;
+    const T c = at < n ? cu[lo + at] : 0, c2 = at2 < n2 ? cu[lo2 + at2] : 0;
+    const int cnt = __syncthreads_count(at < n && (at == 0 || c <= p));
+    const int cnt2 = __syncthreads_count(at2 < n2 && (at2 == 0 || c2 <= q));
+    lo += (cnt - 1) * step;
+    n = min(step, n - (cnt - 1) * step);
+    lo2 += (cnt2 - 1) * step2;
+    n2 = min(step2, n2 - (cnt2 - 1) * step2);
+  }
+  return int2{lo, lo2};
+}
+
+// The bytes' bit 7 gathered into four bits (a multiplication).
+__device__ __forceinline__ uint32_t byte_bits(uint32_t flags) { return (flags >> 7) * 0x10204080u >> 28; }
+// Bit 7 of each byte of w: the byte equals c / lies in [lo, hi], lo >= 1, hi <= 127.
+__device__ __forceinline__ uint32_t bytes_equal(uint32_t w, uint8_t c) {
+  const uint32_t x = w ^ (c * 0x01010101u);
+  return ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
+}
+__device__ __forceinline__ uint32_t bytes_between(uint32_t w, uint8_t lo, uint8_t hi) {
+  const uint32_t x = w & 0x7f7f7f7fu;
+  return (x + (128 - lo) * 0x01010101u) & ~(x + (127 - hi) * 0x01010101u) & ~w & 0x80808080u;
+}
+
 // 16 bytes from an address of any alignment
 __device__ __forceinline__ uint4 load16(const uint8_t* p) {
   uint4 v;

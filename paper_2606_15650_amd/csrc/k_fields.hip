@@ -44,14 +44,6 @@ __device__ __forceinline__ int find_in(const int64_t* cu, int a, int c, int64_t 
   return a;
 }
 
-// A bit per byte of w equal to c (given four times): the bytes of w ^ cccc
-// that are zero, exactly, their flags gathered by a multiplication.
-__device__ __forceinline__ uint32_t match4(uint32_t w, uint32_t cccc) {
-  const uint32_t x = w ^ cccc;
-  const uint32_t zero = ~(((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x | 0x7f7f7f7fu);
-  return (zero >> 7) * 0x10204080u >> 28;
-}
-
 // First set bit at or after o of two bitmaps of the window, kWin if none.
 __device__ __forceinline__ int next_bit(const uint64_t* x, const uint64_t* y, int o) {
   for (int w = o >> 6; w < kWinWords; ++w) {
@@ -86,8 +78,8 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
     uint32_t mn = 0, mc = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      mn |= match4(w[i], 0x0a0a0a0au) << (4 * i);
-      mc |= match4(w[i], 0x3a3a3a3au) << (4 * i);
+      mn |= byte_bits(bytes_equal(w[i], '\n')) << (4 * i);
+      mc |= byte_bits(bytes_equal(w[i], ':')) << (4 * i);
     }
     *(uint4*)(win + piece * 16) = uint4{w[0], w[1], w[2], w[3]};
     ((uint16_t*)nl)[piece] = (uint16_t)mn;

@@ -429,17 +429,29 @@ __device__ __forceinline__ uint4 text16(const uint8_t* __restrict__ text, int64_
   return uint4{w[0], w[1], w[2], w[3]};
 }
 
-// Class bits of 16 staged bytes.
-__device__ __forceinline__ void class_bits(const uint4& v, uint32_t (&m)[C_COUNT]) {
+// Class bits of 16 staged bytes (and of the anchors among them), four bytes at
+// a time: the classes byte by byte took three times the instructions.
+__device__ __forceinline__ uint32_t class_bits(const uint4& v, uint32_t (&m)[C_COUNT]) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  uint32_t anchors = 0;
 #pragma unroll
   for (int k = 0; k < C_COUNT; ++k) m[k] = 0;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const uint8_t c = (w[i >> 2] >> (8 * (i & 3))) & 0xff;
-#pragma unroll
-    for (int k = 0; k < C_COUNT; ++k) m[k] |= (in_class(c, k) ? 1u : 0u) << i;
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t lower = w[i] | 0x20202020u;
+    const uint32_t digit = bytes_between(w[i], '0', '9'), letter = bytes_between(lower, 'a', 'z');
+    const uint32_t dash = bytes_equal(w[i], '-'), dot = bytes_equal(w[i], '.');
+    const uint32_t label = digit | letter | dash;
+    const uint32_t local = label | dot | bytes_equal(w[i], '_') | bytes_equal(w[i], '%') | bytes_equal(w[i], '+');
+    const uint32_t space = bytes_equal(w[i], ' ') | bytes_between(w[i], '\t', '\r');
+    m[C_LABEL] |= byte_bits(label) << (4 * i);
+    m[C_LOCAL] |= byte_bits(local) << (4 * i);
+    m[C_HEX] |= byte_bits(digit | bytes_between(lower, 'a', 'f')) << (4 * i);
+    m[C_LETTER] |= byte_bits(letter) << (4 * i);
+    m[C_TEXT] |= byte_bits(~space & 0x80808080u) << (4 * i);
+    anchors |= byte_bits(dash | dot | bytes_equal(w[i], ':') | bytes_equal(w[i], '@')) << (4 * i);
   }
+  return anchors;
 }
 
 constexpr int kBounds = 64;  // records of a tile whose boundaries are staged
@@ -477,26 +489,28 @@ __global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict
   __shared__ int n_list[L_COUNT], n_entries, bound[kBounds + 1];
   const int64_t p0 = (int64_t)blockIdx.x * kTile;
   const int base = (int)p0 - kBefore, wlo = max(base, 0), whi = (int)min(p0 + kTile + kAfter, n);
+  uint32_t my_hex = 0, my_anchors = 0;
   auto stage = [&](int piece, const uint4& v) {  // 16 bytes and their class bits
     uint32_t m[C_COUNT];
-    class_bits(v, m);
+    my_anchors = class_bits(v, m);
+    my_hex = m[C_HEX];
     *(uint4*)(win + piece * 16) = v;
 #pragma unroll
     for (int k = 0; k < C_COUNT; ++k) ((uint16_t*)cls[k])[piece] = (uint16_t)m[k];
-    return m[C_HEX];
   };
+  // the text travels while the records of the tile's first and last byte are
+  // looked for
   const uint4 mine = text16(text, p0 + tid * 16, n);
-  const uint32_t my_hex = stage(kBefore / 16 + tid, mine);
-  if (tid < kBefore / 16) {
-    stage(tid, p0 > 0 ? load16(text + p0 - kBefore + tid * 16) : uint4{0, 0, 0, 0});
-  } else if (tid >= 64 && tid < 64 + kAfter / 16) {
-    const int k = tid - 64;
-    stage((kBefore + kTile) / 16 + k, text16(text, p0 + kTile + k * 16, n));
-  }
+  const int halo = tid < kBefore / 16 ? tid : (kBefore + kTile) / 16 + tid - 64;  // (waves 0 and 1)
+  const bool has_halo = tid < kBefore / 16 || (tid >= 64 && tid < 64 + kAfter / 16);
+  uint4 other{0, 0, 0, 0};
+  if (has_halo && p0 - kBefore + halo * 16 >= 0) other = text16(text, p0 - kBefore + halo * 16, n);
   if (tid < L_COUNT) n_list[tid] = 0;
   if (tid == 0) n_entries = 0;
-  const int r0 = wg_find_record(cu, B, p0);
-  const int r1 = r0 + wg_find_record(cu + r0, B - r0, min(p0 + kTile, n) - 1);
+  const int2 rr = wg_find_records(cu, B, p0, min(p0 + kTile, n) - 1);
+  const int r0 = rr.x, r1 = max(rr.y, rr.x);
+  if (has_halo) stage(halo, other);
+  stage(kBefore / 16 + tid, mine);
   const bool few = r1 - r0 < kBounds;
   if (few && tid <= r1 - r0 + 1) bound[tid] = (int)min(max(cu[r0 + tid], (int64_t)0), n);
   __syncthreads();
@@ -509,14 +523,7 @@ __global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict
     if (k < room(l)) list[first(l) + k] = (uint16_t)v;
   };
   {
-    const uint32_t v[4] = {mine.x, mine.y, mine.z, mine.w};
-    uint32_t m = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const uint8_t c = (v[i >> 2] >> (8 * (i & 3))) & 0xff;
-      m |= (c == '.' || c == ':' || c == '-' || c == '@' ? 1u : 0u) << i;
-    }
-    for (; m; m &= m - 1) {
+    for (uint32_t m = my_anchors; m; m &= m - 1) {
       const int i = __ffs(m) - 1, off = tid * 16 + i;
       const uint8_t c = me[i], prev = me[i - 1], next = me[i + 1];
       if (c == '.') {
