@@ -72,6 +72,24 @@ __device__ __forceinline__ T wave_sum(T v) {
   for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+// The same sums in registers: the halves and the rows of 16 are exchanged by
+// permlane swaps; once all rows are equal in lanes 8 apart, a rotation by 4
+// finds what an exchange with lane ^ 4 would, and so on.  (Bits as above; the
+// six exchanges through LDS were a fifth of a small LayerNorm.)
+template <>
+__device__ __forceinline__ float wave_sum(float v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  x = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x128, 0xf, 0xf, true));  // row_ror:8
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x124, 0xf, 0xf, true));
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x122, 0xf, 0xf, true));
+  v += __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(v), 0x121, 0xf, 0xf, true));
+#endif
+  return v;
+}
 template <typename T>
 __device__ __forceinline__ T wave_max(T v) {
 #pragma unroll

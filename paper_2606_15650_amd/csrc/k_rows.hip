@@ -207,9 +207,6 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 constexpr int kMaxLabels = 64;
-#ifndef ANON_LN_RPW
-#define ANON_LN_RPW 2
-#endif
 
 // Token classifier on the FP32 matrix cores (C <= 16 NB labels): a wave forms
 // z^T = Wc x^T for 16 tokens with v_mfma_f32_16x16x4_f32, exact products of
@@ -516,16 +513,22 @@ void launch_layernorm(const void* y, ElemType y_t, const float* g, const float* 
                       void* out, ElemType out_t, fp8_t* out_q, float q_inv_scale, hipStream_t s,
                       const int* rows_dev) {
   if (rows <= 0) return;
-  constexpr int RPW = ANON_LN_RPW;
-  const int blocks = ceil_div(rows, 4 * RPW);
+  // One row per wave while the launch is bound by the latency of a row (137
+  // rows of 768: 3.7 us against 4.1 with two; 21,608: 14.6, 15.7) or a row has
+  // the bytes of two (FP32: 126,000 rows 101 us, 104); two BF16 rows where the
+  // bytes in flight count (162,000: 84 us against 92; 855,000: 444, 492).
   if (y_t == ET_F32) {
-    ANON_NPL_SWITCH(h / 64, hipLaunchKernelGGL((layernorm_kernel<float, NPL, RPW>), dim3(blocks), dim3(256), 0, s,
-                                               (const float*)y, g, b, eps, rows, out, out_t, out_q, q_inv_scale,
+    ANON_NPL_SWITCH(h / 64, hipLaunchKernelGGL((layernorm_kernel<float, NPL, 1>), dim3(ceil_div(rows, 4)), dim3(256),
+                                               0, s, (const float*)y, g, b, eps, rows, out, out_t, out_q, q_inv_scale,
                                                rows_dev));
+  } else if (rows < 65536) {
+    ANON_NPL_SWITCH(h / 64, hipLaunchKernelGGL((layernorm_kernel<bf16_t, NPL, 1>), dim3(ceil_div(rows, 4)), dim3(256),
+                                               0, s, (const bf16_t*)y, g, b, eps, rows, out, out_t, out_q,
+                                               q_inv_scale, rows_dev));
   } else {
-    ANON_NPL_SWITCH(h / 64, hipLaunchKernelGGL((layernorm_kernel<bf16_t, NPL, RPW>), dim3(blocks), dim3(256), 0, s,
-                                               (const bf16_t*)y, g, b, eps, rows, out, out_t, out_q, q_inv_scale,
-                                               rows_dev));
+    ANON_NPL_SWITCH(h / 64, hipLaunchKernelGGL((layernorm_kernel<bf16_t, NPL, 2>), dim3(ceil_div(rows, 8)), dim3(256),
+                                               0, s, (const bf16_t*)y, g, b, eps, rows, out, out_t, out_q,
+                                               q_inv_scale, rows_dev));
   }
 }
 

@@ -91,3 +91,19 @@ def test_hidden_states_to_an_unaligned_output(precision, shift):
             assert (buf[:s] == -7).all() and (buf[s + T * 64:] == -7).all()
             outs.append(buf[s:s + T * 64].cpu().numpy())
         np.testing.assert_array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("T", [65535, 65536, 65537])
+def test_layernorm_rows_per_wave(T):
+    """One or two rows per wave, by the number of rows: the same bits."""
+    from paper_2606_15650_amd.pipeline import Pipeline
+    cfg = ModelConfig(n_layers=1, hidden=64, n_heads=1, ffn=128, vocab=300, n_labels=9, max_pos=512)
+    _, m = make_model(cfg, "bf16", 0)
+    pl = Pipeline(m)
+    L = np.array([512] * (T // 512) + ([T % 512] if T % 512 else []))
+    ids = np.random.default_rng(T).integers(0, cfg.vocab, T).astype(np.int32)
+    got = pl.hidden(_batch(ids, L), 1)[:T].cpu().numpy()
+    half = 64 * 512
+    first = pl.hidden(_batch(ids[:half], L[:64]), 1)[:half].cpu().numpy()
+    rest = pl.hidden(_batch(ids[half:], L[64:]), 1)[:T - half].cpu().numpy()
+    np.testing.assert_array_equal(got, np.concatenate([first, rest]))
