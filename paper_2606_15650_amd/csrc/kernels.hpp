@@ -68,8 +68,7 @@ void launch_attention(const void* qkv, void* out, const int4* items, int max_ite
 void launch_embed_ln(const int* ids, const int* cu_seqlens, int B, int T, const float* tok_emb, const float* pos_emb,
                      const float* g, const float* b, float eps, int vocab, int max_pos, int h, void* out,
                      ElemType out_t, fp8_t* out_q, float q_inv_scale, uint32_t* err, hipStream_t s,
-                     int* pos_out = nullptr, const int* t_dev = nullptr);
-void launch_f32_to_bf16(const float* x, bf16_t* out, int64_t n, hipStream_t s);
+                     int* pos_out = nullptr, const int* t_dev = nullptr, bf16_t* out_b = nullptr);
 void launch_layernorm(const void* y, ElemType y_t, const float* g, const float* b, float eps, int rows, int h,
                       void* out, ElemType out_t, fp8_t* out_q, float q_inv_scale, hipStream_t s,
                       const int* rows_dev = nullptr);

@@ -148,7 +148,7 @@ anon_status run_layers(anon_modern* m, const int* ids, const int* cu, int B, int
   {
     ProfScope ps(KC_EMBED, s, 0.0);
     launch_embed_ln(ids, cu, B, T, m->tok_emb, nullptr, m->emb_g, m->zeros, c.ln_eps, c.vocab, c.max_pos, h, w.x,
-                    ET_F32, nullptr, 1.f, err, s, w.pos);
+                    ET_F32, nullptr, 1.f, err, s, w.pos, nullptr, bf ? (bf16_t*)w.hn : nullptr);
   }
   for (int l = 0; l < n_layers; ++l) {
     const ModernLayerW& L = m->layers[l];
@@ -158,8 +158,7 @@ anon_status run_layers(anon_modern* m, const int* ids, const int* cu, int B, int
     {
       ProfScope ps(KC_LN, s, 0.0);
       if (l == 0) {
-        if (bf) launch_f32_to_bf16(w.x, (bf16_t*)w.hn, (int64_t)T * h, s);
-        else hin = w.x;
+        if (!bf) hin = w.x;  // (in bf16 from the embedding)
       } else {
         launch_layernorm(w.x, ET_F32, L.attn_g, m->zeros, c.ln_eps, T, h, w.hn, m->gemm_t, nullptr, 1.f, s);
       }

@@ -107,3 +107,26 @@ def test_layernorm_rows_per_wave(T):
     first = pl.hidden(_batch(ids[:half], L[:64]), 1)[:half].cpu().numpy()
     rest = pl.hidden(_batch(ids[half:], L[64:]), 1)[:T - half].cpu().numpy()
     np.testing.assert_array_equal(got, np.concatenate([first, rest]))
+
+
+@pytest.mark.parametrize("C", [1, 9, 33])
+def test_window_merge_over_short_and_long_records(C):
+    """Record starts inside a wave's and a workgroup's tokens, empty records,
+    windows merged beside records that need none: every record as alone."""
+    from paper_2606_15650_amd.pipeline import Pipeline
+    cfg = ModelConfig(n_layers=1, hidden=64, n_heads=1, ffn=128, vocab=300, n_labels=C, max_pos=64)
+    _, m = make_model(cfg, "bf16", 0)
+    pl = Pipeline(m)
+    rng = np.random.default_rng(C)
+    L = np.concatenate([rng.integers(0, 5, 300), [200, 1, 64, 65, 0, 0, 127], rng.integers(0, 90, 40), [300]])
+    ids = rng.integers(0, cfg.vocab, int(L.sum())).astype(np.int32)
+    T = len(ids)
+    lab, z, mg = (x[:T].cpu().numpy() for x in pl.ner(_batch(ids, L), logits=True, margin=True, window=64, stride=32))
+    at = np.concatenate([[0], np.cumsum(L)])
+    for b in list(range(0, 300, 37)) + list(range(300, len(L))):
+        if L[b] == 0:
+            continue
+        r = slice(at[b], at[b + 1])
+        one = pl.ner(_batch(ids[r], [L[b]]), logits=True, margin=True, window=64, stride=32)
+        for got, want in zip((lab, z, mg), one):
+            np.testing.assert_array_equal(got[r], want[:L[b]].cpu().numpy())
