@@ -8,10 +8,10 @@
 //   bf16: v_mfma_f32_32x32x16_bf16    (K step 16)
 //   fp8 : v_mfma_scale_f32_32x32x64_f8f6f4 with E4M3 operands (K step 64)
 // Two main loops: BF16/FP8 operands stream global -> LDS directly through a
-// ring of ST K tiles (global_load_lds_dwordx4, XOR-swizzled rows); FP32
-// operands go through registers into double-buffered, padded LDS.  In both
-// the MFMA operands of k-step s+1 are read from LDS while those of step s
-// are multiplied.
+// ring of K tiles (XOR-swizzled rows; three forms of it, see gemm_dma_kernel);
+// FP32 operands go through registers into double-buffered, padded LDS.  In
+// both the MFMA operands of the next k-step are read from LDS while those of
+// this one are multiplied.
 //
 // The K loop always runs in increasing k with one MFMA shape per precision,
 // so each output element's sum is formed in the same order whatever the tile
