@@ -1137,6 +1137,15 @@ bool gemm_config_fits(ElemType in, int config, int N, int K) {
 
 static int elem_bytes(ElemType t) { return t == ET_F32 ? 4 : (t == ET_BF16 ? 2 : 1); }
 
+bool gemm_config_launchable(const GemmParams& g, int config) {
+  int n;
+  const Cfg* c = cfgs(g.in, &n);
+  if (config < 0 || config >= n) return false;
+  const Cfg& k = c[config];
+  const int64_t tiles = ((int64_t)g.M + k.bm - 1) / k.bm * (g.N / k.bn);
+  return tiles * (k.st >= kTileRegs ? kLoaders : k.wgm * k.wgn) * 64 <= 0xffffffffll;
+}
+
 bool gemm_config_serves(const GemmParams& g, int config) {
   int n;
   const Cfg* c = cfgs(g.in, &n);
@@ -1218,7 +1227,7 @@ int default_gemm_config(const GemmParams& g) {
   int best = -1;
   float best_t = 0.f;
   auto consider = [&](const TileCost& t) {
-    if (!gemm_config_serves(g, t.config)) return;
+    if (!gemm_config_serves(g, t.config) || !gemm_config_launchable(g, t.config)) return;
     // M is what a captured launch may hold, its row count on the device what
     // a replay brings: then the mean over the quarters of M counts.  8,192
     // rows at most, FFN2 of the base encoder with 4,096 / 8,192 brought:
@@ -1235,13 +1244,14 @@ int default_gemm_config(const GemmParams& g) {
     for (const TileCost& t : kCostF32) consider(t);
   if (best >= 0) return best;
   for (int c = 0; c < n; ++c)
-    if (gemm_config_serves(g, c)) return c;
+    if (gemm_config_serves(g, c) && gemm_config_launchable(g, c)) return c;
   return -1;
 }
 
 bool launch_gemm(const GemmParams& g, hipStream_t s) {
   int ci = g.config;
-  if (ci < 0) ci = default_gemm_config(g);
+  // (a tile kept for fewer rows: a launch holds less than 2^32 threads)
+  if (ci < 0 || (gemm_config_serves(g, ci) && !gemm_config_launchable(g, ci))) ci = default_gemm_config(g);
   if (ci < 0 || !gemm_config_serves(g, ci)) {
     set_error(ANON_EINVAL, "gemm: no tile configuration divides N=" + std::to_string(g.N) + " K=" +
                                std::to_string(g.K));

@@ -42,6 +42,8 @@ bool gemm_config_fits(ElemType in, int config, int N, int K);
 // the configuration divides the shape and, for the paired epilogues, gives
 // each wave whole 64-column blocks
 bool gemm_config_serves(const GemmParams& p, int config);
+// whether the configuration's launch for p.M rows stays below 2^32 threads
+bool gemm_config_launchable(const GemmParams& p, int config);
 
 // ---- attention ------------------------------------------------------------
 // Work list of the attention kernel (validates cu_seqlens on the device).

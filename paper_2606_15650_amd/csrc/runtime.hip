@@ -849,7 +849,7 @@ anon_status anon_autotune(anon_model* m, int32_t T, void* d_workspace, size_t ws
     std::vector<float> best_ms(ncfg, 1e30f);
     for (int round = 0; round < 2 && st == ANON_OK; ++round) {
       for (int ci = 0; ci < ncfg; ++ci) {
-        if (!gemm_config_fits(m->gemm_t, ci, g.N, g.K)) continue;
+        if (!gemm_config_fits(m->gemm_t, ci, g.N, g.K) || !gemm_config_launchable(g, ci)) continue;
         g.config = ci;
         if (!launch_gemm(g, s)) {
           st = ANON_EINVAL;
@@ -872,7 +872,7 @@ anon_status anon_autotune(anon_model* m, int32_t T, void* d_workspace, size_t ws
     const int def = default_gemm_config(g);
     int best_c = def;
     for (int ci = 0; ci < ncfg; ++ci) {
-      const bool fits = gemm_config_fits(m->gemm_t, ci, g.N, g.K);
+      const bool fits = gemm_config_fits(m->gemm_t, ci, g.N, g.K) && gemm_config_launchable(g, ci);
       if (times_ms && ci < max_configs) times_ms[gi * max_configs + ci] = fits ? best_ms[ci] : -1.f;
       if (!fits) continue;
       const float ref = best_c >= 0 ? best_ms[best_c] : 1e30f;

@@ -126,3 +126,34 @@ def test_several_tiles_per_workgroup_rotary_and_gated(torch_dev):
         torch.cuda.synchronize()
         outs.append(out)
     assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
+
+
+def test_a_launch_of_too_many_threads_takes_another_tile(torch_dev):
+    """A tile kept for a few rows, on so many that its workgroups would hold
+    2^32 threads: the call runs on another tile (the same bits), and the
+    autotuner leaves such tiles out."""
+    import torch
+    from paper_2606_15650_amd.pipeline import Pipeline
+    cfg = replace(BASE, n_layers=1, vocab=500, hidden=128, n_heads=2, ffn=32768)
+    _, m = make_model(cfg, "bf16", 0)
+    T, small = 262144 + 2049, 21
+    assert "32x32x128" in m.tile_configs()[small]
+    assert (T // 32) * (cfg.ffn // 32) * 512 >= 2 ** 32
+    L = _lengths(T)
+    cu = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+
+    class Batch:
+        B, h_cu = len(L), cu
+    db = Batch()
+    db.T = T
+    db.ids = torch.from_numpy(np.random.default_rng(2).integers(0, cfg.vocab, T).astype(np.int32)).cuda()
+    db.cu = torch.from_numpy(cu).cuda()
+    say(f"[gemm] {T} rows, ffn {cfg.ffn}")
+    pl = Pipeline(m)
+    want = _hidden_with(m, pl, db, [-1, -1, 14, -1])
+    got = _hidden_with(m, pl, db, [-1, -1, small, -1])
+    assert bool(torch.isfinite(want).all()) and torch.equal(got, want)
+    n = m.workspace_size(T, 1)
+    chosen, ms = m.autotune(T, torch.empty(n, dtype=torch.uint8, device="cuda"), n)
+    assert ms[2][small] < 0 and chosen[2] != small
+    m.close()
