@@ -153,7 +153,7 @@ struct RecogEntry {  // a match: its first byte and its union key
 struct RecogBuffers {
   unsigned long long *begins, *joins;  // bitmaps over the text
   uint16_t* word_rank;                 // per 64 bytes: unions begun before them in the tile
-  int *n_entries, *tile_count, *tile_pre;
+  int *n_entries, *tile_count, *tile_pre, *rec0;  // per tile; rec0: its first byte's record
   unsigned long long* keys;            // per union, at its rank in its tile
   RecogEntry* entries;
 };
