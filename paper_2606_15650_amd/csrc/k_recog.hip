@@ -48,6 +48,7 @@
 // launches.  4.9 MB of text with its NER spans in 4096 records: 467 ->
 // 38 us (the rules 23).
 #include "kernels.hpp"
+#include "text_words.hpp"
 
 namespace anon {
 namespace {
@@ -79,9 +80,10 @@ __device__ __forceinline__ bool in_class(uint8_t c, int k) {
 }
 
 // One record's bytes [lo, hi) of the text; positions are absolute (texts are
-// below 2^31 bytes).  Bytes inside the workgroup's staged window [wlo, whi)
-// are read from LDS (window position of byte i: i - base), the rest (long
-// runs past the window) from global memory.
+// below 2^31 - 2 bytes: a position and the one past it fit an int, the end of
+// its 64-byte word may not, see text_words.hpp).  Bytes inside the workgroup's
+// staged window [wlo, whi) are read from LDS (window position of byte i:
+// i - base), the rest (long runs past the window) from global memory.
 struct Rec {
   const uint8_t* t;
   int lo, hi;
@@ -115,15 +117,9 @@ struct Rec {
   template <int K>
   __device__ int run_end(int p) const {
     const int lim = min(hi, whi);
-    while (p < lim && p >= wlo) {
-      const int o = p - base;
-      const uint64_t stop = ~cls[K][o >> 6] >> (o & 63);
-      if (stop) {
-        p += __ffsll((unsigned long long)stop) - 1;
-        if (p < lim) return p;
-        break;
-      }
-      p += 64 - (o & 63);
+    if (p >= wlo && p < lim) {
+      p = set_run_end(cls[K], base, p, lim);
+      if (p < lim) return p;
     }
     p = min(p, hi);
     while (p < hi && in_class(at(p), K)) ++p;  // past the window
@@ -384,9 +380,8 @@ __global__ __launch_bounds__(256) void rx_init_kernel(unsigned long long* maps, 
 __device__ __forceinline__ void mark_span(const RecogBuffers& w, int b, int e) {
   atomicOr(&w.begins[b >> 6], 1ull << (b & 63));
   for (int i = b + 1; i < e;) {
-    const int stop = min(e, (i | 63) + 1);
-    const unsigned long long m = (stop - i == 64 ? ~0ull : (1ull << (stop - i)) - 1) << (i & 63);
-    atomicOr(&w.joins[i >> 6], m);
+    const int stop = word_stop(i, e);
+    atomicOr(&w.joins[i >> 6], word_mask(i, stop));
     i = stop;
   }
 }
