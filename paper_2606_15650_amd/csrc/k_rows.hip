@@ -222,15 +222,19 @@ constexpr int kMaxLabels = 64;
 // The head is laid out in LDS once per workgroup in the order in which lanes
 // read it (every read 1 KB without conflicts); the hidden state comes straight
 // from memory, kAheadX pairs of chunks in flight.  Bound by latency for a
-// small batch (137 tokens of 768: 32 -> 17 us; 32x32x2 MFMAs with each
-// chunk's loads waited for before) and by the MFMAs for a large one (162,000
-// tokens: 112 -> 108 us).
-constexpr int kClsWaves = 8;
+// small batch and by the MFMAs for a large one, for which two waves a SIMD are
+// too few: bf16 rows of 768, 17 labels, us per launch
+//   tokens                                            112  18,052  162,529  874,505
+//   32x32x2 MFMAs, each chunk's loads waited for     31.1    38.0    107.6      562
+//   8 waves a workgroup, 4 pairs in flight           15.3    31.4    109.6      600
+//   16 waves, 2 pairs                                13.7    27.2     90.6      517
+// (FP32 rows, 123,714 tokens: 145.6, 115.5, 110.0.)
+constexpr int kClsWaves = 16;
 template <typename TX, int H, int NB>
 __global__ __launch_bounds__(kClsWaves * 64) void classifier_mfma_kernel(
     const TX* __restrict__ x, const float* __restrict__ wc, const float* __restrict__ bc, int T_cap, int C,
     uint8_t* __restrict__ labels, float* __restrict__ logits, float* __restrict__ margin, const int* t_dev) {
-  constexpr int kPairs = H / 64, kAheadX = kPairs < 4 ? kPairs : 4;
+  constexpr int kPairs = H / 64, kAheadX = 2;
   static_assert(kPairs % kAheadX == 0, "the ring divides the chunks");
   __shared__ floatx4 head[kPairs * 2 * NB * 2 * 64];  // [chunk][n][half][lane] of 4 values
   const int tid = threadIdx.x, lane = tid & 63;

@@ -49,6 +49,26 @@ def test_classifier_blocks_and_tiles(C, hidden, precision):
         np.testing.assert_array_equal(mg, top[:, -1] - top[:, -2] if C > 1 else np.full(T, np.inf))
 
 
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+@pytest.mark.parametrize("T", [65536 - 16, 65536, 65536 + 1, 2 * 65536 + 17])
+def test_classifier_around_a_tile_per_wave(T, precision):
+    """256 workgroups of 16 waves hold 65,536 tokens at once; the waves go on
+    from there."""
+    from paper_2606_15650_amd.pipeline import Pipeline
+    cfg = ModelConfig(n_layers=1, hidden=256, n_heads=4, ffn=128, vocab=300, n_labels=17, max_pos=512)
+    W, m = make_model(cfg, precision, 0)
+    pl = Pipeline(m)
+    db = _batch(np.random.default_rng(T).integers(0, cfg.vocab, T).astype(np.int32),
+                [min(512, T - i) for i in range(0, T, 512)])
+    x = pl.hidden(db, 1)[:T].cpu().numpy().astype(np.float64)
+    lab, z, _ = (t[:T].cpu().numpy() for t in pl.ner(db, logits=True, margin=True))
+    say(f"[classifier] {precision}, {T} tokens")
+    wc, bc = W["wc"].T.astype(np.float64), W["bc"].astype(np.float64)
+    bound = (cfg.hidden + 1) * 2.0 ** -24 * (np.abs(x) @ np.abs(wc).T + np.abs(bc))
+    assert (np.abs(z - (x @ wc.T + bc)) <= bound).all()
+    np.testing.assert_array_equal(lab, z.argmax(1))
+
+
 @pytest.mark.parametrize("B", [1, 2, 63, 64, 65, 4095, 4096, 4097, 9000])
 def test_embedding_finds_records(B):
     from paper_2606_15650_amd.pipeline import Pipeline
