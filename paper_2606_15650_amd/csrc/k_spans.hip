@@ -15,8 +15,6 @@
 // and takes two launches where an int flag per token, a three-kernel scan of
 // them and a record search per labelled token took six.  978,000 tokens in
 // 4096 records: 38 -> 14 us (6 and 8 in the two kernels).
-#include <limits.h>
-
 #include "kernels.hpp"
 
 namespace anon {
@@ -215,15 +213,15 @@ __global__ __launch_bounds__(256) void bio_flags_kernel(const uint8_t* __restric
   const uint32_t l[4] = {lv.x, lv.y, lv.z, lv.w};
   int prev = t0 > 0 && t0 < T ? labels[t0 - 1] : 0;
   if (tid < kTile / 32) starts[tid] = 0;
-  // record boundaries inside the tile, from the last one at or before it
-  const int first = wg_find_record(cu, B, base);
-  for (int b = first;; b += 256) {
-    __syncthreads();
-    const int i = b + tid;
-    const int c = i <= B ? cu[i] : INT_MAX;
+  // record boundaries inside the tile
+  const int2 rr = wg_find_records(cu, B, base, min(last, T - 1));
+  const int first = rr.x;
+  __syncthreads();
+  wg_each_record(cu, first, max(rr.y, first), [&](int b) {
+    const int c = cu[b];
     if (c >= base && c <= last) atomicOr(&starts[(c - base) >> 5], 1u << ((c - base) & 31));
-    if (!__syncthreads_or(tid == 255 && i < B && c <= last)) break;
-  }
+  });
+  __syncthreads();
   const uint32_t rs = starts[tid >> 1] >> ((tid & 1) * 16);
   uint32_t f = 0;
 #pragma unroll
@@ -313,16 +311,20 @@ __global__ __launch_bounds__(256) void bio_write_kernel(const uint8_t* __restric
   // the tile's records lie between its first and the next tile's first
   const int r0 = rec0[blockIdx.x], r1 = (int)blockIdx.x + 1 < n_tiles ? rec0[blockIdx.x + 1] : B - 1;
   __syncthreads();
+  int a = r0, next = -1;  // the span's record and the first token past it
   for (; f; f &= f - 1, ++idx) {
     if (idx >= span_cap) break;
     const int t = t0 + __ffs(f) - 1;
-    int a = r0, c = r1;  // the record: largest index of [r0, r1] with cu <= t
-    while (a < c) {
-      const int m = (a + c + 1) >> 1;
-      if (cu[m] <= t) a = m;
-      else c = m - 1;
+    if (next <= t) {  // largest index of [a, r1] with cu <= t
+      int c = r1;
+      while (a < c) {
+        const int m = (a + c + 1) >> 1;
+        if (cu[m] <= t) a = m;
+        else c = m - 1;
+      }
+      next = cu[a + 1];
     }
-    const int end_tok = min(cu[a + 1], T);
+    const int end_tok = min(next, T);
     const int typ = (lab[t - base] + 1) >> 1, cont = 2 * typ;  // I-typ continues the span
     int e = t;
     while (e + 1 < end_tok && (e < last ? lab[e + 1 - base] : labels[e + 1]) == cont) ++e;

@@ -1,0 +1,94 @@
+"""Batches with very many empty records at one place: results as for the same
+batch without them, and no call is much slower than with as many empty records
+spread over it (a workgroup must not go through them one after the other)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from tests.gpu_common import say
+
+pytestmark = pytest.mark.gpu
+N_TYPES = 8
+EMPTY = 400_000
+
+
+def _us(fn):
+    """Best of five: GPU time of a call, in microseconds."""
+    import torch
+    fn()
+    best = 1e30
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(3):
+            fn()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 3 * 1e3)
+    return best
+
+
+def _lengths(full, where):
+    """`full` with EMPTY zeros: at one place, or spread over it."""
+    full = np.asarray(full, np.int64)
+    if where == "one place":
+        return np.concatenate([full[:len(full) // 2], np.zeros(EMPTY, np.int64), full[len(full) // 2:]])
+    out = np.zeros((len(full), EMPTY // len(full) + 1), np.int64)
+    out[:, 0] = full
+    return out.ravel()
+
+
+def _cu(lengths, dtype):
+    import torch
+    return torch.from_numpy(np.concatenate([[0], np.cumsum(lengths)]).astype(dtype)).cuda()
+
+
+def _unrecord(spans, cu_spans, lengths):
+    """Spans with the index of their record among those that are not empty."""
+    n = int(cu_spans[-1])
+    got = spans[:n].cpu().numpy()
+    rec = got[:, 0] & 0xFFFFFFFF
+    per = np.searchsorted(cu_spans.cpu().numpy(), np.arange(n), side="right") - 1
+    np.testing.assert_array_equal(rec, per)  # (record r's spans are cu_spans[r] .. cu_spans[r + 1])
+    index = np.cumsum(lengths > 0) - 1
+    got[:, 0] += index[rec] - rec
+    return got
+
+
+def _compare(call, full):
+    """call(lengths) -> (function, spans, cu_spans)"""
+    out, us = {}, {}
+    for where in ("none", "spread", "one place"):
+        lengths = np.asarray(full, np.int64) if where == "none" else _lengths(full, where)
+        fn, spans, cu_spans = call(lengths)
+        us[where] = _us(fn)
+        out[where] = _unrecord(spans, cu_spans, lengths)
+        say(f"[empty records] {where}: {len(lengths)} records, {len(out[where])} spans, {us[where]:.1f} us")
+    assert len(out["none"]) > 0
+    np.testing.assert_array_equal(out["spread"], out["none"])
+    np.testing.assert_array_equal(out["one place"], out["none"])
+    from paper_2606_15650_amd import api
+    assert api.device_errors() == 0
+    assert us["one place"] < 3 * us["spread"] + 50
+
+
+def test_decode_spans():
+    import torch
+    from paper_2606_15650_amd import api
+    full = [200] * 2000
+    T = sum(full)
+    rng = np.random.default_rng(1)
+    lab = rng.integers(1, 2 * N_TYPES + 1, T).astype(np.uint8)
+    lab[rng.random(T) < 0.7] = 0
+    off = np.stack([np.arange(T) % 200 * 3, np.arange(T) % 200 * 3 + 2], 1).astype(np.int32)
+    d_lab, d_off = torch.from_numpy(lab).cuda(), torch.from_numpy(off).cuda()
+
+    def call(lengths):
+        B = len(lengths)
+        cu, spans = _cu(lengths, np.int32), torch.empty((T, 3), dtype=torch.int64, device="cuda")
+        cu_spans = torch.empty(B + 1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(api.decode_workspace_size(T, B), dtype=torch.uint8, device="cuda")
+        return (lambda: api.decode_spans(d_lab, d_off, cu, B, T, N_TYPES, spans, T, cu_spans, ws, ws.numel()), spans,
+                cu_spans)
+    _compare(call, full)
