@@ -525,11 +525,11 @@ __global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict
       push(L_OTHER, (tid * 16) | (K_HEX << 12));
   }
   // record starts: a hash there may follow the last record's hex digits
-  for (int64_t r = r0 + tid; r <= r1; r += 256) {
+  wg_each_record(cu, r0, r1, [&](int r) {
     const int64_t x = cu[r];
     if (x >= p0 && x < min(p0 + kTile, n) && cu[r + 1] > x && is_hex(win[kBefore + (x - p0)]))
       push(L_OTHER, (int)(x - p0) | (K_REC << 12));
-  }
+  });
   __syncthreads();
 
   auto record = [&](int a) {  // of the anchor at byte a
@@ -713,15 +713,8 @@ __global__ __launch_bounds__(256) void rx_emit_kernel(const int64_t* __restrict_
   if (tile >= n_tiles || i >= words) return;
   unsigned long long u = w.begins[i];
   int k = w.word_rank[i], b = w.rec0[tile];
-  if (u) {  // the record of the word's first begin, from there on one by one
-    const int p = (int)(i * 64) + __ffsll(u) - 1;
-    int top = tile + 1 < n_tiles ? w.rec0[tile + 1] : B - 1;
-    while (b < top) {
-      const int m = (b + top + 1) >> 1;
-      if (cu[m] <= p) b = m;
-      else top = m - 1;
-    }
-  }
+  const int last = tile + 1 < n_tiles ? w.rec0[tile + 1] : B - 1;
+  int64_t next = -1;  // the first byte past record b
   for (; u; u &= u - 1, ++k) {
     const int idx = w.tile_pre[tile] + k;
     if (idx >= cap) return;
@@ -731,7 +724,15 @@ __global__ __launch_bounds__(256) void rx_emit_kernel(const int64_t* __restrict_
     unsigned long long open = ~w.joins[j] & (~0ull << ((p + 1) & 63));
     while (open == 0) open = ~w.joins[++j];
     const int e = (int)(j * 64) + __ffsll(open) - 1;
-    while (b + 1 < B && cu[b + 1] <= p) ++b;
+    if (next <= p) {  // largest index of [b, last] with cu <= p
+      int top = last;
+      while (b < top) {
+        const int m = (b + top + 1) >> 1;
+        if (cu[m] <= p) b = m;
+        else top = m - 1;
+      }
+      next = cu[b + 1];
+    }
     out[idx] = anon_span{b, (int)(w.keys[(size_t)tile * kTile + k] & 0xff), p - cu[b], e - cu[b]};
   }
 }

@@ -92,3 +92,44 @@ def test_decode_spans():
         return (lambda: api.decode_spans(d_lab, d_off, cu, B, T, N_TYPES, spans, T, cu_spans, ws, ws.numel()), spans,
                 cu_spans)
     _compare(call, full)
+
+
+def _batch(text, lengths):
+    """What Pipeline reads of a batch that has a text only."""
+    import torch
+
+    class Batch:
+        B, n_bytes = len(lengths), len(text)
+    Batch.text = torch.from_numpy(np.frombuffer(text, np.uint8).copy()).cuda()
+    Batch.cu_bytes = _cu(lengths, np.int64)
+    return Batch
+
+
+def _pipeline(names):
+    import torch
+    from paper_2606_15650_amd.pipeline import Pipeline
+    from tests.gpu_common import make_cache
+    pl = Pipeline.__new__(Pipeline)
+    pl.cache, pl.device, pl._ws, pl.n_types = make_cache(names), torch.device("cuda:0"), {}, len(names)
+    return pl
+
+
+def test_recognize_spans():
+    pl = _pipeline(["IP_ADDRESS", "HOSTNAME", "EMAIL_ADDRESS", "URL", "HASH"])
+    records = [b"host.lan 10.0.0.1 x@y.org " + b"0123456789abcdef" * 2 + b" http://a.lan/" + b"p" * (i % 90)
+               for i in range(1998)]
+    # around the place, in one 64-byte word: an address, then a hash that only the record's start lets begin
+    at = sum(map(len, records[:999]))
+    records[999:999] = [b" " * (64 - at % 64 + 20) + b"10.0.0.1", b"0123456789abcdef" * 2]
+    text, full = b"".join(records), [len(r) for r in records]
+
+    def call(lengths):
+        db = _batch(text, lengths)
+        spans, cu_spans, _ = pl.recognize(db)
+
+        def fn():
+            s, c, _ = pl.recognize(db)
+            spans[:] = s
+            cu_spans[:] = c
+        return fn, spans, cu_spans
+    _compare(call, full)
