@@ -158,6 +158,19 @@ __device__ __forceinline__ void wg_each_record(const T* cu, int r0, int r1, F f)
   }
 }
 
+// The same for the records from r0 on that begin at or before p, r0 the record
+// of a byte or token; most often they are few, and no second search is made.
+// Ends with a barrier.
+template <typename T, typename F>
+__device__ __forceinline__ void wg_each_record_to(const T* cu, int B, int r0, T p, F f) {
+  const int b = r0 + (int)threadIdx.x;
+  const bool in = b < B && cu[b] <= p;
+  if (in) f(b);
+  if (!__syncthreads_or(in && threadIdx.x == blockDim.x - 1)) return;
+  wg_each_record(cu, r0 + (int)blockDim.x, wg_find_record(cu, B, p), f);
+  __syncthreads();
+}
+
 // The bytes' bit 7 gathered into four bits (a multiplication).
 __device__ __forceinline__ uint32_t byte_bits(uint32_t flags) { return (flags >> 7) * 0x10204080u >> 28; }
 // Bit 7 of each byte of w: the byte equals c / lies in [lo, hi], lo >= 1, hi <= 127.

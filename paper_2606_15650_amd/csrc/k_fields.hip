@@ -56,7 +56,7 @@ __device__ __forceinline__ int next_bit(const uint64_t* x, const uint64_t* y, in
 
 __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict__ text,
                                                        const int64_t* __restrict__ cu, int B, int64_t n,
-                                                       FieldTable ft, FieldBuffers out, uint32_t* err) {
+                                                       FieldTable ft, FieldBuffers out) {
   __shared__ __align__(16) uint8_t win[kWin + 48];  // (names are read as 36 bytes)
   __shared__ __align__(16) uint64_t nl[kWinWords], colon[kWinWords], rec[kWinWords];
   __shared__ uint16_t lines[kTile];
@@ -99,17 +99,11 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
   if (tid < kAfter / 16) stage(kTile / 16 + tid, v2);
   const bool after_break = before == '\n';
   __syncthreads();
-  // record starts of the window (and the check of cu_bytes' tile part)
-  for (int b = r0;; b += 256) {
-    const int i = b + tid;
-    const int64_t c = i <= B ? cu[i] : INT64_MAX;
-    if (i < B && c >= p0 && c < p0 + whi) atomicOr((uint32_t*)rec + ((c - p0) >> 5), 1u << ((c - p0) & 31));
-    if (!__syncthreads_or(tid == 255 && i < B && c < p0 + whi)) break;
-  }
-  for (int64_t b = (int64_t)blockIdx.x * 256 + tid; b <= B; b += (int64_t)gridDim.x * 256) {
-    const int64_t x = cu[b];
-    if ((b == 0 && x != 0) || (b == B && x != n) || (b < B && cu[b + 1] < x)) raise_error(err, ANON_ERR_TEXT);
-  }
+  // record starts of the window
+  wg_each_record_to(cu, B, r0, p0 + whi - 1, [&](int b) {
+    const int64_t c = cu[b];
+    if (c >= p0 && c < p0 + whi) atomicOr((uint32_t*)rec + ((c - p0) >> 5), 1u << ((c - p0) & 31));
+  });
   uint32_t starts = (my_nl << 1) | (after_break ? 1u : 0u) | ((const uint32_t*)rec)[tid];
   if (mine == 0) starts |= 1;  // the text's first byte
   starts &= ~my_nl;            // (an empty line)
@@ -208,7 +202,8 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
 }
 
 // A wave per tile writes its spans (pre: exclusive prefix of the tiles'
-// counts); the blocks above write cu_spans[b] = fields before record b.
+// counts); the blocks above check cu_bytes and write cu_spans[b] = fields
+// before record b.
 __global__ __launch_bounds__(256) void fd_emit_kernel(const int64_t* __restrict__ cu, int B, int64_t n, int n_tiles,
                                                       int tile_blocks, FieldBuffers w, anon_span* out, int cap,
                                                       int* cu_spans, uint32_t* err) {
@@ -216,7 +211,8 @@ __global__ __launch_bounds__(256) void fd_emit_kernel(const int64_t* __restrict_
   if ((int)blockIdx.x >= tile_blocks) {
     const int b = (blockIdx.x - tile_blocks) * 256 + tid;
     if (b > B) return;
-    const int64_t x = min(max(cu[b], (int64_t)0), n);
+    const int64_t c = cu[b], x = min(max(c, (int64_t)0), n);
+    if ((b == 0 && c != 0) || (b == B && c != n) || (b < B && cu[b + 1] < c)) raise_error(err, ANON_ERR_TEXT);
     const int total = w.counts[n_tiles], tile = (int)(x / kTile);
     int k = total;
     if (x < n) {
@@ -261,24 +257,18 @@ size_t field_workspace_bytes(int64_t n) {
   return k.used + 256;
 }
 
-// An empty text has no tile: its record boundaries are checked here.
-__global__ __launch_bounds__(256) void fd_empty_kernel(const int64_t* __restrict__ cu, int B, int* counts,
-                                                       uint32_t* err) {
-  for (int b = blockIdx.x * 256 + threadIdx.x; b <= B; b += gridDim.x * 256)
-    if (cu[b] != 0) raise_error(err, ANON_ERR_TEXT);
-  if (blockIdx.x == 0 && threadIdx.x == 0) counts[0] = 0;
-}
+// An empty text has no tile.
+__global__ void fd_empty_kernel(int* counts) { counts[0] = 0; }
 
 void launch_field_spans(const uint8_t* text, const int64_t* cu_bytes, int B, int64_t n, const FieldTable& ft,
                         const FieldBuffers& w, anon_span* out, int cap, int* cu_spans, uint32_t* err,
                         hipStream_t s) {
   const int tiles = (int)((n + kTile - 1) / kTile), tile_blocks = ceil_div(tiles, 4);
   if (tiles > 0) {
-    hipLaunchKernelGGL(fd_match_kernel, dim3(tiles), dim3(256), 0, s, text, cu_bytes, B, n, ft, w, err);
+    hipLaunchKernelGGL(fd_match_kernel, dim3(tiles), dim3(256), 0, s, text, cu_bytes, B, n, ft, w);
     launch_scan_counts(w.counts, tiles, s);
   } else {
-    hipLaunchKernelGGL(fd_empty_kernel, dim3(std::min(ceil_div(B + 1, 256), 1024)), dim3(256), 0, s, cu_bytes, B,
-                       w.counts, err);
+    hipLaunchKernelGGL(fd_empty_kernel, dim3(1), dim3(1), 0, s, w.counts);
   }
   hipLaunchKernelGGL(fd_emit_kernel, dim3(tile_blocks + ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, tiles,
                      tile_blocks, w, out, cap, cu_spans, err);

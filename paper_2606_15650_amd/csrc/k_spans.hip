@@ -214,14 +214,12 @@ __global__ __launch_bounds__(256) void bio_flags_kernel(const uint8_t* __restric
   int prev = t0 > 0 && t0 < T ? labels[t0 - 1] : 0;
   if (tid < kTile / 32) starts[tid] = 0;
   // record boundaries inside the tile
-  const int2 rr = wg_find_records(cu, B, base, min(last, T - 1));
-  const int first = rr.x;
+  const int first = wg_find_record(cu, B, base);
   __syncthreads();
-  wg_each_record(cu, first, max(rr.y, first), [&](int b) {
+  wg_each_record_to(cu, B, first, min(last, T - 1), [&](int b) {
     const int c = cu[b];
     if (c >= base && c <= last) atomicOr(&starts[(c - base) >> 5], 1u << ((c - base) & 31));
   });
-  __syncthreads();
   const uint32_t rs = starts[tid >> 1] >> ((tid & 1) * 16);
   uint32_t f = 0;
 #pragma unroll

@@ -133,3 +133,21 @@ def test_recognize_spans():
             cu_spans[:] = c
         return fn, spans, cu_spans
     _compare(call, full)
+
+
+def test_field_spans():
+    pl = _pipeline(["IP_ADDRESS", "HOSTNAME"])
+    records = [b"Source IP: 10.0.0.%d\nHost: a%d.lan\nNote: %s\n" % (i % 256, i, b"x" * (i % 70)) for i in range(8000)]
+    text, full = b"".join(records), [len(r) for r in records]
+
+    def call(lengths):
+        db = _batch(text, lengths)
+        config = {"Source IP": 1, "Host": 2}
+        spans, cu_spans, _ = pl.fields(db, config)
+
+        def fn():
+            s, c, _ = pl.fields(db, config)
+            spans[:] = s
+            cu_spans[:] = c
+        return fn, spans, cu_spans
+    _compare(call, full)
