@@ -450,7 +450,16 @@ __global__ __launch_bounds__(256) void window_merge_kernel(const int* __restrict
   // the record of the wave's first token, then on from there
   int b = wave_find_record(cu, B, min(t0 + (tid & ~63), T - 1), tid & 63);
   if (t < T) {
-    while (b + 1 < B && cu[b + 1] <= t) ++b;
+    if (b + 1 < B && cu[b + 1] <= t) {  // largest index of [b + 1, B) with cu <= t
+      int top = B - 1;
+      ++b;
+      if (b < top && cu[b + 1] > t) top = b;  // (most often the next record)
+      while (b < top) {
+        const int m = (b + top + 1) >> 1;
+        if (cu[m] <= t) b = m;
+        else top = m - 1;
+      }
+    }
     const int i = t - cu[b];
     const int nw = rec_win0[b + 1] - rec_win0[b];
     const int half = (window - stride) / 2;

@@ -151,3 +151,31 @@ def test_field_spans():
             cu_spans[:] = c
         return fn, spans, cu_spans
     _compare(call, full)
+
+
+def test_windowed_forward():
+    """The window merge (the records' windows are listed on the host): a short
+    record before the place and one after it in one wave of tokens."""
+    import torch
+    from paper_2606_15650_amd import api
+    from synth.configs import TINY
+    from tests.gpu_common import make_model
+    _, m = make_model(TINY, "bf16", 0)
+    full = [700] * 20 + [5, 7] + [700] * 20
+    T = sum(full)
+    ids = torch.from_numpy(np.random.default_rng(2).integers(0, TINY.vocab, T).astype(np.int32)).cuda()
+    out, us = {}, {}
+    for where in ("none", "spread", "one place"):
+        lengths = np.asarray(full, np.int64) if where == "none" else _lengths(full, where)
+        B, h_cu = len(lengths), np.concatenate([[0], np.cumsum(lengths)]).astype(np.int32)
+        cu, labels = torch.from_numpy(h_cu).cuda(), torch.empty(T, dtype=torch.uint8, device="cuda")
+        z = torch.empty((T, TINY.n_labels), dtype=torch.float32, device="cuda")
+        ws = torch.empty(m.windowed_workspace_size(h_cu, 512, 256), dtype=torch.uint8, device="cuda")
+        us[where] = _us(lambda: api.ner_forward_windowed(m, ids, cu, h_cu, B, T, 512, 256, labels, z, None, ws,
+                                                         ws.numel(), None))
+        out[where] = labels.cpu().numpy(), z.cpu().numpy()
+        say(f"[empty records] {where}: {B} records, windowed {us[where]:.1f} us")
+    for where in ("spread", "one place"):
+        np.testing.assert_array_equal(out[where][0], out["none"][0])
+        np.testing.assert_array_equal(out[where][1], out["none"][1])
+    assert us["one place"] < 3 * us["spread"] + 50
