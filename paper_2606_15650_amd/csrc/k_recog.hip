@@ -619,29 +619,48 @@ __global__ __launch_bounds__(256) void rx_count_kernel(RecogBuffers w, int n_til
   for (int k = lane; k < total; k += 64) w.keys[(size_t)tile * kTile + k] = 0;
 }
 
-// The key slot of the union that holds byte p: its rank within the tile where
-// it begins, which is p's tile or, for a long union, one before it.
-__device__ __forceinline__ size_t union_slot(const RecogBuffers& w, int p) {
-  int tile = p / kTile;
+// The unions of p's tile that begin at or before byte p: the rank, counted from
+// 1, of the union that holds p; 0 if it began in an earlier tile.
+__device__ __forceinline__ int union_rank(const RecogBuffers& w, int p) {
   const unsigned long long u = w.begins[p >> 6] & (~0ull >> (63 - (p & 63)));
-  int k = w.word_rank[p >> 6] + __popcll(u);
+  return w.word_rank[p >> 6] + __popcll(u);
+}
+
+// The key slot of the union that holds byte p.
+__device__ __forceinline__ size_t union_slot(const RecogBuffers& w, int p) {
+  int tile = p / kTile, k = union_rank(w, p);
   while (k == 0 && tile > 0) k = w.tile_count[--tile];
   return (size_t)tile * kTile + max(k - 1, 0);
 }
 
-constexpr int kEntryTiles = 64;  // tiles per member workgroup
+// The last tile before `tile` where a union begins, -1 if there is none, by a
+// whole wave, 64 tiles a step.
+__device__ __forceinline__ int last_begin_tile(const RecogBuffers& w, int tile, int lane) {
+  for (int top = tile; top > 0; top -= 64) {
+    const int t = top - 1 - lane;
+    const uint64_t some = __ballot(t >= 0 && w.tile_count[max(t, 0)] > 0);
+    if (some) return top - __ffsll((unsigned long long)some);
+  }
+  return -1;
+}
 
 // Block 0: the prefix of the tiles' union counts.  The next blocks: every
-// match's key into its union, 64 tiles to a workgroup.  The rest: the NER
-// spans' keys.
+// match's key into its union, a wave per tile.  The rest: the NER spans' keys.
+// A tile's matches before its first union's begin are in one union, which
+// began in an earlier tile: that tile is looked for once, and one atomic takes
+// their largest key.  (64 tiles to a workgroup left most CUs idle on dense
+// text: 1.2 MB of IPv6 addresses of three bytes 228 us, of IPv4 addresses 112.)
 __global__ __launch_bounds__(256) void rx_members_kernel(const int64_t* __restrict__ cu, int B, int64_t n, int n_tiles,
                                                          int entry_blocks, const anon_span* __restrict__ ner,
                                                          const int* __restrict__ ner_cu, int ner_cap, int n_types,
                                                          RecogBuffers w) {
-  __shared__ int pre[257];
-  const int tid = threadIdx.x;
-  auto scan = [&](int v) {  // inclusive scan of one value per thread into pre[1..256]
-    pre[tid + 1] = v;
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (blockIdx.x == 0) {
+    __shared__ int pre[257];
+    const int per = (n_tiles + 255) / 256, a = min(n_tiles, tid * per), b = min(n_tiles, a + per);
+    int s = 0;
+    for (int i = a; i < b; ++i) s += w.tile_count[i];
+    pre[tid + 1] = s;
     if (tid == 0) pre[0] = 0;
     __syncthreads();
     for (int o = 1; o < 256; o <<= 1) {
@@ -650,12 +669,6 @@ __global__ __launch_bounds__(256) void rx_members_kernel(const int64_t* __restri
       pre[tid + 1] += x;
       __syncthreads();
     }
-  };
-  if (blockIdx.x == 0) {
-    const int per = (n_tiles + 255) / 256, a = min(n_tiles, tid * per), b = min(n_tiles, a + per);
-    int s = 0;
-    for (int i = a; i < b; ++i) s += w.tile_count[i];
-    scan(s);
     int run = pre[tid];
     for (int i = a; i < b; ++i) {
       w.tile_pre[i] = run;
@@ -665,18 +678,20 @@ __global__ __launch_bounds__(256) void rx_members_kernel(const int64_t* __restri
     return;
   }
   if ((int)blockIdx.x <= entry_blocks) {
-    const int t0 = (blockIdx.x - 1) * kEntryTiles;
-    scan(tid < kEntryTiles && t0 + tid < n_tiles ? w.n_entries[t0 + tid] : 0);
-    const int total = pre[256];
-    for (int i = tid; i < total; i += 256) {
-      int a = 0, b = kEntryTiles - 1;  // last tile with pre <= i
-      while (a < b) {
-        const int m = (a + b + 1) >> 1;
-        if (pre[m] <= i) a = m;
-        else b = m - 1;
-      }
-      const RecogEntry e = w.entries[(size_t)(t0 + a) * kTileEntries + (i - pre[a])];
-      atomicMax(&w.keys[union_slot(w, e.p)], e.key);
+    const int tile = (blockIdx.x - 1) * 4 + (tid >> 6);
+    if (tile >= n_tiles) return;
+    const int total = w.n_entries[tile];
+    unsigned long long earlier = 0;  // of the union that began before the tile
+    for (int i = lane; i < total; i += 64) {
+      const RecogEntry e = w.entries[(size_t)tile * kTileEntries + i];
+      if (e.p / kTile == tile && union_rank(w, e.p) == 0) earlier = max(earlier, e.key);
+      else atomicMax(&w.keys[union_slot(w, e.p)], e.key);  // (a match may begin before its anchor's tile)
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) earlier = max(earlier, (unsigned long long)__shfl_xor(earlier, o, 64));
+    if (earlier) {
+      const int t = last_begin_tile(w, tile, lane);
+      if (lane == 0 && t >= 0) atomicMax(&w.keys[(size_t)t * kTile + w.tile_count[t] - 1], earlier);
     }
     return;
   }
@@ -685,8 +700,8 @@ __global__ __launch_bounds__(256) void rx_members_kernel(const int64_t* __restri
   for (int64_t i = (int64_t)(blockIdx.x - first) * 256 + tid; i < total; i += (int64_t)(gridDim.x - first) * 256) {
     const anon_span s = ner[i];
     int b, e;
-    if (ner_span(s, cu, B, n, n_types, b, e, nullptr))
-      atomicMax(&w.keys[union_slot(w, b)], span_key(e - b, 0, (int)s.begin, s.type));
+    if (!ner_span(s, cu, B, n, n_types, b, e, nullptr)) continue;
+    atomicMax(&w.keys[union_slot(w, b)], span_key(e - b, 0, (int)s.begin, s.type));
   }
 }
 
@@ -775,7 +790,7 @@ void launch_recognize(const uint8_t* text, const int64_t* cu_bytes, int B, int64
   // the NER spans' count is on the device: enough blocks for it in a few
   // rounds, and none that idles in its thousands when the capacity is large
   const int ner_blocks = have_ner ? std::min(ceil_div(ner_cap, 256), 1024) : 0;
-  const int entry_blocks = ceil_div(tiles, kEntryTiles), tile_blocks = ceil_div(tiles, 4);
+  const int tile_blocks = ceil_div(tiles, 4);
   hipLaunchKernelGGL(rx_init_kernel, dim3(std::max(1, std::min(ceil_div(std::max<int64_t>(2 * words, B + 1), 256), 2048))),
                      dim3(256), 0, s, w.begins, 2 * words, cu_bytes, B, n, err);
   if (tiles + ner_blocks > 0)
@@ -783,8 +798,8 @@ void launch_recognize(const uint8_t* text, const int64_t* cu_bytes, int B, int64
                        ner, ner_cu, ner_cap, n_types, w, err);
   if (tiles > 0)
     hipLaunchKernelGGL(rx_count_kernel, dim3(tile_blocks), dim3(256), 0, s, w, tiles, words);
-  hipLaunchKernelGGL(rx_members_kernel, dim3(1 + entry_blocks + (tiles > 0 ? ner_blocks : 0)), dim3(256), 0, s,
-                     cu_bytes, B, n, tiles, entry_blocks, ner, ner_cu, ner_cap, n_types, w);
+  hipLaunchKernelGGL(rx_members_kernel, dim3(1 + tile_blocks + (tiles > 0 ? ner_blocks : 0)), dim3(256), 0, s,
+                     cu_bytes, B, n, tiles, tile_blocks, ner, ner_cu, ner_cap, n_types, w);
   hipLaunchKernelGGL(rx_emit_kernel, dim3(tile_blocks + ceil_div(B + 1, 256)), dim3(256), 0, s, cu_bytes, B, n, tiles,
                      tile_blocks, w, words, out, cap, cu_spans, err);
 }
