@@ -51,3 +51,29 @@ def test_dense_matches(word):
     dense, plain = _us(call), _us(none)
     say(f"[recognize] {word}: {len(got)} spans, {dense:.1f} us, without matches {plain:.1f} us")
     assert dense < 5.5 * plain
+
+
+@pytest.mark.parametrize("size", [1023, 1025, 4096, 20000, 300000])
+def test_long_ner_spans(size):
+    """NER spans around the length from which a wave marks them and over many
+    tiles, with matches inside, at every offset in a 64-byte word."""
+    words = [b"alpha ", b"10.0.0.1 ", b"host.lan ", b"x@y.org ", b"z" * 61 + b" "]
+    rng = np.random.default_rng(size)
+    body = b"".join(words[k] for k in rng.integers(0, len(words), size // 5))
+    shifts = range(0, 66, 5) if size < 10000 else (0, 1, 64)
+    records = [b"-" * (i % 7) + body[:size + 40] + b" 10.0.0.9 " + b"q" * (64 - i) for i in shifts]
+    ner = [(r, 1 + r % 2, 3 + i // 2, 3 + i // 2 + size - r) for r, i in enumerate(shifts)]
+    got, call = _run(records, ner)
+    _check(got, records, ner)
+    bare, none = _run(records)
+    say(f"[recognize] NER spans of {size}: {len(got)} spans, {_us(call):.1f} us; without {len(bare)}, {_us(none):.1f} us")
+
+
+def test_one_span_over_eight_megabytes():
+    records = [b"alpha 10.0.0.1 beta x@y.org gamma host.lan " * 190000]
+    size = len(records[0])
+    got, call = _run(records, [(0, 2, 1, size - 1)])
+    np.testing.assert_array_equal(got, [[0, 2, 1, size - 1]])
+    one, none = _us(call), _us(_run(records)[1])
+    say(f"[recognize] one NER span of {size} bytes {one:.1f} us, without it {none:.1f} us")
+    assert one < 40 * none
