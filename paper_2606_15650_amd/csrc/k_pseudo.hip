@@ -252,90 +252,117 @@ __device__ __forceinline__ bool same_bytes(const Entry* e, const uint32_t (&m)[k
   return diff == 0;
 }
 
-// A wave per record: each span's output offset within the record, its
-// pseudonym's length and where the text goes on after it.  A span is valid
-// if it lies in the record and begins at or after the end of the last valid,
-// not preserved one.  64 spans at a time are laid out as if all were valid
-// (prefix sums); only if one turns out not to be does lane 0 go through them
-// one by one.  16,384 records of 7.8 KB: 46 -> 11 us against a thread per
-// record, whose reads of neighbouring records' spans shared no cache line.
+// Each span's output offset within its record, its pseudonym's length and
+// where the text goes on after it.  A span is valid if it lies in the record
+// and begins at or after the end of the last valid, not preserved one.
+//
+// A wave takes `per` records, one for up to 16,384 of them.  64 spans of a
+// record at a time are laid out as if all were valid (prefix sums); only if one
+// turns out not to be does lane 0 go through them one by one.  16,384 records
+// of 7.8 KB: 46 -> 11 us against a thread per record, whose reads of
+// neighbouring records' spans shared no cache line.  Of more records most have
+// few spans, and a wave for each would wait for its reads alone (a million
+// empty ones: 144 us against 5.5 of a thread each): a lane reads a record's
+// bounds, and lays out up to kFewSpans by itself.
+constexpr int kFewSpans = 8;
 __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int64_t* __restrict__ cu_bytes, int B,
-                                                        const anon_span* __restrict__ spans,
+                                                        int per, const anon_span* __restrict__ spans,
                                                         const int* __restrict__ cu_spans, int span_cap,
                                                         int64_t* __restrict__ out_len, int64_t* __restrict__ sp_out,
                                                         int* __restrict__ sp_plen, int64_t* __restrict__ sp_in_end,
                                                         uint32_t* err) {
-  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (b >= B) return;
-  int64_t in_len = cu_bytes[b + 1] - cu_bytes[b];
-  if (in_len < 0) {
-    raise_error(err, ANON_ERR_SPAN);
-    in_len = 0;
-  }
-  int s0 = cu_spans[b], s1 = cu_spans[b + 1];
-  if (s1 > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
-  s0 = min(max(s0, 0), span_cap);
-  s1 = min(max(s1, s0), span_cap);
-  int64_t acc = 0, prev_end = 0;
+  const int lane = threadIdx.x & 63;
+  const int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per;
   const int tail = pc.slug > 0 ? pc.slug + 1 : 0;
-  for (int c0 = s0; c0 < s1; c0 += 64) {
-    const int s = c0 + lane;
-    const bool in = s < s1;
-    anon_span sp{b, 0, 0, 0};
-    if (in) sp = spans[s];
-    const bool typed = sp.type >= 1 && sp.type <= pc.n_types;
-    const bool keep = in && typed && preserved(pc, sp.type);
-    const int plen = in && typed && !keep ? 2 + (pc.name_off[sp.type] - pc.name_off[sp.type - 1]) + tail : 0;
-    // ends of the replaced spans up to and before this lane's, the growth likewise
-    int64_t e = plen > 0 ? sp.end : 0, d = plen > 0 ? plen - (sp.end - sp.begin) : 0;
-    const int64_t own = d;
+  // spans [i0, i1) of record b in their order, after acc bytes of growth and a
+  // replaced span's end at prev_end
+  auto one_by_one = [&](int b, int64_t in_len, int i0, int i1, int64_t& acc, int64_t& prev_end) {
+    for (int i = i0; i < i1; ++i) {
+      const anon_span q = spans[i];
+      const bool valid = q.record == b && q.type >= 1 && q.type <= pc.n_types && q.begin >= prev_end &&
+                         q.end >= q.begin && q.end <= in_len;
+      if (valid && !preserved(pc, q.type)) {
+        const int n = 2 + (pc.name_off[q.type] - pc.name_off[q.type - 1]) + tail;
+        sp_out[i] = q.begin + acc;
+        sp_plen[i] = n;
+        sp_in_end[i] = q.end;
+        acc += n - (q.end - q.begin);
+        prev_end = q.end;
+      } else {
+        if (!valid) raise_error(err, ANON_ERR_SPAN);
+        sp_out[i] = prev_end + acc;
+        sp_plen[i] = 0;
+        sp_in_end[i] = prev_end;
+      }
+    }
+  };
+  // this lane's record
+  const bool mine = lane < per && first + lane < B;
+  int64_t my_len = 0;
+  int my_s0 = 0, my_s1 = 0;
+  if (mine) {
+    const int64_t b = first + lane;
+    my_len = cu_bytes[b + 1] - cu_bytes[b];
+    if (my_len < 0) {
+      raise_error(err, ANON_ERR_SPAN);
+      my_len = 0;
+    }
+    my_s0 = cu_spans[b], my_s1 = cu_spans[b + 1];
+    if (my_s1 > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
+    my_s0 = min(max(my_s0, 0), span_cap);
+    my_s1 = min(max(my_s1, my_s0), span_cap);
+  }
+  const bool few = per > 1 && my_s1 - my_s0 <= kFewSpans;
+  if (mine && few) {
+    int64_t acc = 0, prev_end = 0;
+    one_by_one((int)first + lane, my_len, my_s0, my_s1, acc, prev_end);
+    out_len[first + lane] = my_len + acc;
+  }
+  for (uint64_t todo = __ballot(mine && !few); todo; todo &= todo - 1) {
+    const int of = __ffsll((unsigned long long)todo) - 1, b = (int)first + of;
+    const int64_t in_len = __shfl(my_len, of, 64);
+    const int s0 = __shfl(my_s0, of, 64), s1 = __shfl(my_s1, of, 64);
+    int64_t acc = 0, prev_end = 0;
+    for (int c0 = s0; c0 < s1; c0 += 64) {
+      const int s = c0 + lane;
+      const bool in = s < s1;
+      anon_span sp{b, 0, 0, 0};
+      if (in) sp = spans[s];
+      const bool typed = sp.type >= 1 && sp.type <= pc.n_types;
+      const bool keep = in && typed && preserved(pc, sp.type);
+      const int plen = in && typed && !keep ? 2 + (pc.name_off[sp.type] - pc.name_off[sp.type - 1]) + tail : 0;
+      // ends of the replaced spans up to and before this lane's, the growth likewise
+      int64_t e = plen > 0 ? sp.end : 0, d = plen > 0 ? plen - (sp.end - sp.begin) : 0;
+      const int64_t own = d;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int64_t y = __shfl_up(e, o, 64), z = __shfl_up(d, o, 64);
-      if (lane >= o) {
-        e = max(e, y);
-        d += z;
-      }
-    }
-    int64_t before = __shfl_up(e, 1, 64);
-    before = lane > 0 ? max(before, prev_end) : prev_end;
-    const bool ok = !in || (sp.record == b && typed && sp.begin >= before && sp.end >= sp.begin && sp.end <= in_len);
-    if (__all(ok)) {
-      const int64_t a = acc + d - own;
-      if (in) {
-        // a preserved type: the span's bytes are copied like the text around it
-        sp_out[s] = (plen > 0 ? sp.begin : before) + a;
-        sp_plen[s] = plen;
-        sp_in_end[s] = plen > 0 ? sp.end : before;
-      }
-      acc += __shfl(d, 63, 64);
-      prev_end = max(prev_end, __shfl(e, 63, 64));
-      continue;
-    }
-    if (lane == 0) {
-      for (int i = c0; i < min(c0 + 64, s1); ++i) {
-        const anon_span q = spans[i];
-        const bool valid = q.record == b && q.type >= 1 && q.type <= pc.n_types && q.begin >= prev_end &&
-                           q.end >= q.begin && q.end <= in_len;
-        if (valid && !preserved(pc, q.type)) {
-          const int n = 2 + (pc.name_off[q.type] - pc.name_off[q.type - 1]) + tail;
-          sp_out[i] = q.begin + acc;
-          sp_plen[i] = n;
-          sp_in_end[i] = q.end;
-          acc += n - (q.end - q.begin);
-          prev_end = q.end;
-        } else {
-          if (!valid) raise_error(err, ANON_ERR_SPAN);
-          sp_out[i] = prev_end + acc;
-          sp_plen[i] = 0;
-          sp_in_end[i] = prev_end;
+      for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up(e, o, 64), z = __shfl_up(d, o, 64);
+        if (lane >= o) {
+          e = max(e, y);
+          d += z;
         }
       }
+      int64_t before = __shfl_up(e, 1, 64);
+      before = lane > 0 ? max(before, prev_end) : prev_end;
+      const bool ok = !in || (sp.record == b && typed && sp.begin >= before && sp.end >= sp.begin && sp.end <= in_len);
+      if (__all(ok)) {
+        const int64_t a = acc + d - own;
+        if (in) {
+          // a preserved type: the span's bytes are copied like the text around it
+          sp_out[s] = (plen > 0 ? sp.begin : before) + a;
+          sp_plen[s] = plen;
+          sp_in_end[s] = plen > 0 ? sp.end : before;
+        }
+        acc += __shfl(d, 63, 64);
+        prev_end = max(prev_end, __shfl(e, 63, 64));
+        continue;
+      }
+      if (lane == 0) one_by_one(b, in_len, c0, min(c0 + 64, s1), acc, prev_end);
+      acc = __shfl(acc, 0, 64);
+      prev_end = __shfl(prev_end, 0, 64);
     }
-    acc = __shfl(acc, 0, 64);
-    prev_end = __shfl(prev_end, 0, 64);
+    if (lane == 0) out_len[b] = in_len + acc;
   }
-  if (lane == 0) out_len[b] = in_len + acc;
 }
 
 // A thread per span, the grid striding over the spans there are (their count
@@ -631,8 +658,9 @@ void launch_ps_layout(const PcacheDev& pc, const int64_t* cu_bytes, int B, const
                       const int* cu_spans, int span_cap, int64_t* out_len, int64_t* sp_out, int* sp_plen,
                       int64_t* sp_in_end, uint32_t* err, hipStream_t s) {
   if (B <= 0) return;
-  hipLaunchKernelGGL(ps_layout_kernel, dim3(ceil_div(B, 4)), dim3(256), 0, s, pc, cu_bytes, B, spans, cu_spans,
-                     span_cap, out_len, sp_out, sp_plen, sp_in_end, err);
+  const int per = std::min(ceil_div(B, 16384), 64);
+  hipLaunchKernelGGL(ps_layout_kernel, dim3(ceil_div(B, (int64_t)4 * per)), dim3(256), 0, s, pc, cu_bytes, B, per, spans,
+                     cu_spans, span_cap, out_len, sp_out, sp_plen, sp_in_end, err);
 }
 
 void launch_ps_hash(const PcacheDev& pc, const uint8_t* text, const int64_t* cu_bytes, int B, const anon_span* spans,

@@ -131,3 +131,26 @@ def test_output_chunks_at_every_alignment_and_short_capacity(shift):
         got, total, cap = _run(records, spans, 12, cache, out_short=short, out_shift=shift)
         assert total == len(want) and b"".join(got) == want[:cap]
         assert bool(api.device_errors(0, clear=True) & api.ERR_OUT_CAP) == (short > 0)
+
+
+@pytest.mark.parametrize("n_records", [16384, 16385, 40000, 63 * 16384 + 1])
+def test_several_records_to_a_wave(n_records):
+    """Above 16,384 records a wave lays out several: most empty, some with as
+    many spans as one lane takes (8), with more, with a wave's and an invalid
+    one among them."""
+    from paper_2606_15650_amd import api
+    rng = random.Random(n_records)
+    records, spans = [b""] * n_records, [[] for _ in range(n_records)]
+    special = [0, 1, 62, 63, 64, 65, n_records - 2, n_records - 1] + [rng.randrange(n_records) for _ in range(500)]
+    for i, b in enumerate(special):
+        records[b], spans[b] = _record(rng, [0, 1, 2, 7, 8, 9, 63, 64, 65, 130][i % 10], [0, 3, 20, 60], 9)
+        if i % 7 == 3 and spans[b]:
+            k = rng.randrange(len(spans[b]))
+            spans[b][k] = (rng.choice([0, 4, 1]), spans[b][k][1], len(records[b]) + 1)
+    cache = api.PseudonymCache(KEY, 10, TYPES, 1 << 14)
+    api.device_errors(0, clear=True)
+    say(f"[pseudonymize] {n_records} records, {sum(map(len, spans))} spans")
+    got, total, _ = _run(records, spans, 10, cache)
+    want = _want(records, spans, 10)
+    assert total == len(b"".join(want)) and got == want
+    assert api.device_errors(0, clear=True) == api.ERR_SPAN
