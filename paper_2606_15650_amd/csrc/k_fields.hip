@@ -33,7 +33,7 @@ constexpr int kTile = 8192;
 constexpr int kAfter = 448;                 // staged past the tile
 constexpr int kWin = kTile + kAfter;
 constexpr int kWinWords = kWin / 64;
-constexpr int kTileFields = kTile / 4;      // "x: v" is 4 bytes
+constexpr int kTileFields = kTile / 4;      // (a field has 4 bytes at least: "x: v")
 
 __device__ __forceinline__ int find_in(const int64_t* cu, int a, int c, int64_t p) {
   while (a < c) {  // largest index of [a, c] with cu <= p
@@ -179,6 +179,7 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
   const int n_lines = ws[0] + ws[1] + ws[2] + ws[3];
   int total = 0;  // fields found so far
   FieldEntry* to = out.entries + (size_t)blockIdx.x * kTileFields;
+  const int room = (int)min((int64_t)kTileFields, (n - p0 + 3) / 4);
   __syncthreads();
   for (int l0 = 0; l0 < n_lines; l0 += 256) {
     FieldEntry f{0, 0, 0, 0};
@@ -192,11 +193,11 @@ __global__ __launch_bounds__(256) void fd_match_kernel(const uint8_t* __restrict
       if (w < wave) at += ws[w];
       total += ws[w];
     }
-    if (f.type > 0 && at < kTileFields) to[at] = f;
+    if (f.type > 0 && at < room) to[at] = f;
     __syncthreads();
   }
   if (tid == 0) {
-    out.counts[blockIdx.x] = min(total, kTileFields);
+    out.counts[blockIdx.x] = min(total, room);
     out.rec0[blockIdx.x] = r0;
   }
 }
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(256) void fd_emit_kernel(const int64_t* __restrict_
 FieldBuffers field_layout(int64_t n, Carver& k) {
   const int64_t tiles = (n + kTile - 1) / kTile;
   FieldBuffers w;
-  w.entries = k.take<FieldEntry>(tiles * kTileFields);
+  w.entries = k.take<FieldEntry>((n + 3) / 4);
   w.counts = k.take<int>(tiles + 1);
   w.rec0 = k.take<int>(tiles + 1);
   return w;

@@ -338,9 +338,10 @@ __device__ int match_ipv6(const Rec& r, int p) {
 
 constexpr int kRecognizers = kNumRecognizers;
 constexpr int kTileWords = kTile / 64;
-// matches per tile: an anchor gives at most two, a 16-byte block and a record
-// start one each
-constexpr int kTileEntries = 2 * kTile + kTile / 16;
+// matches of a tile: an anchor gives at most two, a 16-byte block and a record
+// start (no anchor) one each
+__host__ __device__ constexpr int64_t tile_entries(int64_t bytes) { return 2 * bytes + (bytes + 15) / 16; }
+constexpr int kTileEntries = (int)tile_entries(kTile);
 struct RecTypes {
   int t[kRecognizers];  // type index per recognizer, 0 = off
 };
@@ -560,11 +561,12 @@ __global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict
     else record_bounds(cu, x, n, lo, hi);
     return Rec{text, lo, hi, win, cls, base, wlo, whi};
   };
+  const int entry_room = (int)tile_entries(min((int64_t)kTile, n - p0));
   auto emit = [&](const Rec& r, int rule, int p, int e) {
     if (e < 0) return;
     mark_span(w, p, e);
     const int slot = atomicAdd(&n_entries, 1);
-    if (slot < kTileEntries)
+    if (slot < entry_room)
       w.entries[(size_t)blockIdx.x * kTileEntries + slot] =
           RecogEntry{p, 0, span_key(e - p, 1 + rule, p - r.lo, rt.t[rule])};
   };
@@ -609,7 +611,7 @@ __global__ __launch_bounds__(256) void rx_match_kernel(const uint8_t* __restrict
   }
   __syncthreads();
   if (tid == 0) {
-    w.n_entries[blockIdx.x] = min(n_entries, kTileEntries);
+    w.n_entries[blockIdx.x] = min(n_entries, entry_room);
     w.rec0[blockIdx.x] = r0;
   }
 }
@@ -810,8 +812,8 @@ RecogBuffers recog_layout(int64_t n, Carver& k) {
   w.tile_count = k.take<int>(tiles + 1);
   w.tile_pre = k.take<int>(tiles + 1);
   w.rec0 = k.take<int>(tiles + 1);
-  w.keys = k.take<unsigned long long>(tiles * kTile);
-  w.entries = k.take<RecogEntry>(tiles * kTileEntries);
+  w.keys = k.take<unsigned long long>(n);
+  w.entries = k.take<RecogEntry>(tiles > 0 ? (tiles - 1) * kTileEntries + tile_entries(n - (tiles - 1) * kTile) : 0);
   return w;
 }
 

@@ -343,10 +343,10 @@ void launch_exclusive_scan_i64(const int64_t* in, int64_t* out, int64_t n, void*
 
 size_t bio_layout(int T, Carver& k, BioBuffers& w) {
   const int tiles = ceil_div(T, kTile);
-  w.bits = k.take<uint16_t>((size_t)tiles * (kTile / 16));
-  w.rank = k.take<uint16_t>((size_t)tiles * (kTile / 16));
-  w.counts = k.take<int>(tiles + 1);
-  w.rec0 = k.take<int>(tiles + 1);
+  w.bits = k.take<uint16_t>(ceil_div(T, 16));
+  w.rank = k.take<uint16_t>(ceil_div(T, 16));
+  w.counts = k.take<int>((size_t)2 * (tiles + 1));
+  w.rec0 = w.counts + tiles + 1;
   return k.used;
 }
 

@@ -1122,8 +1122,8 @@ anon_status anon_decode_workspace_size(int32_t T, int32_t B, size_t* bytes) {
   if (!bytes || T < 0 || B < 0) return set_error(ANON_EINVAL, "bad arguments");
   Carver k(nullptr, SIZE_MAX);
   BioBuffers w;
-  // the buffers take 1.5 bytes per token; the size asked for stays an int per
-  // token, which callers may rely on as its least
+  // the buffers take a quarter of a byte per token; the size asked for stays an
+  // int per token, which callers may rely on as its least
   *bytes = std::max(bio_layout(T, k, w), (size_t)T * 4) + 256;
   return ANON_OK;
 }
