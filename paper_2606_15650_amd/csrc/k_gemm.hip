@@ -498,9 +498,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // 4.80 / 3.59 ms with the same ring, not kept.
 //
 // Where the epilogue stages no more than a wave's own part of A's third slot
-// (BF16 256x256, all but the residual epilogue), a workgroup keeps its CU for
-// every 256th tile: the next tile's first copies, all but those into that
-// slot, travel during the epilogue.  855,055 rows: FFN1 4.71 -> 4.54 ms, QKV
+// (stays()), a workgroup keeps its CU for every 256th tile: the next tile's
+// first copies, all but those into that slot, travel during the epilogue.  855,055 rows: FFN1 4.71 -> 4.54 ms, QKV
 // 2.76 -> 2.72; the epilogue itself (the GELU is 92 of its clocks per element
 // and wave) still runs with the matrix pipe idle, and two workgroups of 128x256
 // tiles per CU, which overlap it, lose more in the main loop (QKV of 200,000
@@ -593,6 +592,19 @@ constexpr int kAhead = -1;
 constexpr int kTileRegs = 100;
 constexpr int kLoaders = 8;
 
+// Whether a workgroup stays for several tiles, by the kernel and by its
+// launch: it has a CU to itself, and its epilogue needs no more LDS than A's
+// third slot (BM x BK).  BF16: the 256x256 tiles but with the residual
+// epilogue, with the gated one, which writes half as many columns, all of one
+// workgroup per CU.
+template <typename TI, typename TO, int EPI, int BM, int BN, int BK, int WGM, int WGN, int ST, int OCC>
+constexpr bool stays() {
+  if constexpr (ST == kAhead && OCC == 1 && sizeof(TI) == 2 && EPI != EPI_RESID)
+    return BM * BK * (int)sizeof(TI) >=
+           WGM * WGN * Staging<TO, EPI, BM / WGM / 32, BN / WGN / 32, WGM * WGN, 1 << 20>::STRIP;
+  return false;
+}
+
 template <typename TI, typename TO, typename TR, int EPI, int BM, int BN, int BK, int WGM, int WGN, int ST,
           int OCC>
 __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OCC) void gemm_dma_kernel(DevParams p) {
@@ -617,10 +629,7 @@ __global__ __launch_bounds__(ST >= kTileRegs ? kLoaders * 64 : WGM* WGN * 64, OC
   constexpr bool AHEAD = ST == kAhead, WHOLE = ST >= kTileRegs;
   constexpr int SL = WHOLE ? ST - kTileRegs : ST;  // stages
   static_assert(AHEAD || (SL - 1) * LPT < 64, "vmcnt range");
-  // a workgroup stays for several tiles where the epilogue needs no more than
-  // A's third slot (see kAhead above)
-  constexpr bool PERSIST =
-      AHEAD && OCC == 1 && sizeof(TI) == 2 && EPI != EPI_RESID && A_BYTES >= NW * Staging<TO, EPI, TM, TN, NW, 1 << 20>::STRIP;
+  constexpr bool PERSIST = stays<TI, TO, EPI, BM, BN, BK, WGM, WGN, ST, OCC>();
   constexpr int SMEM = AHEAD ? 3 * A_BYTES + 2 * (STAGE - A_BYTES) : SL * STAGE;
   static_assert(SMEM <= 160 * 1024, "LDS ring exceeds the CU's 160 KB");
   __shared__ __align__(1024) char smem[SMEM];
@@ -1052,9 +1061,7 @@ bool run(const GemmParams& g, hipStream_t s) {
   DevParams p{g.A, g.W, g.bias, g.resid, g.C, g.M, g.N, g.K, g.qscale, g.qcols, g.acc_scale, g.out_inv_scale, gm,
               g.ldc > 0 ? g.ldc : (g.epi == EPI_GEGLU ? g.N / 2 : g.N), g.pos, g.rope, g.rope_cols, g.m_dev};
   const int tiles = ((g.M + BM - 1) / BM) * (g.N / BN);
-  // (a workgroup of the persistent kernel has a CU to itself)
-  constexpr bool PERSIST = ST == kAhead && OCC == 1 && sizeof(TI) == 2 && EPI != EPI_RESID &&
-                           BM * BK * (int)sizeof(TI) >= WGM * WGN * Staging<TO, EPI, BM / WGM / 32, BN / WGN / 32, WGM * WGN, 1 << 20>::STRIP;
+  constexpr bool PERSIST = stays<TI, TO, EPI, BM, BN, BK, WGM, WGN, ST, OCC>();
   if constexpr (ST == 0) {
     hipLaunchKernelGGL((gemm_kernel<TI, TO, TR, EPI, BM, BN, BK, WGM, WGN, OCC>), dim3(tiles),
                        dim3(WGM * WGN * 64), 0, s, p);

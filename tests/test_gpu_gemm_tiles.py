@@ -128,6 +128,45 @@ def test_several_tiles_per_workgroup_rotary_and_gated(torch_dev):
     assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
 
 
+@pytest.mark.parametrize("tile,name", [(12, "192x256"), (13, "128x256")])
+def test_several_narrower_gated_tiles_per_workgroup(torch_dev, tile, name):
+    """The gated epilogue lets workgroups of 192x256 and 128x256 tiles stay for
+    several too: more than 256 of each, the bits of 128x128 tiles."""
+    import torch
+    from paper_2606_15650_amd import api
+    from synth.configs import MODERN_TINY
+    cfg = replace(MODERN_TINY, n_layers=1, vocab=2000, hidden=256, n_heads=4, intermediate=512)
+    m = api.ModernModel(cfg, synth.weights_blob(cfg, synth.make_weights(cfg, 0, None)), "bf16")
+    T = 30011  # 157 or 235 row blocks of four column blocks
+    L = _lengths(T)
+    ids = torch.from_numpy(np.random.default_rng(1).integers(0, cfg.vocab, T).astype(np.int32)).cuda()
+    d_cu = torch.from_numpy(np.concatenate([[0], np.cumsum(L)]).astype(np.int32)).cuda()
+    n = m.workspace_size(T, len(L))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    say(f"[gemm] {T} rows, gated, {name}")
+    outs = []
+    for t in (14, tile):
+        m.set_tiles([t, -1, t, -1, -1])
+        out = torch.empty((T, cfg.hidden), dtype=torch.float32, device="cuda")
+        m.hidden(ids, d_cu, len(L), T, 1, out, ws, n)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert bool(torch.isfinite(outs[0]).all()) and torch.equal(outs[0], outs[1])
+
+
+def test_several_tiles_per_workgroup_in_a_bucket_replay(torch_dev):
+    """Replays of a bucket whose live tiles are more than the workgroups and
+    fewer than the bucket holds."""
+    from tests.test_gpu_graph import _bucket_replays_match_eager
+    cfg = replace(BASE, n_layers=1, vocab=2000)
+    _, m = make_model(cfg, "bf16", 0)
+    m.set_tiles([11, -1, 11, -1])
+    assert "256x256" in m.tile_configs()[11]
+    batches = [[512] * 18 + [1], [512] * 32, [200] * 40, [97] * 100, [512] * 24]
+    _bucket_replays_match_eager(m, 16384, batches, 50)
+    m.close()
+
+
 def test_a_launch_of_too_many_threads_takes_another_tile(torch_dev):
     """A tile kept for a few rows, on so many that its workgroups would hold
     2^32 threads: the call runs on another tile (the same bits), and the
