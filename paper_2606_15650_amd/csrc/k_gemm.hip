@@ -1238,7 +1238,14 @@ int default_gemm_config(const GemmParams& g) {
     // M is what a captured launch may hold, its row count on the device what
     // a replay brings: then the mean over the quarters of M counts.  8,192
     // rows at most, FFN2 of the base encoder with 4,096 / 8,192 brought:
-    // 128x256 tiles (best when full) 41 / 42.5 us, 128x128 27 / 44.4.
+    // 128x256 tiles (best when full) 41 / 42.5 us, 128x128 27 / 44.4.  The
+    // server's buckets halve and the smallest that holds a batch is replayed,
+    // so all but its smallest are half full at least; with the mean over
+    // 50-100% instead, a replay of four base layers took, at 51 / 75 / 100%
+    //   2,048 rows at most   278 / 327 / 355 us   (here 272 / 348 / 370)
+    //   4,096                396 / 454 / 499      (360 / 462 / 512)
+    //   8,192                534 / 674 / 796      (522 / 679 / 806)
+    // and 512, 1,024 and 16,384 the same: no gain, and 5-20% lost below half.
     float us = 0.f;
     for (int q = g.m_dev ? 1 : 4; q <= 4; ++q) us += tile_cost(t, cs[t.config], g, (int)((int64_t)g.M * q / 4));
     if (best < 0 || us < best_t) best = t.config, best_t = us;
