@@ -155,30 +155,34 @@ __device__ inline void hmac_words(const PcacheDev& pc, const uint32_t (&m)[kMsgW
     const uint32_t pad = (len >> 2) == i ? 0x80u << (8 * (len & 3)) : 0;
     return __builtin_bswap32(v | pad);
   };
-  const uint32_t bits = (64 + (uint32_t)len) * 8;
-  uint32_t w[16];
-  if (len < 56) {
+  // the blocks of the message, then the outer one, by one compression's code
+  // (a copy of it for each is more than the instruction cache holds)
+  const int blocks = len < 56 ? 1 : 2;
+#pragma unroll 1
+  for (int blk = 0; blk <= blocks; ++blk) {
+    const bool outer = blk == blocks;
+    uint32_t w[16];
 #pragma unroll
-    for (int i = 0; i < 15; ++i) w[i] = word(i);
-    w[15] = bits;
-    sha256_compress(st, w);
-  } else {
+    for (int i = 0; i < 16; ++i) {
+      const uint32_t pad = i == 8 ? 0x80000000u : i == 15 ? (64 + 32) * 8 : 0;
+      w[i] = outer ? (i < 8 ? st[i & 7] : pad) : blk == 0 ? word(i) : word(16 + i);
+    }
+    if (blk == blocks - 1) w[15] = (64 + (uint32_t)len) * 8;
+    if (outer) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) w[i] = word(i);
-    sha256_compress(st, w);
-#pragma unroll
-    for (int i = 0; i < 15; ++i) w[i] = word(16 + i);
-    w[15] = bits;
+      for (int i = 0; i < 8; ++i) st[i] = pc.opad[i];
+    }
     sha256_compress(st, w);
   }
-  hmac_outer(pc, st, out);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) out[i] = st[i];
 }
 
 // Table entry: state, length, fingerprint, entity bytes, digest, and for the
 // mapping export the smallest type the entity was pseudonymized under and the
 // first and last call that met it.
 struct __align__(16) Entry {
-  uint32_t state;  // 0 empty, 1 being written, 2 ready
+  uint32_t state;  // 0 empty, 1 being written, 2 ready; above them 30 bits of fp
   uint32_t len;
   uint64_t fp;
   uint8_t bytes[kMaxEntity];
@@ -265,6 +269,7 @@ __device__ __forceinline__ bool same_bytes(const Entry* e, const uint32_t (&m)[k
 // empty ones: 144 us against 5.5 of a thread each): a lane reads a record's
 // bounds, and lays out up to kFewSpans by itself.
 constexpr int kFewSpans = 8;
+template <bool SEVERAL>  // records to a wave
 __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int64_t* __restrict__ cu_bytes, int B,
                                                         int per, const anon_span* __restrict__ spans,
                                                         const int* __restrict__ cu_spans, int span_cap,
@@ -296,32 +301,19 @@ __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int6
       }
     }
   };
-  // this lane's record
-  const bool mine = lane < per && first + lane < B;
-  int64_t my_len = 0;
-  int my_s0 = 0, my_s1 = 0;
-  if (mine) {
-    const int64_t b = first + lane;
-    my_len = cu_bytes[b + 1] - cu_bytes[b];
-    if (my_len < 0) {
+  auto bounds = [&](int64_t b, int64_t& in_len, int& s0, int& s1) {
+    in_len = cu_bytes[b + 1] - cu_bytes[b];
+    if (in_len < 0) {
       raise_error(err, ANON_ERR_SPAN);
-      my_len = 0;
+      in_len = 0;
     }
-    my_s0 = cu_spans[b], my_s1 = cu_spans[b + 1];
-    if (my_s1 > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
-    my_s0 = min(max(my_s0, 0), span_cap);
-    my_s1 = min(max(my_s1, my_s0), span_cap);
-  }
-  const bool few = per > 1 && my_s1 - my_s0 <= kFewSpans;
-  if (mine && few) {
-    int64_t acc = 0, prev_end = 0;
-    one_by_one((int)first + lane, my_len, my_s0, my_s1, acc, prev_end);
-    out_len[first + lane] = my_len + acc;
-  }
-  for (uint64_t todo = __ballot(mine && !few); todo; todo &= todo - 1) {
-    const int of = __ffsll((unsigned long long)todo) - 1, b = (int)first + of;
-    const int64_t in_len = __shfl(my_len, of, 64);
-    const int s0 = __shfl(my_s0, of, 64), s1 = __shfl(my_s1, of, 64);
+    s0 = cu_spans[b], s1 = cu_spans[b + 1];
+    if (s1 > span_cap) raise_error(err, ANON_ERR_SPAN_CAP);
+    s0 = min(max(s0, 0), span_cap);
+    s1 = min(max(s1, s0), span_cap);
+  };
+  // record b by the whole wave
+  auto by_wave = [&](int b, int64_t in_len, int s0, int s1) {
     int64_t acc = 0, prev_end = 0;
     for (int c0 = s0; c0 < s1; c0 += 64) {
       const int s = c0 + lane;
@@ -362,6 +354,27 @@ __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int6
       prev_end = __shfl(prev_end, 0, 64);
     }
     if (lane == 0) out_len[b] = in_len + acc;
+  };
+  int64_t in_len = 0;
+  int s0 = 0, s1 = 0;
+  if constexpr (!SEVERAL) {
+    if (first >= B) return;
+    bounds(first, in_len, s0, s1);
+    by_wave((int)first, in_len, s0, s1);
+    return;
+  }
+  const int b = (int)first + lane;  // this lane's record
+  const bool mine = lane < per && first + lane < B;
+  if (mine) bounds(b, in_len, s0, s1);
+  const bool few = s1 - s0 <= kFewSpans;
+  if (mine && few) {
+    int64_t acc = 0, prev_end = 0;
+    one_by_one(b, in_len, s0, s1, acc, prev_end);
+    out_len[b] = in_len + acc;
+  }
+  for (uint64_t todo = __ballot(mine && !few); todo; todo &= todo - 1) {
+    const int of = __ffsll((unsigned long long)todo) - 1;
+    by_wave((int)first + of, __shfl(in_len, of, 64), __shfl(s0, of, 64), __shfl(s1, of, 64));
   }
 }
 
@@ -370,9 +383,18 @@ __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int6
 // once into registers with 16-byte loads, and hashed, compared and stored
 // from there.  The counters are summed per workgroup into one of
 // kCounterSlots slots, where every wave's two atomics met on one line.  Bound
-// by the latency of text, probe and entry, each found by the one before: 128
-// MB in 16,384 records, 160 -> 50 us.
-__global__ __launch_bounds__(256) void ps_hash_kernel(PcacheDev pc, const uint8_t* __restrict__ text,
+// by the latency of text, probe and entry, each found by the one before, and
+// for new entities by fences: a slot's state carries 30 bits of its
+// fingerprint, so that only a slot that is nearly surely the entity's is read
+// behind a fence or waited for.  us per call, cold being a first meeting:
+//   139,000 spans of 359 entities in 128 MB: 49, cold 131 (a thread per
+//     span, bytewise: 160, 265)
+//   120,000 spans, nearly all of an entity each: cold 130 (every occupied slot
+//     behind a fence, every slot being written waited for: 396; neither
+//     waiting nor tags: 167)
+// Three waves a SIMD, and one copy of the compression for an entity's blocks
+// (hmac_words): 57 -> 49 for the hits.
+__global__ __launch_bounds__(256, 3) void ps_hash_kernel(PcacheDev pc, const uint8_t* __restrict__ text,
                                                       const int64_t* __restrict__ cu_bytes, int B,
                                                       const anon_span* __restrict__ spans,
                                                       const int* __restrict__ cu_spans, int span_cap,
@@ -397,6 +419,7 @@ __global__ __launch_bounds__(256) void ps_hash_kernel(PcacheDev pc, const uint8_
       uint32_t m[kMsgWords];
       load_entity(text, at, len, text_end, m);
       const uint64_t fp = pc.enabled ? fingerprint(m, len) : 0;
+      const uint32_t tag = (uint32_t)(fp >> 32) & ~3u;
       bool have = false;
       if (pc.enabled) {
         ++lookups;
@@ -405,7 +428,7 @@ __global__ __launch_bounds__(256) void ps_hash_kernel(PcacheDev pc, const uint8_
           Entry* e = table + slot;
           const uint32_t stt = __hip_atomic_load(&e->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if (stt == 0) break;
-          if (stt != 2) continue;
+          if (stt != (tag | 2)) continue;
           // a ready entry: this fence pairs with its writer's release fence, so
           // the entry's fields read below are the ones written before "ready"
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
@@ -422,53 +445,64 @@ __global__ __launch_bounds__(256) void ps_hash_kernel(PcacheDev pc, const uint8_
       if (!have) {
         hmac_words(pc, m, len, dg);
         if (pc.enabled) {
-          // A slot that is being written is looked at again, a bounded number
-          // of times: it may be getting this very entity.  The loop's condition
-          // is the wave's, so that a lane that claimed a slot has published it
-          // before the wave's other lanes look again; else the many lanes of
-          // one frequent new entity fill kMaxProbe slots with it, and an entity
+          // In rounds of the wave: every lane goes on to a slot that it can
+          // claim, to its entity, or to a slot that is being written; then one
+          // release fence publishes all that were claimed (a fence is a cache
+          // write-back on this part).  A slot being written that has this
+          // entity's tag may be getting this very entity, so it is looked at
+          // again, a bounded number of times: else the many lanes of one
+          // frequent new entity fill kMaxProbe slots with it, and an entity
           // whose place is the first of them finds no room.
           uint64_t slot = fp & pc.mask;
           int probe = 0, waits = 0;
-          bool placed = false;
-          while (__any(!placed && probe < kMaxProbe)) {
-            if (placed || probe >= kMaxProbe) continue;
-            Entry* e = table + slot;
-            // claiming an empty slot reads nothing of another writer's, so the
-            // claim needs no ordering; the fields are published by one release
-            // fence ahead of the "ready" store (a fence is a cache write-back on
-            // this part: one per wave instead of one per atomic)
-            uint32_t expected = 0;
-            if (__hip_atomic_compare_exchange_strong(&e->state, &expected, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT)) {
-              e->len = (uint32_t)len;
-              e->fp = fp;
+          bool open = true;
+          while (__any(open)) {
+            Entry* claimed = nullptr;
+            while (open) {
+              if (probe >= kMaxProbe) {
+                open = false;
+                break;
+              }
+              Entry* e = table + slot;
+              // claiming an empty slot reads nothing of another writer's, so the
+              // claim needs no ordering (waiting is a load: many waves wait for
+              // one frequent new entity)
+              uint32_t expected = 0;
+              if (waits > 0) expected = __hip_atomic_load(&e->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              if (expected == 0 && __hip_atomic_compare_exchange_strong(&e->state, &expected, tag | 1, __ATOMIC_RELAXED,
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                claimed = e;
+                break;
+              }
+              if (expected == (tag | 2)) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (e->fp == fp && e->len == (uint32_t)len && same_bytes(e, m, len)) {
+                  touch(e, sp.type, pc.call);
+                  open = false;
+                  break;
+                }
+              } else if (expected == (tag | 1) && waits < kMaxProbe) {
+                ++waits;
+                break;
+              }
+              ++probe;
+              slot = (slot + 1) & pc.mask;
+            }
+            if (claimed) {
+              claimed->len = (uint32_t)len;
+              claimed->fp = fp;
 #pragma unroll
               for (int c = 0; c < kMsgWords / 4; ++c)
-                *(uint4*)(e->bytes + 16 * c) = uint4{m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]};
+                *(uint4*)(claimed->bytes + 16 * c) = uint4{m[4 * c], m[4 * c + 1], m[4 * c + 2], m[4 * c + 3]};
 #pragma unroll
-              for (int k = 0; k < 8; ++k) e->digest[k] = dg[k];
-              e->type = sp.type;
-              e->first = e->last = pc.call;
+              for (int k = 0; k < 8; ++k) claimed->digest[k] = dg[k];
+              claimed->type = sp.type;
+              claimed->first = claimed->last = pc.call;
               __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-              __hip_atomic_store(&e->state, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(&claimed->state, tag | 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               ++inserts;
-              placed = true;
-              continue;
+              open = false;
             }
-            if (expected == 2) {
-              __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-              if (e->fp == fp && e->len == (uint32_t)len && same_bytes(e, m, len)) {
-                touch(e, sp.type, pc.call);
-                placed = true;
-                continue;
-              }
-            } else if (waits < kMaxProbe) {
-              ++waits;
-              continue;
-            }
-            ++probe;
-            slot = (slot + 1) & pc.mask;
           }
         }
       }
@@ -659,8 +693,9 @@ void launch_ps_layout(const PcacheDev& pc, const int64_t* cu_bytes, int B, const
                       int64_t* sp_in_end, uint32_t* err, hipStream_t s) {
   if (B <= 0) return;
   const int per = std::min(ceil_div(B, 16384), 64);
-  hipLaunchKernelGGL(ps_layout_kernel, dim3(ceil_div(B, (int64_t)4 * per)), dim3(256), 0, s, pc, cu_bytes, B, per, spans,
-                     cu_spans, span_cap, out_len, sp_out, sp_plen, sp_in_end, err);
+  hipLaunchKernelGGL(per > 1 ? ps_layout_kernel<true> : ps_layout_kernel<false>, dim3(ceil_div(B, (int64_t)4 * per)),
+                     dim3(256), 0, s, pc, cu_bytes, B, per, spans, cu_spans, span_cap, out_len, sp_out, sp_plen,
+                     sp_in_end, err);
 }
 
 void launch_ps_hash(const PcacheDev& pc, const uint8_t* text, const int64_t* cu_bytes, int B, const anon_span* spans,

@@ -1407,7 +1407,7 @@ anon_status anon_pcache_export(anon_pcache* p, anon_mapping* h_out, int64_t cap,
                              (size_t)cn * sizeof(PcacheEntryView), hipMemcpyDeviceToHost));
     for (int64_t ei = 0; ei < cn; ++ei) {
       const PcacheEntryView& e = tab[(size_t)ei];
-      if (e.state != 2 || e.len > 96) continue;
+      if ((e.state & 3) != 2 || e.len > 96) continue;
       const std::string k((const char*)e.bytes, e.len);
       auto it = merged.find(k);
       if (it == merged.end()) {
