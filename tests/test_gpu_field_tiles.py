@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import random
 
+import numpy as np
 import pytest
 
 from oracle import fields as F
@@ -93,3 +94,35 @@ def test_names_of_one_key():
         _, got = _fields_gpu(rb, make_cache(TYPE_NAMES_17), config)
         assert got == F.field_spans_batch(rb.text, rb.cu_bytes, config)
         assert sum(map(len, got)) > 0
+
+
+@pytest.mark.parametrize("line", [b"a\n", b"ab: \n", b"a:b: c\n", b"n" * 32 + b": v\n", b"n" * 33 + b": v\n"])
+def test_short_lines_that_hold_no_field_or_few(line):
+    """As many lines as a tile can hold, without a ':' or with one that makes no
+    configured field: a line costs no look past its name."""
+    import torch
+    from paper_2606_15650_amd import api
+    from tests.test_gpu_empty_records import _us
+    config = {"a": 1, "n" * 32: 2}
+
+    def call(text, B):
+        n = len(text)
+        d_text = torch.from_numpy(np.frombuffer(text, np.uint8).copy()).cuda()
+        cu = torch.linspace(0, n, B + 1, dtype=torch.float64).to(torch.int64).cuda()
+        cap = n // 4 + 1
+        spans, cs = torch.empty((cap, 3), dtype=torch.int64, device="cuda"), torch.empty(B + 1, dtype=torch.int32, device="cuda")
+        ws = torch.empty(api.field_workspace_size(n, B), dtype=torch.uint8, device="cuda")
+        return lambda: api.field_spans(d_text, cu, B, n, config, 2, spans, cap, cs, ws, ws.numel()), spans, cs
+    count = 4_800_000 // len(line)
+    fn, spans, cs = call(line * count, 1)
+    many = _us(fn)
+    n = int(cs[1])
+    assert n == (count if len(line) == 36 and line[0] == ord("n") and line[32] == ord(":") else 0)
+    if n:
+        got = spans[:n].cpu().numpy()
+        begin = np.arange(n) * len(line) + 34
+        np.testing.assert_array_equal(got, np.stack([np.full(n, 2 << 32), begin, begin + 1], 1))
+    few = _us(call((b"x" * 1199 + b"\n") * 4000, 1)[0])
+    say(f"[fields] {count} lines {line[:8]}: {n} fields, {many:.1f} us, lines of 1200 bytes {few:.1f} us")
+    assert many < 4 * few + 20
+    assert api.device_errors() == 0
