@@ -203,3 +203,33 @@ def test_many_new_entities_at_once():
     say(f"[pseudonymize] {len(rows)} new entities {cold:.1f} us, without a table {without:.1f} us")
     assert cold < 3.3 * without
     assert api.device_errors(0, clear=True) == 0
+
+
+def test_many_invalid_spans():
+    """Every second span invalid: the calls end with the error bit and the valid
+    spans replaced, and the invalid ones do not queue up for the bit."""
+    import torch
+    from paper_2606_15650_amd import api
+    from tests.test_gpu_empty_records import _us
+    B, per = 1024, 60
+    records = [bytes(97 + (i + j) % 26 for j in range(per * 10)) for i in range(B)]
+    cu = torch.arange(0, B * per * 10 + 1, per * 10, dtype=torch.int64, device="cuda")
+    cs = torch.arange(0, B * per + 1, per, dtype=torch.int32, device="cuda")
+    d_text = torch.from_numpy(np.frombuffer(b"".join(records), np.uint8).copy()).cuda()
+    cap = B * per * 40
+    out, cu_out = torch.empty(cap, dtype=torch.uint8, device="cuda"), torch.empty(B + 1, dtype=torch.int64, device="cuda")
+    n_ws = api.pseudonymize_workspace_size(B, B * per)
+    ws = torch.empty(n_ws, dtype=torch.uint8, device="cuda")
+    cache = api.PseudonymCache(KEY, 10, TYPES, 1 << 16)
+    us = {}
+    for kind in ("valid", "invalid"):
+        lists = [[(1 + k % 3, 10 * k + 2, 10 * k + (8 if kind == "valid" or k % 2 else 1)) for k in range(per)] for _ in range(B)]
+        rows = np.array([(b | t << 32, s, e) for b in range(B) for t, s, e in lists[b]], np.int64)
+        d_sp = torch.from_numpy(rows).cuda()
+        api.device_errors(0, clear=True)
+        us[kind] = _us(lambda: api.pseudonymize(cache, d_text, cu, B, d_sp, cs, B * per, out, cap, cu_out, ws, n_ws))
+        assert api.device_errors(0, clear=True) == (0 if kind == "valid" else api.ERR_SPAN)
+        want = _want(records[:40], lists[:40], 10)
+        assert out[:int(cu_out[40])].cpu().numpy().tobytes() == b"".join(want)
+    say(f"[pseudonymize] {B * per} spans {us['valid']:.1f} us, every second invalid {us['invalid']:.1f} us")
+    assert us["invalid"] < 3 * us["valid"]
