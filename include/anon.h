@@ -192,7 +192,8 @@ void anon_graph_free(anon_graph* graph);
 /* GEMM tile autotuner.  Times every tile configuration that fits each of the
  * four encoder GEMMs (0 QKV, 1 output projection, 2 FFN1, 3 FFN2) on T rows,
  * using d_workspace (>= anon_ner_workspace_size(T, 1) bytes; overwritten) as
- * operand memory, and keeps the fastest for this model's later calls; then,
+ * operand memory, and keeps the fastest for this model's later calls of T/2
+ * to 2 T rows (those of other sizes take the built-in choice by rows); then,
  * with that tile, it times the tile orders (groups of 2, 4, 6, 8 or 12 row
  * blocks against the order by shape, see anon_model_set_tile_groups) and
  * keeps one that is at least 1% faster than the order by shape.  All

@@ -126,6 +126,8 @@ struct anon_model {
   ElemType qkv_t;   // Q, K, V and attention operands
   int gemm_cfg[4] = {-1, -1, -1, -1};
   int gemm_gm[4] = {0, 0, 0, 0};  // row blocks per tile group (0: by shape)
+  int tuned_rows = 0;              // rows that the autotuner chose gemm_cfg for (0: a caller's choice or none)
+  bool groups_tuned = false;       // gemm_gm is the autotuner's
   int attn_cfg = -1;               // attention tile configuration (-1: default)
 };
 
@@ -497,6 +499,18 @@ static anon_status check_batch(const anon_model* m, const void* d_ids, const voi
 
 static double gemm_flops(double M, double N, double K) { return 2.0 * M * N * K; }
 
+// The tile of GEMM `which` for g.M rows.  The autotuner's holds from half to
+// twice the rows that it timed; for others the tile is chosen by rows, as
+// without it: tuned on a record of 137 tokens, whose fastest tile has 32x32
+// elements, a batch of 100,000 ran in 16.4 ms (two base layers; 3.6 by rows),
+// and tuned on 100,000, one of 3,000 in 334 us (230).
+static void set_tile(const anon_model* m, int which, GemmParams& g) {
+  const int64_t rows = g.M, tuned = m->tuned_rows;
+  const bool away = tuned > 0 && (rows > 2 * tuned || 2 * rows < tuned);
+  g.config = away ? -1 : m->gemm_cfg[which];
+  g.group_m = away && m->groups_tuned ? 0 : m->gemm_gm[which];
+}
+
 // Runs the embedding and the first n_layers layers; returns the hidden state.
 // t_dev (nullable): the token count in device memory, at most T (the
 // capacity every grid is sized for).
@@ -534,8 +548,7 @@ static anon_status run_encoder(anon_model* m, const int* ids, const int* cu, int
     g.qscale = 0.125f;
     g.qcols = h;
     g.acc_scale = fp8 ? L.sa[0] * L.sw[0] : 1.f;
-    g.config = m->gemm_cfg[0];
-    g.group_m = m->gemm_gm[0];
+    set_tile(m, 0, g);
     {
       ProfScope ps(KC_QKV, s, gemm_flops(T, 3 * h, h));
       if (!launch_gemm(g, s)) return ANON_EINVAL;
@@ -559,8 +572,7 @@ static anon_status run_encoder(anon_model* m, const int* ids, const int* cu, int
     g.qscale = 1.f;
     g.qcols = 0;
     g.acc_scale = fp8 ? L.sa[1] * L.sw[1] : 1.f;
-    g.config = m->gemm_cfg[1];
-    g.group_m = m->gemm_gm[1];
+    set_tile(m, 1, g);
     {
       ProfScope ps(KC_OPROJ, s, gemm_flops(T, h, h));
       if (!launch_gemm(g, s)) return ANON_EINVAL;
@@ -582,8 +594,7 @@ static anon_status run_encoder(anon_model* m, const int* ids, const int* cu, int
     g.epi = EPI_GELU;
     g.acc_scale = fp8 ? L.sa[2] * L.sw[2] : 1.f;
     g.out_inv_scale = fp8 ? 1.f / L.sa[3] : 1.f;
-    g.config = m->gemm_cfg[2];
-    g.group_m = m->gemm_gm[2];
+    set_tile(m, 2, g);
     {
       ProfScope ps(KC_FFN1, s, gemm_flops(T, f, h));
       if (!launch_gemm(g, s)) return ANON_EINVAL;
@@ -601,8 +612,7 @@ static anon_status run_encoder(anon_model* m, const int* ids, const int* cu, int
     g.epi = EPI_RESID;
     g.acc_scale = fp8 ? L.sa[3] * L.sw[3] : 1.f;
     g.out_inv_scale = 1.f;
-    g.config = m->gemm_cfg[3];
-    g.group_m = m->gemm_gm[3];
+    set_tile(m, 3, g);
     {
       ProfScope ps(KC_FFN2, s, gemm_flops(T, h, f));
       if (!launch_gemm(g, s)) return ANON_EINVAL;
@@ -780,6 +790,7 @@ anon_status anon_model_set_tiles(anon_model* m, const int32_t tiles[4]) {
     if (tiles[i] >= 0 && !gemm_config_fits(m->gemm_t, tiles[i], NK[i][0], NK[i][1]))
       return set_error(ANON_EINVAL, "tile configuration does not fit GEMM " + std::to_string(i));
   for (int i = 0; i < 4; ++i) m->gemm_cfg[i] = tiles[i];
+  m->tuned_rows = 0;
   return ANON_OK;
 }
 
@@ -788,6 +799,7 @@ anon_status anon_model_set_tile_groups(anon_model* m, const int32_t groups[4]) {
   for (int i = 0; i < 4; ++i)
     if (groups[i] < 0 || groups[i] > 1024) return set_error(ANON_EINVAL, "tile group must be in [0, 1024]");
   for (int i = 0; i < 4; ++i) m->gemm_gm[i] = groups[i];
+  m->groups_tuned = false;
   return ANON_OK;
 }
 
@@ -880,6 +892,7 @@ anon_status anon_autotune(anon_model* m, int32_t T, void* d_workspace, size_t ws
       if (best_ms[ci] < ref * margin) best_c = ci;
     }
     m->gemm_cfg[gi] = best_c;
+    m->tuned_rows = T;
     if (chosen) chosen[gi] = best_c;
     // then the tile order of that tile: groups of 2..12 row blocks against
     // the order by shape (kept unless another is at least 1% faster)
@@ -909,6 +922,7 @@ anon_status anon_autotune(anon_model* m, int32_t T, void* d_workspace, size_t ws
     for (int j = 1; j < NG; ++j)
       if (gbest[j] < gbest[gsel] * (gsel == 0 ? 0.99f : 1.0f)) gsel = j;
     m->gemm_gm[gi] = kGroups[gsel];
+    m->groups_tuned = true;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

@@ -196,3 +196,42 @@ def test_a_launch_of_too_many_threads_takes_another_tile(torch_dev):
     chosen, ms = m.autotune(T, torch.empty(n, dtype=torch.uint8, device="cuda"), n)
     assert ms[2][small] < 0 and chosen[2] != small
     m.close()
+
+
+def test_tiles_tuned_on_a_few_rows_or_many_serve_other_sizes(torch_dev):
+    """A model tuned on one batch size runs others on tiles chosen by rows: the
+    same bits, and hardly slower than a model that was not tuned.  Tiles that the
+    caller sets hold for every size."""
+    import torch
+    from paper_2606_15650_amd.pipeline import Pipeline
+    from tests.test_gpu_empty_records import _us
+    cfg = replace(BASE, n_layers=1, vocab=500)
+    _, m = make_model(cfg, "bf16", 0)
+    pl = Pipeline(m)
+
+    def batch(T):
+        L = _lengths(T)
+        cu = np.concatenate([[0], np.cumsum(L)]).astype(np.int32)
+
+        class Batch:
+            B, h_cu = len(L), cu
+        Batch.T = T
+        Batch.ids = torch.from_numpy(np.random.default_rng(T).integers(0, cfg.vocab, T).astype(np.int32)).cuda()
+        Batch.cu = torch.from_numpy(cu).cuda()
+        return Batch
+    batches = {T: batch(T) for T in (137, 3000, 60000)}
+    want = {T: pl.hidden(b, 1).clone() for T, b in batches.items()}
+    free = {T: _us(lambda b=b: pl.ner(b)) for T, b in batches.items()}
+    for tuned in (137, 60000):
+        chosen, _ = pl.autotune(tuned)
+        assert list(m.get_tiles()[0]) == list(chosen)
+        for T, b in batches.items():
+            us = _us(lambda: pl.ner(b))
+            say(f"[gemm] tuned on {tuned} rows, {T}: {us:.1f} us, not tuned {free[T]:.1f} us")
+            assert torch.equal(pl.hidden(b, 1), want[T])
+            assert us < 1.3 * free[T] + 10
+    m.set_tiles([11] * 4)
+    wide = _us(lambda: pl.ner(batches[137]))
+    say(f"[gemm] 256x256 tiles set, 137: {wide:.1f} us")
+    assert wide > 1.3 * free[137] and torch.equal(pl.hidden(batches[137], 1), want[137])
+    m.close()
