@@ -201,8 +201,9 @@ void anon_graph_free(anon_graph* graph);
  * the same MFMA sequence in the same K order, so tuning never changes
  * results.
  *   chosen:   [4] picked configuration per GEMM, or NULL
- *   times_ms: [4 * max_configs] mean time per configuration (-1: does not
- *             fit the shape), or NULL
+ *   times_ms: [4 * max_configs] mean time per configuration (of one launch
+ *             where it is far from the fastest; -1: does not fit the shape),
+ *             or NULL
  * Synchronises the stream. */
 anon_status anon_autotune(anon_model* model, int32_t T, void* d_workspace, size_t ws_bytes, void* stream,
                           int32_t* chosen, float* times_ms, int32_t max_configs);

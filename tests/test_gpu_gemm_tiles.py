@@ -235,3 +235,28 @@ def test_tiles_tuned_on_a_few_rows_or_many_serve_other_sizes(torch_dev):
     say(f"[gemm] 256x256 tiles set, 137: {wide:.1f} us")
     assert wide > 1.3 * free[137] and torch.equal(pl.hidden(batches[137], 1), want[137])
     m.close()
+
+
+def test_autotuning_many_rows_leaves_tiles_for_few_rows(torch_dev):
+    """Tiles that are far from the fastest are not timed in full: tuning takes
+    less than 350 launches of the chosen tiles (ten of each of the twelve tiles
+    for many rows, and of six orders, are 237; of all 23 tiles 570)."""
+    import time
+
+    import torch
+    cfg = replace(BASE, n_layers=1, vocab=500)
+    _, m = make_model(cfg, "bf16", 0)
+    T = 60000
+    n = m.workspace_size(T, 1)
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    m.autotune(T, ws, n)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    chosen, ms = m.autotune(T, ws, n)
+    torch.cuda.synchronize()
+    took = (time.perf_counter() - t0) * 1e3
+    best = sum(float(ms[g][chosen[g]]) for g in range(4))
+    say(f"[gemm] tuning on {T} rows {took:.0f} ms, {took / best:.0f} launches of the chosen tiles")
+    assert all(float(ms[g][chosen[g]]) <= min(float(x) for x in ms[g] if x > 0) * 1.05 for g in range(4))
+    assert took < 350 * best
+    m.close()
