@@ -19,8 +19,8 @@
 // Bound by instructions (three quarters of the match's time is vector issue):
 // one read of the text and 16 bytes per field, where a thread per byte read
 // three bytes each, wrote an int flag, scanned the flags in three kernels and
-// tested every line a second time.  128 MB in 16,384 records: 4.8 ms -> 0.12
-// ms, 95 us of it the match (16 bytes a thread, lines taken where they began
+// tested every line a second time.  128 MB in 16,384 records: 4.8 ms -> 0.11
+// ms, 91 us of it the match (16 bytes a thread, lines taken where they began
 // and every name compared in full: 215).
 #include <algorithm>
 

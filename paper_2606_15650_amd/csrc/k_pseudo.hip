@@ -231,7 +231,8 @@ __device__ __forceinline__ void load_entity(const uint8_t* text, int64_t at, int
 }
 
 // 64-bit mix of the entity's dwords and length (table position and first
-// comparison only; equal bytes are compared in full).
+// comparison only; equal bytes are compared in full).  The multipliers are
+// those of MurmurHash3's 64-bit finalizer (A. Appleby, public domain).
 __device__ __forceinline__ uint64_t fingerprint(const uint32_t (&m)[kMsgWords], int len) {
   uint64_t h = 0x9e3779b97f4a7c15ull * (uint64_t)(len + 1);
 #pragma unroll
@@ -390,9 +391,9 @@ __global__ __launch_bounds__(256) void ps_layout_kernel(PcacheDev pc, const int6
 // for new entities by fences: a slot's state carries 30 bits of its
 // fingerprint, so that only a slot that is nearly surely the entity's is read
 // behind a fence or waited for.  us per call, cold being a first meeting:
-//   139,000 spans of 359 entities in 128 MB: 49, cold 131 (a thread per
+//   139,000 spans of 359 entities in 128 MB: 46, cold 131 (a thread per
 //     span, bytewise: 160, 265)
-//   120,000 spans, nearly all of an entity each: cold 130 (every occupied slot
+//   120,000 spans, nearly all of an entity each: cold 120 (every occupied slot
 //     behind a fence, every slot being written waited for: 396; neither
 //     waiting nor tags: 167)
 // Three waves a SIMD, and one copy of the compression for an entity's blocks

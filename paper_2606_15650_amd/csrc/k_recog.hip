@@ -46,7 +46,7 @@
 // bit of bitmap traffic, where per-byte counters, flags, keys and their
 // three-kernel scans moved about 140 bytes of memory per text byte over 20
 // launches.  4.9 MB of text with its NER spans in 4096 records: 467 ->
-// 38 us (the rules 23).
+// 35 us (the rules 22).
 #include "kernels.hpp"
 #include "text_words.hpp"
 
@@ -355,7 +355,7 @@ __device__ __forceinline__ unsigned long long span_key(int len, int prio, int lo
 }
 
 // Record b's bytes, clamped to the text [0, n) (a malformed cu_bytes is
-// flagged by rx_check_kernel and cannot send a read outside the text).
+// flagged by rx_init_kernel and cannot send a read outside the text).
 __device__ __forceinline__ void record_bounds(const int64_t* cu, int b, int64_t n, int& lo, int& hi) {
   const int64_t l = min(max(cu[b], (int64_t)0), n);
   lo = (int)l;

@@ -142,8 +142,9 @@ __device__ __forceinline__ void ln_store(float (&v)[NPL], const float (&gv)[NPL]
 
 // A wave takes one token: its table row is requested before its record is
 // looked for, by the whole wave.  Bound by the gathered table rows and the
-// output: 855,000 rows of 768, 802 -> 696 us (5.6 TB/s); two or four rows a
-// wave, with one search, took 754 and 891.
+// output: 874,505 rows of 768, ids spread over 30,522, 841 -> 660 us against a
+// search by each lane ahead of the row (6.1 TB/s); two or four rows a wave,
+// with one search, were 8 and 28% slower than one.
 template <int NPL>
 __global__ __launch_bounds__(256) void embed_ln_kernel(const int* __restrict__ ids, const int* __restrict__ cu,
                                                        int B, int T_cap, const float* __restrict__ tok,

@@ -10,11 +10,11 @@
 // record (labels staged in LDS) to find the span's last token.  Every token
 // is visited by at most one walk, so the work is O(T).
 //
-// Bound by latency and launches: a call moves 1.5 bytes per token beyond the
-// spans themselves (labels read twice, a quarter byte of flags and ranks),
-// and takes two launches where an int flag per token, a three-kernel scan of
-// them and a record search per labelled token took six.  978,000 tokens in
-// 4096 records: 38 -> 14 us (6 and 8 in the two kernels).
+// Bound by latency and launches: a call moves 2.5 bytes per token beyond the
+// spans themselves (labels read twice, a quarter byte of flags and ranks
+// written and read), and takes two launches where an int flag per token, a
+// three-kernel scan of them and a record search per labelled token took six.
+// 978,000 tokens in 4096 records: 38 -> 11.5 us (6 in each kernel).
 #include "kernels.hpp"
 
 namespace anon {

@@ -178,7 +178,8 @@ struct FieldTable {  // passed by value to the kernels
   int n;
 };
 // A 32-bit mix of a name's zero-padded dwords and length, by which the fields
-// a line could be are found.
+// a line could be are found (a multiplier of MurmurHash3's 32-bit finalizer,
+// A. Appleby, public domain, and the golden ratio's).
 __host__ __device__ inline uint32_t field_key(const uint32_t (&d)[kFieldNameMax / 4], int len) {
   uint32_t h = (uint32_t)len * 0x9e3779b1u;
   for (int i = 0; i < kFieldNameMax / 4; ++i) {
