@@ -490,8 +490,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, OCC) void gemm_kernel(DevParams p) {
 // of the base encoder (256x256x64): QKV 2.99 -> 2.79 ms, output projection
 // 1.17 -> 1.14, FFN1 4.76 -> 4.57, FFN2 3.64 -> 3.42 per launch; one tile
 // alone on the chip, K = 3072: 60.7 -> 54.2 us (a K tile 2690 -> 2380 clocks,
-// 2048 of them MFMA).  At full load the shader clock falls (QKV 1.75 GHz, output
-// projection 1.99, FFN1 1.88, FFN2 1.73) and a K tile takes 2400-2600 of its
+// 2048 of them MFMA).  At full load the shader clock falls (QKV 1.76 GHz, output
+// projection 1.96, FFN1 1.89, FFN2 1.74) and a K tile takes 2400-2600 of its
 // clocks, so the matrix pipe is 80-85% busy outside the epilogue.  What holds
 // the rest is not settled: a library's kernel does the output projection and
 // FFN2 shapes, without the residual, in 0.98 and 3.01 ms.  A layout of 4
